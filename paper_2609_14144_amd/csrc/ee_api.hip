@@ -40,6 +40,8 @@ struct ee_ctx {
   std::map<int, std::pair<void*, float*>> readout;
   ee::LayerW* d_layers = nullptr;
   std::vector<ee::LayerW> h_layers;   // the same pointers, host side (batched pass)
+  std::vector<ee::LayerT> tiled;      // bf16 weights: the batched pass's copies of the layers' matrices
+  std::set<const void*> untiled;      // matrices loaded since their copies were made
   ee::BatchBuffers bbuf{};            // batched full-depth pass (prompt, refresh)
   int prefill_chunk = -1;             // -1: batched in chunks of bbuf.max_positions; 0: one position per step
 
@@ -552,22 +554,28 @@ int load_one(ee_ctx* c, const ee_tensor& t) {
                           hipMemcpyDefault));
     } else if (leaf == "wq") {
       if ((r = need(A * D * H * es))) return r;
+      c->untiled.insert(qkv);
       if ((r = copy_rope_heads(c, qkv, src, static_cast<int>(A)))) return r;
     } else if (leaf == "wk") {
       if ((r = need(K * D * H * es))) return r;
+      c->untiled.insert(qkv);
       if ((r = copy_rope_heads(c, qkv + A * D * rb, src, static_cast<int>(K)))) return r;
     } else if (leaf == "wv") {
       if ((r = need(K * D * H * es))) return r;
+      c->untiled.insert(qkv);
       HIPCHK(c, hipMemcpy(qkv + (A + K) * D * rb, t.ptr, t.nbytes, hipMemcpyDefault));
     } else if (leaf == "wo") {
       if ((r = need(H * A * D * es))) return r;
+      c->untiled.insert(c->wo[l]);
       HIPCHK(c, hipMemcpy(c->wo[l], t.ptr, t.nbytes, hipMemcpyDefault));
     } else if (leaf == "w_gate" || leaf == "w_up") {
       if ((r = need(F * H * es))) return r;
+      c->untiled.insert(c->wgu[l]);
       char* dst = static_cast<char*>(c->wgu[l]) + (leaf == "w_up" ? rb : 0);
       if ((r = copy_rows(c, dst, 2 * rb, src, rb, rb, static_cast<size_t>(F)))) return r;
     } else if (leaf == "w_down") {
       if ((r = need(H * F * es))) return r;
+      c->untiled.insert(c->wd[l]);
       HIPCHK(c, hipMemcpy(c->wd[l], t.ptr, t.nbytes, hipMemcpyDefault));
     } else {
       return fail(c, EE_EINVAL, "unknown tensor " + name);
@@ -599,6 +607,27 @@ int load_one(ee_ctx* c, const ee_tensor& t) {
     return fail(c, EE_EINVAL, "unknown tensor " + name);
   }
   c->loaded.insert(name);
+  return EE_OK;
+}
+
+// Bring the tiled copies of the matrices loaded since the last call up to date.
+int tile_weights(ee_ctx* c) {
+  const ee_config& g = c->cfg;
+  const int H = g.hidden, AD = g.n_q_heads * g.head_dim, QKV = AD + 2 * g.n_kv_heads * g.head_dim, F = g.ffn;
+  if (c->wbf16) {
+    for (size_t l = 0; l < c->tiled.size(); ++l) {
+      const ee::LayerT& t = c->tiled[l];
+      const struct { const void* w; int n, k; void* t; } m[4] = {
+          {c->wqkv[l], QKV, H, t.wqkv}, {c->wo[l], H, AD, t.wo}, {c->wgu[l], 2 * F, H, t.wgu}, {c->wd[l], H, F, t.wd}};
+      for (const auto& x : m) {
+        if (!c->untiled.count(x.w)) continue;
+        const hipError_t e = ee::launch_tile_weights(x.w, x.n, x.k, x.t, c->stream);
+        if (e != hipSuccess) return hip_fail(c, e, "weight tiling launch");
+        c->untiled.erase(x.w);
+      }
+    }
+  }
+  c->untiled.clear();
   return EE_OK;
 }
 
@@ -667,6 +696,15 @@ static int create_body(ee_ctx* c, const ee_config* cfg, void* hip_stream, ee_ctx
     if ((r = dalloc(c, &c->wo[l], H * A * D * es))) return bail(r);
     if ((r = dalloc(c, &c->wgu[l], 2 * F * H * es))) return bail(r);
     if ((r = dalloc(c, &c->wd[l], H * F * es))) return bail(r);
+    if (c->wbf16) {
+      c->tiled.push_back(ee::LayerT{});
+      ee::LayerT& t = c->tiled.back();
+      if ((r = dalloc(c, &t.wqkv, ee::batch_weight_bytes(static_cast<int>((A + 2 * K) * D), static_cast<int>(H)))) ||
+          (r = dalloc(c, &t.wo, ee::batch_weight_bytes(static_cast<int>(H), static_cast<int>(A * D)))) ||
+          (r = dalloc(c, &t.wgu, ee::batch_weight_bytes(static_cast<int>(2 * F), static_cast<int>(H)))) ||
+          (r = dalloc(c, &t.wd, ee::batch_weight_bytes(static_cast<int>(H), static_cast<int>(F)))))
+        return bail(r);
+    }
     if ((r = dalloc(c, &c->g_attn[l], H * 4))) return bail(r);
     if ((r = dalloc(c, &c->g_mlp[l], H * 4))) return bail(r);
   }
@@ -728,7 +766,10 @@ static int create_body(ee_ctx* c, const ee_config* cfg, void* hip_stream, ee_ctx
     b.attn_ws_floats = std::min<size_t>(size_t(8) << 20, 16 * Pm * A * (D + 2));
     b.n_tile_ctr = ee::batch_tile_counters(static_cast<int>(Pm), static_cast<int>(nmax));
     if ((r = dalloc(c, &b.X, Pm * H * 4)) || (r = dalloc(c, &b.Q, Pm * A * D * 4)) ||
-        (r = dalloc(c, &b.O, Pm * A * D * 4)) || (r = dalloc(c, &b.Act, Pm * F * 4)) ||
+        (!c->wbf16 && ((r = dalloc(c, &b.O, Pm * A * D * 4)) || (r = dalloc(c, &b.Act, Pm * F * 4)))) ||
+        (c->wbf16 && ((r = dalloc(c, &b.Xp, ee::batch_plane_bytes(b.max_positions, static_cast<int>(H)))) ||
+                      (r = dalloc(c, &b.Op, ee::batch_plane_bytes(b.max_positions, static_cast<int>(A * D)))) ||
+                      (r = dalloc(c, &b.Ap, ee::batch_plane_bytes(b.max_positions, static_cast<int>(F)))))) ||
         (r = dalloc(c, &b.gemm_ws, b.gemm_ws_floats * 4)) || (r = dalloc(c, &b.attn_ws, b.attn_ws_floats * 4)) ||
         (r = dalloc(c, &b.tile_ctr, b.n_tile_ctr * 4)))
       return bail(r);
@@ -767,12 +808,16 @@ static int load_weights_impl(ee_ctx* c, const ee_tensor* tensors, int32_t n_tens
   c->err.clear();
   if (!tensors || n_tensors < 0) return fail(c, EE_EINVAL, "bad tensor list");
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  for (int i = 0; i < n_tensors; ++i) {
-    const int r = load_one(c, tensors[i]);
-    if (r) return r;
-  }
+  int r = EE_OK;
+  for (int i = 0; i < n_tensors && !r; ++i) r = load_one(c, tensors[i]);
+  // also after an error: the tensors before it are loaded. The copies into
+  // the weights ran on the null stream and are complete before the tiling.
   HIPCHK(c, hipDeviceSynchronize());
-  return EE_OK;
+  const std::string why = c->err;
+  const int t = tile_weights(c);
+  HIPCHK(c, hipDeviceSynchronize());
+  if (r) c->err = why;
+  return r ? r : t;
 }
 
 // Full depth over positions pos .. pos + n - 1 with device input tokens
@@ -785,6 +830,7 @@ static int batched_full_depth(ee_ctx* c, const int32_t* d_tokens, int n, bool he
   ee::BatchPass bp{};
   bp.p = make_params(c, INFINITY, 0);
   bp.layers = c->h_layers.data();
+  bp.tiled = c->wbf16 ? c->tiled.data() : nullptr;
   bp.buf = c->bbuf;
   if (c->prefill_chunk > 0) bp.buf.max_positions = std::min(c->prefill_chunk, c->bbuf.max_positions);
   bp.wbf16 = c->wbf16;
@@ -1243,6 +1289,12 @@ static void destroy_impl(ee_ctx* c) {
   for (void* p : c->wo) dfree(p);
   for (void* p : c->wgu) dfree(p);
   for (void* p : c->wd) dfree(p);
+  for (const ee::LayerT& t : c->tiled) {
+    dfree(t.wqkv);
+    dfree(t.wo);
+    dfree(t.wgu);
+    dfree(t.wd);
+  }
   for (float* p : c->g_attn) dfree(p);
   for (float* p : c->g_mlp) dfree(p);
   dfree(c->g_final);
@@ -1259,6 +1311,7 @@ static void destroy_impl(ee_ctx* c) {
   dfree(c->d_force_tok); dfree(c->d_force_exit); dfree(c->d_dbg_r); dfree(c->d_dbg_f);
   dfree(c->d_timeline);
   dfree(c->bbuf.X); dfree(c->bbuf.Q); dfree(c->bbuf.O); dfree(c->bbuf.Act);
+  dfree(c->bbuf.Xp); dfree(c->bbuf.Op); dfree(c->bbuf.Ap);
   dfree(c->bbuf.gemm_ws); dfree(c->bbuf.attn_ws); dfree(c->bbuf.tile_ctr);
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);

@@ -5,7 +5,7 @@
 // read once per chunk and the work is a tiled matrix product (positions x
 // weight rows) instead of matrix-vector products.
 //
-// Per layer, five launches (stream order is the only synchronisation):
+// Per layer (stream order is the only synchronisation):
 //   1. QKV:    Y = RMSNorm(X; g_attn) W_qkv^T, RoPE on q and k at each
 //              position, k and v stored to the paged cache, q kept;
 //   2. attn:   causal grouped-query attention of the chunk's queries over
@@ -15,10 +15,12 @@
 //   3. W_o:    X += O W_o^T;
 //   4. gate/up: A = SiLU(RMSNorm(X; g_mlp) W_g^T) * (RMSNorm(X; g_mlp) W_u^T);
 //   5. down:   X += A W_d^T.
-// The matrix products split K over several workgroups when the output tiles
-// alone do not fill the device; the last workgroup to finish a tile adds the
-// K-slices' partial sums in slice order and applies the epilogue, so every
-// result is independent of scheduling.
+// With bf16 weights the products run on the matrix cores (ee_mm.h): the
+// producer of each vector splits it into bf16 terms once, and the residual
+// products store the partial sums of their K slices, which the kernel that
+// prepares the next product's input adds up in slice order. With fp32 weights
+// the vector ALU computes them (k_bp_gemm), the last workgroup to finish a
+// tile adding its K slices. Every result is independent of scheduling.
 //
 // Numerics follow the decode program: weights as stored (bf16 or fp32),
 // activations and accumulation fp32, cache entries rounded to the storage
@@ -32,10 +34,9 @@
 #include <vector>
 
 #include "ee_internal.h"
+#include "ee_mm.h"
 
 namespace ee {
-
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -59,24 +60,6 @@ __device__ __forceinline__ float2 ld_agent2(const float* p) {
   return make_float2(__uint_as_float(static_cast<uint32_t>(v)), __uint_as_float(static_cast<uint32_t>(v >> 32)));
 }
 __device__ __forceinline__ void drain_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// Bounds-checked 16-byte loads without a branch: an out-of-range lane reads
-// from `safe` (any valid address) and its bits are masked to zero where the
-// value is consumed. A load inside a conditional, or selected against zero,
-// is compiled to a branch around the load, and the branch's join waits for
-// every outstanding load; masking at the load itself waits for the load
-// there. Either would serialise a ring of prefetches.
-template <typename T>
-__device__ __forceinline__ T ld_clamped(const T* p, const T* safe, bool ok) {
-  return *(ok ? p : safe);
-}
-template <typename T>
-__device__ __forceinline__ T zero_unless(T v, bool ok) {
-  static_assert(sizeof(T) == 16, "16-byte values");
-  u32x4 u = __builtin_bit_cast(u32x4, v);
-  u &= ok ? 0xffffffffu : 0u;
-  return __builtin_bit_cast(T, u);
-}
 
 __device__ __forceinline__ float exp_hw(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896341f); }
 
@@ -213,6 +196,8 @@ struct GemmArgs {
   uint32_t* tile_ctr;  // arrivals per output tile (zero before, reset by the last arrival)
   // epilogue targets
   float* Y;            // kEpiResid: X [P][N] (+=); kEpiSwiGlu: A [P][N/2]; kEpiQkv: q [P][A*D]
+  u32x4* planes;       // kEpiSwiGlu on the matrix cores: term planes of A, k32_out K blocks
+  int k32_out;
   // kEpiQkv: RoPE and cache
   int pos0, Aq, Kh, D;
   const float* rope_cos;
@@ -478,514 +463,121 @@ __global__ __launch_bounds__(256) void k_bp_gemm(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------------------
-// The same product for bf16 weights on the matrix cores
-// (v_mfma_f32_16x16x32_bf16): 16 weight rows x 16 positions per MFMA. The
-// weights are exact bf16 operands; every fp32 activation x (times its gain)
-// is split exactly into three bf16 terms t1 + t2 + t3 (t1 its top 16 bits,
-// t2 those of the remainder, t3 the rest, which fits in 8 significant bits),
-// and the three products accumulate in fp32, so the result carries fp32
-// accumulation error only, as the vector-ALU product does.
-// Block: 4 waves, each RB row blocks of 16 rows; CP column blocks of 16
-// positions; K in steps of 64. Lane l (row / position l % 16, group
-// g = l / 16) loads 32 contiguous bytes of its row, k0 + 16 g .. + 15 (four
-// lanes read a whole 128-byte line); the low half feeds one MFMA whose k
-// slots (g, j) are k0 + 16 g + j, the high half a second with k0 + 16 g + 8
-// + j, and the activation operands in LDS are laid out to match.
+// bf16 weights: the products of ee_mm.h, their epilogues, and what runs
+// between them
 // ---------------------------------------------------------------------------
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+// tiled copy of a row-major [N][K] matrix (K a multiple of 8), padded with zeros
+__global__ __launch_bounds__(256) void k_bp_tile_weights(const uint16_t* __restrict__ W, int N, int K, int k32,
+                                                         int64_t chunks, u32x4* __restrict__ T) {
+  for (int64_t c = blockIdx.x * 256ll + threadIdx.x; c < chunks; c += gridDim.x * 256ll) {
+    const int lane = static_cast<int>(c & 63);
+    const int64_t t = c >> 6;
+    const int64_t n = t / k32 * 16 + (lane & 15);
+    const int k = static_cast<int>(t % k32) * 32 + 8 * (lane >> 4);
+    T[c] = n < N && k < K ? *reinterpret_cast<const u32x4*>(W + n * K + k) : u32x4{0u, 0u, 0u, 0u};
+  }
+}
 
-__device__ __forceinline__ bf16x8 as_bf16x8(const uint4& u) { return __builtin_bit_cast(bf16x8, u); }
+// Epilogue targets of a product on the matrix cores (GemmArgs, with kEpiResid
+// storing its K slices' partial sums in g.part [split][P][N] for
+// k_bp_reduce_norm, and kEpiSwiGlu storing term planes).
+template <int EPI, int RB, int CP, int NW, int PF>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bp_mm(MmArgs m, GemmArgs g) {
+  mm_tile<RB, CP, NW, PF>(m, [&](int split, int p, int n, const f32x4& y) {
+    if (n >= m.N) return;
+    if constexpr (EPI == kEpiResid) {
+      *reinterpret_cast<f32x4*>(g.part + (static_cast<int64_t>(split) * m.P + p) * m.N + n) = y;
+    } else if constexpr (EPI == kEpiSwiGlu) {
+      // interleaved rows: n = 2j gate row j, n + 1 up row j
+      const float a0 = y[0] / (1.f + exp_hw(-y[0])) * y[1];
+      const float a1 = y[2] / (1.f + exp_hw(-y[2])) * y[3];
+      const int j = n >> 1;
+      uint32_t t[3];
+      mm_split2(a0, a1, t);
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+        *(reinterpret_cast<uint32_t*>(g.planes + mm_chunk(p, j & ~7, i, g.k32_out)) + ((j & 7) >> 1)) = t[i];
+    } else {
+      epi_pair<uint16_t>(g, EPI, p, n, y[0], y[1]);
+      epi_pair<uint16_t>(g, EPI, p, n + 2, y[2], y[3]);
+    }
+  });
+}
 
-// three bf16 terms of each of four floats: term t of element i in 16 bits
-__device__ __forceinline__ void split3(const float4& x, uint2* t) {
-  const float v[4] = {x.x, x.y, x.z, x.w};
-  uint32_t b[3][4];
+// The residual stream after a product, and the input of the next: X += the
+// product's K slices in slice order (splits may be 0), then, with a gain,
+// the term planes of x * rsqrt(mean(x^2) + eps) * gain. One workgroup per
+// position, thread = 8 elements (H <= 2048). The 16 positions of a block of
+// planes go to workgroups of one XCD, whose L2 then merges their 16-byte
+// pieces into whole lines. Bound by the reads of the slices.
+constexpr int kNormThreads = 256;
+__global__ __launch_bounds__(kNormThreads) void k_bp_reduce_norm(float* __restrict__ X, const float* __restrict__ part,
+                                                                 int splits, int P, int H,
+                                                                 const float* __restrict__ gain, float eps,
+                                                                 u32x4* __restrict__ planes, int k32) {
+  __shared__ float red[kNormThreads / 64];
+  const int b = blockIdx.x, loc = b >> 3;
+  const int p = ((loc >> 4) * 8 + (b & 7)) * 16 + (loc & 15);
+  if (p >= P) return;
+  const int k = 8 * threadIdx.x;
+  const bool on = k < H;
+  f32x4 x[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}}, gv[2];
+  f32x4* xp = reinterpret_cast<f32x4*>(X + static_cast<int64_t>(p) * H + k);
+  if (on) {
+    x[0] = xp[0];
+    x[1] = xp[1];
+    if (gain) {
+      gv[0] = reinterpret_cast<const f32x4*>(gain + k)[0];
+      gv[1] = reinterpret_cast<const f32x4*>(gain + k)[1];
+    }
+    // the slices' sum first, then the residual: groups of kSG slices with
+    // every load of a group in flight
+    if (splits > 0) {
+      constexpr int kSG = 8;
+      f32x4 y[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+      const int64_t PH = static_cast<int64_t>(P) * H;
+      const float* q = part + static_cast<int64_t>(p) * H + k;
+      for (int s0 = 0; s0 < splits; s0 += kSG) {
+        f32x4 v[kSG][2];
+#pragma unroll
+        for (int u = 0; u < kSG; ++u) {
+          const f32x4* r = reinterpret_cast<const f32x4*>(q + min(s0 + u, splits - 1) * PH);
+          v[u][0] = r[0];
+          v[u][1] = r[1];
+        }
+#pragma unroll
+        for (int u = 0; u < kSG; ++u)
+          if (s0 + u < splits) {
+            y[0] += v[u][0];
+            y[1] += v[u][1];
+          }
+      }
+      x[0] += y[0];
+      x[1] += y[1];
+      xp[0] = x[0];
+      xp[1] = x[1];
+    }
+  }
+  if (!gain) return;
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) ss = fmaf(x[i >> 2][i & 3], x[i >> 2][i & 3], ss);
+  ss = wave_sum64(ss);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  float t = 0.f;
+#pragma unroll
+  for (int w = 0; w < kNormThreads / 64; ++w) t += red[w];
+  const float r = rsqrtf(t / static_cast<float>(H) + eps);
+  if (!on) return;
+  uint32_t w[4][3];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const uint32_t u = __float_as_uint(v[i]);
-    const uint32_t h1 = u & 0xffff0000u;
-    const float r1 = v[i] - __uint_as_float(h1);
-    const uint32_t h2 = __float_as_uint(r1) & 0xffff0000u;
-    const float r2 = r1 - __uint_as_float(h2);
-    b[0][i] = h1 >> 16;
-    b[1][i] = h2 >> 16;
-    b[2][i] = __float_as_uint(r2) >> 16;  // exact: r2 has at most 8 significant bits
+    const int e = 2 * i;
+    mm_split2(x[e >> 2][e & 3] * r * gv[e >> 2][e & 3], x[e >> 2][(e & 3) + 1] * r * gv[e >> 2][(e & 3) + 1], w[i]);
   }
 #pragma unroll
-  for (int k = 0; k < 3; ++k) t[k] = make_uint2(b[k][0] | (b[k][1] << 16), b[k][2] | (b[k][3] << 16));
-}
-
-// A ring of PF steps of weight and activation loads is in flight; bounds are
-// applied without branches (an out-of-range lane reads a valid address and
-// is masked where consumed: a branch around a load makes its join wait for
-// every outstanding load), and the K-slice's RMSNorm gains are staged in LDS
-// once (a gain load per step would be waited for together with the ring).
-constexpr int kWideGainMax = 2048;  // longest K-slice of a normalised product on wide tiles
-
-template <int EPI, int RB, int CP, int PF>
-__global__ __launch_bounds__(256) void k_bp_gemm_mfma(GemmArgs g) {
-  constexpr int BN = 64 * RB, BP = 16 * CP, KS = 64;
-  constexpr int XCH = BP * KS / 4 / 256;  // float4 of activations per thread per step
-  // activation terms of one step, double buffered:
-  // [buf][term][column block][group][position][half] as 16-byte chunks
-  __shared__ uint4 Xs[2][3][CP][4][16][2];
-  __shared__ float ss_part[BP];
-  __shared__ int last_flag;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int lg = lane >> 4, lr = lane & 15;
-  const int n0 = blockIdx.x * BN, p0 = blockIdx.y * BP;
-  const int split = blockIdx.z, splits = gridDim.z;
-  const int kb = split * g.k_split, ke = min(g.K, kb + g.k_split);
-  const uint16_t* W = static_cast<const uint16_t*>(g.W);
-
-  constexpr int kGW = kWideGainMax / (4 * 256);  // gain float4s per thread
-  __shared__ float4 gsm[EPI != kEpiResid ? kWideGainMax / 4 : 1];
-  float4 gl[EPI != kEpiResid ? kGW : 1];
-  if constexpr (EPI != kEpiResid) {
-    const float4* g4 = reinterpret_cast<const float4*>(g.gain + kb);
-#pragma unroll
-    for (int j = 0; j < kGW; ++j) gl[j] = ld_clamped(g4 + tid + 256 * j, g4, 4 * (tid + 256 * j) < ke - kb);
-    asm volatile("" ::: "memory");  // issued before the ring's loads
-  }
-  float ssq[XCH];
-#pragma unroll
-  for (int i = 0; i < XCH; ++i) ssq[i] = 0.f;
-  const int nsteps = (ke - kb + KS - 1) / KS;
-  uint4 wq[PF][RB][2];
-  float4 xq[PF][XCH];
-  // loads of step st into ring slot `slot` (masked when consumed)
-  auto load = [&](int st, int slot) {
-    const bool sok = st < nsteps;
-    const int k0 = kb + st * KS;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const int n = n0 + (wave * RB + rb) * 16 + lr;
-      const int k = k0 + 16 * lg;
-      const uint4* src = reinterpret_cast<const uint4*>(W + static_cast<int64_t>(n) * g.K + k);
-      const uint4* w0 = reinterpret_cast<const uint4*>(W);
-      wq[slot][rb][0] = ld_clamped(src, w0, sok && n < g.N && k < ke);
-      wq[slot][rb][1] = ld_clamped(src + 1, w0, sok && n < g.N && k + 8 < ke);
-    }
-#pragma unroll
-    for (int i = 0; i < XCH; ++i) {
-      const int c = tid + 256 * i;
-      const int p = c >> 4, k = k0 + 4 * (c & 15);
-      xq[slot][i] = ld_clamped(reinterpret_cast<const float4*>(g.A + static_cast<int64_t>(p0 + p) * g.K + k),
-                               reinterpret_cast<const float4*>(g.A), sok && p0 + p < g.P && k < ke);
-    }
-  };
-  // step st's activations of ring slot `slot`: masked, normalised, split into
-  // three bf16 terms in LDS buffer buf
-  auto store_x = [&](int buf, int st, int slot) {
-    const int k0 = kb + st * KS;
-#pragma unroll
-    for (int i = 0; i < XCH; ++i) {
-      const int c = tid + 256 * i;
-      const int p = c >> 4, kq = c & 15, k = k0 + 4 * kq;
-      float4 a = zero_unless(xq[slot][i], p0 + p < g.P && k < ke);
-      if constexpr (EPI != kEpiResid) {
-        ssq[i] = fmaf(a.x, a.x, fmaf(a.y, a.y, fmaf(a.z, a.z, fmaf(a.w, a.w, ssq[i]))));
-        const float4 gg = gsm[min(k - kb, kWideGainMax - 4) / 4];
-        a.x *= gg.x; a.y *= gg.y; a.z *= gg.z; a.w *= gg.w;
-      }
-      uint2 t[3];
-      split3(a, t);
-      const int grp = kq >> 2, j0 = 4 * (kq & 3);  // k - k0 = 16 grp + j0
-#pragma unroll
-      for (int term = 0; term < 3; ++term) {
-        uint2* dst = reinterpret_cast<uint2*>(&Xs[buf][term][p >> 4][grp][p & 15][j0 >> 3]) + ((j0 >> 2) & 1);
-        *dst = t[term];
-      }
-    }
-  };
-
-  f32x4 acc[RB][CP];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int cp = 0; cp < CP; ++cp) acc[rb][cp] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  auto products = [&](int buf, const uint4 (&wc)[RB][2]) {
-#pragma unroll
-    for (int cp = 0; cp < CP; ++cp) {
-#pragma unroll
-      for (int term = 0; term < 3; ++term) {
-        const bf16x8 blo = as_bf16x8(Xs[buf][term][cp][lg][lr][0]);
-        const bf16x8 bhi = as_bf16x8(Xs[buf][term][cp][lg][lr][1]);
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          acc[rb][cp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wc[rb][0]), blo, acc[rb][cp], 0, 0, 0);
-          acc[rb][cp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wc[rb][1]), bhi, acc[rb][cp], 0, 0, 0);
-        }
-      }
-    }
-  };
-
-#pragma unroll
-  for (int i = 0; i < PF; ++i) load(i, i);
-  if constexpr (EPI != kEpiResid) {
-    asm volatile("" ::: "memory");  // the ring's loads all issued first
-    static_assert(kGW * 256 * 4 == kWideGainMax, "gain staging covers the LDS copy");
-#pragma unroll
-    for (int j = 0; j < kGW; ++j) gsm[tid + 256 * j] = gl[j];  // past the slice: valid gains of masked activations
-    __syncthreads();
-  }
-  int buf = 0;
-  for (int st0 = 0; st0 < nsteps; st0 += PF) {
-#pragma unroll
-    for (int i = 0; i < PF; ++i) {
-      const int st = st0 + i;
-      if (st >= nsteps) break;  // the same for every wave
-      store_x(buf, st, i);
-      __syncthreads();
-      const int k = kb + st * KS + 16 * lg;
-      uint4 wc[RB][2];
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const bool rok = n0 + (wave * RB + rb) * 16 + lr < g.N;
-        wc[rb][0] = zero_unless(wq[i][rb][0], rok && k < ke);
-        wc[rb][1] = zero_unless(wq[i][rb][1], rok && k + 8 < ke);
-      }
-      load(st + PF, i);  // refill the slot just read
-      products(buf, wc);
-      buf ^= 1;  // the other buffer is written next; this one is read until the barrier after that store
-    }
-  }
-
-  // per-position sums of squares of this K-slice: the 16 threads of a
-  // position are consecutive lanes
-  if (g.gain) {
-#pragma unroll
-    for (int i = 0; i < XCH; ++i) {
-      float v = ssq[i];
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o);
-      const int c = tid + 256 * i;
-      if ((c & 15) == 0) ss_part[c >> 4] = v;
-    }
-  }
-  __syncthreads();
-
-  // lane's outputs: rows n0 + (wave RB + rb) 16 + 4 lg + i (i < 4), position p0 + 16 cp + lr
-  const int64_t PN = static_cast<int64_t>(g.P) * g.N;
-  if (splits > 1) {
-    float* part = g.part + split * PN;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int cp = 0; cp < CP; ++cp) {
-        const int n = n0 + (wave * RB + rb) * 16 + 4 * lg, p = p0 + 16 * cp + lr;
-        if (n < g.N && p < g.P) {
-          float* d = part + static_cast<int64_t>(p) * g.N + n;
-          st_agent2(d, acc[rb][cp][0], acc[rb][cp][1]);
-          st_agent2(d + 2, acc[rb][cp][2], acc[rb][cp][3]);
-        }
-      }
-    if (g.gain && tid < BP && p0 + tid < g.P) st_agent(g.part + splits * PN + split * g.P + p0 + tid, ss_part[tid]);
-    drain_stores();
-    __syncthreads();
-    if (tid == 0) {
-      uint32_t* ctr = g.tile_ctr + blockIdx.y * gridDim.x + blockIdx.x;
-      const uint32_t old = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last_flag = old == static_cast<uint32_t>(splits - 1);
-      if (last_flag) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    if (!last_flag) return;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int cp = 0; cp < CP; ++cp) acc[rb][cp] = f32x4{0.f, 0.f, 0.f, 0.f};
-    constexpr int kSG = (RB * CP >= 4) ? 1 : 16;  // slices with loads in flight together
-    for (int s0 = 0; s0 < splits; s0 += kSG) {
-      float2 v[kSG][RB][CP][2];
-#pragma unroll
-      for (int u = 0; u < kSG; ++u)
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-          for (int cp = 0; cp < CP; ++cp) {
-            const int n = n0 + (wave * RB + rb) * 16 + 4 * lg, p = p0 + 16 * cp + lr;
-            const bool ok = s0 + u < splits && n < g.N && p < g.P;
-            const float* d = g.part + (s0 + u) * PN + static_cast<int64_t>(p) * g.N + n;
-            v[u][rb][cp][0] = ok ? ld_agent2(d) : make_float2(0.f, 0.f);
-            v[u][rb][cp][1] = ok ? ld_agent2(d + 2) : make_float2(0.f, 0.f);
-          }
-#pragma unroll
-      for (int u = 0; u < kSG; ++u)
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-          for (int cp = 0; cp < CP; ++cp) {
-            acc[rb][cp][0] += v[u][rb][cp][0].x;
-            acc[rb][cp][1] += v[u][rb][cp][0].y;
-            acc[rb][cp][2] += v[u][rb][cp][1].x;
-            acc[rb][cp][3] += v[u][rb][cp][1].y;
-          }
-    }
-    if (g.gain && tid < BP && p0 + tid < g.P) {
-      float t = 0.f;
-      for (int s0 = 0; s0 < splits; s0 += 8) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          v[u] = s0 + u < splits ? ld_agent(g.part + splits * PN + (s0 + u) * g.P + p0 + tid) : 0.f;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) t += v[u];
-      }
-      ss_part[tid] = t;
-    }
-    __syncthreads();
-  }
-
-#pragma unroll
-  for (int cp = 0; cp < CP; ++cp) {
-    const int pl = 16 * cp + lr, p = p0 + pl;
-    if (p >= g.P) continue;
-    const float rinv = g.gain ? rsqrtf(ss_part[pl] / static_cast<float>(g.K) + g.eps) : 1.f;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const int n = n0 + (wave * RB + rb) * 16 + 4 * lg;
-      if (n < g.N) epi_pair<uint16_t>(g, EPI, p, n, acc[rb][cp][0] * rinv, acc[rb][cp][1] * rinv);
-      if (n + 2 < g.N) epi_pair<uint16_t>(g, EPI, p, n + 2, acc[rb][cp][2] * rinv, acc[rb][cp][3] * rinv);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Few positions (P <= 16) on the matrix cores: a workgroup owns RB x 16
-// weight rows and all 16 positions over one K-slice (blockIdx.y of
-// gridDim.y), its NW waves split the slice into contiguous ranges of 64-wide
-// steps, and the waves' sums meet in LDS in wave order. Lane l (row /
-// position l % 16, group l / 16) loads its own operands straight into
-// registers: 32 bytes of its weight row and 16 activations of its position,
-// the same k range k0 + 16 (l / 16) .. + 15 as above (the slice's RMSNorm
-// gains come from LDS); a ring of PF steps is in flight. With several slices
-// the last workgroup of a tile to arrive adds the slices' sums (and sums of
-// squares) in slice order.
-// ---------------------------------------------------------------------------
-constexpr int kNarrowGainMax = 4096;  // longest K-slice of a normalised product on narrow tiles
-
-template <int EPI, int RB, int NW, int PF>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bp_gemm_narrow(GemmArgs g) {
-  constexpr int KS = 64;
-  constexpr bool kGain = EPI != kEpiResid;  // the gated products normalise their input
-  constexpr int kGQ = kNarrowGainMax / (4 * NW * 64);  // gain float4s per thread
-  __shared__ f32x4 red[NW][RB][64];
-  __shared__ float ssr[NW][64];
-  __shared__ float4 gs[kGain ? kNarrowGainMax / 4 : 1];  // the slice's RMSNorm gains
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lg = lane >> 4, lr = lane & 15;
-  const int n0 = blockIdx.x * 16 * RB;
-  const int split = blockIdx.y, splits = gridDim.y;
-  const int kb = split * g.k_split, ke = min(g.K, kb + g.k_split);
-  const int nsteps = (ke - kb + KS - 1) / KS;
-  const int s0 = nsteps * wave / NW, s1 = nsteps * (wave + 1) / NW;
-  // every wave runs the same number of ring turns (steps at or past s1
-  // read a valid address and are masked to zero), so that the loop body
-  // has no branch: a branch around a load makes its join wait for every
-  // outstanding load
-  const int turns = ((nsteps + NW - 1) / NW + PF - 1) / PF;
-  const bool pok = lr < g.P;
-  const uint16_t* W = static_cast<const uint16_t*>(g.W);
-  const float* xrow = g.A + static_cast<int64_t>(lr) * g.K;
-
-  // the slice's gains go through LDS (they are the same for every row and
-  // position); their loads are issued ahead of the weight ring's
-  float4 gl[kGain ? kGQ : 1];
-  if constexpr (kGain) {
-    const float4* g4 = reinterpret_cast<const float4*>(g.gain + kb);
-#pragma unroll
-    for (int j = 0; j < kGQ; ++j) {
-      const int c = tid + NW * 64 * j;
-      gl[j] = ld_clamped(g4 + c, g4, 4 * c < ke - kb);
-    }
-    // issued before the weight loads (the vector-memory counter is in
-    // order), so their LDS copy below waits for them alone
-    asm volatile("" ::: "memory");
-  }
-  uint4 wr[PF][RB][2];
-  float4 xr[PF][4];
-  // loads of step st into ring slot `slot`, out-of-range parts masked when
-  // the slot is consumed
-  auto load = [&](int st, int slot) {
-    const bool sok = st < s1;
-    const int k = kb + st * KS + 16 * lg;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const int row = n0 + rb * 16 + lr;
-      const uint4* src = reinterpret_cast<const uint4*>(W + static_cast<int64_t>(row) * g.K + k);
-      const uint4* w0 = reinterpret_cast<const uint4*>(W);
-      wr[slot][rb][0] = ld_clamped(src, w0, sok && row < g.N && k < ke);
-      wr[slot][rb][1] = ld_clamped(src + 1, w0, sok && row < g.N && k + 8 < ke);
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      xr[slot][q] = ld_clamped(reinterpret_cast<const float4*>(xrow + k + 4 * q),
-                               reinterpret_cast<const float4*>(g.A), sok && pok && k + 4 * q < ke);
-  };
-  f32x4 acc[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float ssq = 0.f;
-#pragma unroll
-  for (int i = 0; i < PF; ++i) load(s0 + i, i);
-  if constexpr (kGain) {
-    asm volatile("" ::: "memory");  // the ring's loads all issued first
-    static_assert(kGQ * NW * 64 * 4 == kNarrowGainMax, "gain staging covers the LDS copy");
-#pragma unroll
-    for (int j = 0; j < kGQ; ++j) {
-      const int c = tid + NW * 64 * j;
-      gs[c] = gl[j];  // past the slice: a valid gain, multiplying masked (zero) activations
-    }
-    __syncthreads();
-  }
-  for (int turn = 0; turn < turns; ++turn) {
-    const int st0 = s0 + turn * PF;
-#pragma unroll
-    for (int i = 0; i < PF; ++i) {
-      {
-        const int st = st0 + i;
-        const bool sok = st < s1;
-        const int k = kb + st * KS + 16 * lg;
-        float4 x[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          x[q] = zero_unless(xr[i][q], sok && pok && k + 4 * q < ke);
-          if constexpr (kGain) {
-            const float4 gq = gs[min((k - kb) / 4 + q, kNarrowGainMax / 4 - 1)];
-            ssq = fmaf(x[q].x, x[q].x, fmaf(x[q].y, x[q].y, fmaf(x[q].z, x[q].z, fmaf(x[q].w, x[q].w, ssq))));
-            x[q].x *= gq.x; x[q].y *= gq.y; x[q].z *= gq.z; x[q].w *= gq.w;
-          }
-        }
-        // three bf16 terms of the low (k .. k + 7) and high (k + 8 .. + 15) halves
-        uint2 t[4][3];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) split3(x[q], t[q]);
-        uint4 wc[RB][2];
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          const bool rok = n0 + rb * 16 + lr < g.N;
-          wc[rb][0] = zero_unless(wr[i][rb][0], sok && rok && k < ke);
-          wc[rb][1] = zero_unless(wr[i][rb][1], sok && rok && k + 8 < ke);
-        }
-        load(st + PF, i);  // refill the slot just read
-#pragma unroll
-        for (int term = 0; term < 3; ++term) {
-          const uint4 blo = make_uint4(t[0][term].x, t[0][term].y, t[1][term].x, t[1][term].y);
-          const uint4 bhi = make_uint4(t[2][term].x, t[2][term].y, t[3][term].x, t[3][term].y);
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb) {
-            acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wc[rb][0]), as_bf16x8(blo), acc[rb], 0, 0, 0);
-            acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wc[rb][1]), as_bf16x8(bhi), acc[rb], 0, 0, 0);
-          }
-        }
-      }
-    }
-  }
-  // The tile's outputs in units of two: unit u = (row block u / 2, half
-  // u % 2 of each lane's four rows), lane (lg, lr) holding rows
-  // n0 + 16 (u / 2) + 4 lg + 2 (u % 2) + {0, 1} of position lr. Wave w sums
-  // units w, w + NW, ... over the waves' partial products (in wave order)
-  // and, with several K-slices, stores them, and the last workgroup of the
-  // tile to arrive merges every slice of every unit with all of its loads in
-  // flight at once.
-  constexpr int NU = 2 * RB, UPW = (NU + NW - 1) / NW;
-  __shared__ int last_flag;
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) red[wave][rb][lane] = acc[rb];
-  ssr[wave][lane] = ssq;
-  __syncthreads();
-  float2 y[UPW];
-#pragma unroll
-  for (int j = 0; j < UPW; ++j) {
-    const int u = wave + NW * j;
-    y[j] = make_float2(0.f, 0.f);
-    if (u < NU) {
-      const int rb = u >> 1, c = 2 * (u & 1);
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        y[j].x += red[w][rb][lane][c];
-        y[j].y += red[w][rb][lane][c + 1];
-      }
-    }
-  }
-  // position lr's sum of squares over the slice: the four lane groups of
-  // every wave
-  float t = 0.f;
-  if constexpr (kGain) {
-#pragma unroll
-    for (int w = 0; w < NW; ++w)
-      t += (ssr[w][lr] + ssr[w][lr + 16]) + (ssr[w][lr + 32] + ssr[w][lr + 48]);
-  }
-  auto unit_n = [&](int j) { const int u = wave + NW * j; return n0 + 16 * (u >> 1) + 4 * lg + 2 * (u & 1); };
-  auto unit_ok = [&](int j) { return wave + NW * j < NU && unit_n(j) < g.N && pok; };
-  // the residual rows the epilogue adds to, requested before any wait
-  float2 xold[EPI == kEpiResid ? UPW : 1];
-  if constexpr (EPI == kEpiResid) {
-#pragma unroll
-    for (int j = 0; j < UPW; ++j) {
-      const float2* xp = reinterpret_cast<const float2*>(g.Y + static_cast<int64_t>(lr) * g.N + unit_n(j));
-      xold[j] = unit_ok(j) ? *xp : make_float2(0.f, 0.f);
-    }
-  }
-  if (splits > 1) {
-    const int64_t PN = static_cast<int64_t>(g.P) * g.N;
-#pragma unroll
-    for (int j = 0; j < UPW; ++j)
-      if (unit_ok(j)) st_agent2(g.part + split * PN + static_cast<int64_t>(lr) * g.N + unit_n(j), y[j].x, y[j].y);
-    if (kGain && wave == 0 && lg == 0 && pok) st_agent(g.part + splits * PN + split * g.P + lr, t);
-    drain_stores();
-    __syncthreads();  // every wave's partial sums stored
-    if (tid == 0) {
-      uint32_t* ctr = g.tile_ctr + blockIdx.x;
-      const uint32_t old = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last_flag = old == static_cast<uint32_t>(splits - 1);
-      if (last_flag) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    if (!last_flag) return;
-    constexpr int kSG = 16;  // slices with loads in flight together
-#pragma unroll
-    for (int j = 0; j < UPW; ++j) y[j] = make_float2(0.f, 0.f);
-    t = 0.f;
-    for (int q0 = 0; q0 < splits; q0 += kSG) {
-      float2 v[UPW][kSG];
-      float vs[kSG];
-#pragma unroll
-      for (int u = 0; u < kSG; ++u) {
-#pragma unroll
-        for (int j = 0; j < UPW; ++j) {
-          const float* d = g.part + (q0 + u) * PN + static_cast<int64_t>(lr) * g.N + unit_n(j);
-          v[j][u] = (unit_ok(j) && q0 + u < splits) ? ld_agent2(d) : make_float2(0.f, 0.f);
-        }
-        vs[u] = (kGain && pok && q0 + u < splits) ? ld_agent(g.part + splits * PN + (q0 + u) * g.P + lr) : 0.f;
-      }
-#pragma unroll
-      for (int u = 0; u < kSG; ++u) {
-#pragma unroll
-        for (int j = 0; j < UPW; ++j) {
-          y[j].x += v[j][u].x;
-          y[j].y += v[j][u].y;
-        }
-        t += vs[u];
-      }
-    }
-  }
-  const float rinv = kGain ? rsqrtf(t / static_cast<float>(g.K) + g.eps) : 1.f;
-#pragma unroll
-  for (int j = 0; j < UPW; ++j) {
-    if (!unit_ok(j)) continue;
-    const int n = unit_n(j);
-    if constexpr (EPI == kEpiResid) {
-      *reinterpret_cast<float2*>(g.Y + static_cast<int64_t>(lr) * g.N + n) =
-          make_float2(xold[j].x + y[j].x, xold[j].y + y[j].y);
-    } else {
-      epi_pair<uint16_t>(g, EPI, lr, n, y[j].x * rinv, y[j].y * rinv);
-    }
-  }
+  for (int i = 0; i < 3; ++i) planes[mm_chunk(p, k, i, k32)] = u32x4{w[0][i], w[1][i], w[2][i], w[3][i]};
 }
 
 // ---------------------------------------------------------------------------
@@ -999,7 +591,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // ---------------------------------------------------------------------------
 struct AttnArgs {
   const float* Q;      // [P][A*D], pair-interleaved within heads (as the cached keys)
-  float* O;            // [P][A*D], natural order
+  float* O;            // [P][A*D], natural order (fp32 weights), or
+  u32x4* planes;       // its term planes (bf16 weights), k32 K blocks
+  int k32;
   float* part;         // [P][A][nsplit][D + 2]
   const void* kpool;
   const void* vpool;
@@ -1012,6 +606,24 @@ struct AttnArgs {
 };
 
 constexpr int kKT = 64;  // keys per LDS tile
+
+// DPL neighbouring elements (element e of query qi, e even for DPL = 2) of the attention output
+template <typename WT, int DPL>
+__device__ __forceinline__ void attn_store(const AttnArgs& a, int qi, int e, const float (&o)[DPL]) {
+  if constexpr (sizeof(WT) == 4) {
+#pragma unroll
+    for (int i = 0; i < DPL; ++i) a.O[static_cast<int64_t>(qi) * a.A * a.D + e + i] = o[i];
+  } else {
+    uint32_t t[3];
+    mm_split2(o[0], DPL == 2 ? o[DPL - 1] : 0.f, t);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      uint16_t* c = reinterpret_cast<uint16_t*>(a.planes + mm_chunk(qi, e & ~7, i, a.k32)) + (e & 7);
+      if constexpr (DPL == 2) *reinterpret_cast<uint32_t*>(c) = t[i];
+      else *c = static_cast<uint16_t>(t[i]);
+    }
+  }
+}
 
 // Block = (KV head, tile of QT query positions, key split); wave w takes
 // query position w % QT and the GW query heads (w / QT) GW .. + GW - 1 of the
@@ -1178,8 +790,8 @@ __attribute__((amdgpu_waves_per_eu(sizeof(WT) == 4 ? 1 : ((QT * (G / GW) + 3) / 
     if (a.nsplit == 1) {
       const float inv = 1.f / l_run[h];
 #pragma unroll
-      for (int e = 0; e < DPL; ++e)
-        a.O[static_cast<int64_t>(qi) * a.A * D + head * D + DPL * lane + e] = acc[h][e] * inv;
+      for (int e = 0; e < DPL; ++e) acc[h][e] *= inv;
+      attn_store<WT, DPL>(a, qi, head * D + DPL * lane, acc[h]);
     } else {
       float* r = a.part + ((static_cast<int64_t>(qi) * a.A + head) * a.nsplit + sp) * (D + 2);
 #pragma unroll
@@ -1193,7 +805,7 @@ __attribute__((amdgpu_waves_per_eu(sizeof(WT) == 4 ? 1 : ((QT * (G / GW) + 3) / 
 }
 
 // one wave per (query, head): the splits' partial records in split order
-template <int D>
+template <typename WT, int D>
 __global__ __launch_bounds__(256) void k_bp_attn_merge(AttnArgs a) {
   constexpr int DPL = D / 64;
   const int w = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -1239,7 +851,8 @@ __global__ __launch_bounds__(256) void k_bp_attn_merge(AttnArgs a) {
   const int qi = w / a.A, head = w - qi * a.A;
   const float inv = 1.f / den;
 #pragma unroll
-  for (int e = 0; e < DPL; ++e) a.O[static_cast<int64_t>(qi) * a.A * D + head * D + DPL * lane + e] = num[e] * inv;
+  for (int e = 0; e < DPL; ++e) num[e] *= inv;
+  attn_store<WT, DPL>(a, qi, head * D + DPL * lane, num);
 }
 
 // ---------------------------------------------------------------------------
@@ -1270,99 +883,11 @@ void choose_split(int tiles, int P, int N, int K, int BK, size_t ws_floats, int 
   *splits = (K + ks - 1) / ks;
 }
 
-template <int EPI, int RB, int CP, int PF>
-hipError_t gemm_mfma(GemmArgs g, const BatchBuffers& b, int n_cu, int wgs_per_cu, hipStream_t s) {
-  constexpr int BN = 64 * RB, BP = 16 * CP;
-  const int tiles = ((g.N + BN - 1) / BN) * ((g.P + BP - 1) / BP);
-  if (static_cast<size_t>(tiles) > b.n_tile_ctr) return hipErrorInvalidValue;
-  int splits;
-  choose_split(tiles, g.P, g.N, g.K, 64, b.gemm_ws_floats, wgs_per_cu, n_cu, &g.k_split, &splits,
-               EPI != kEpiResid ? kWideGainMax : (1 << 30));
-  if (EPI != kEpiResid && g.k_split > kWideGainMax) return hipErrorInvalidValue;  // gains staged in LDS
-  hipLaunchKernelGGL((k_bp_gemm_mfma<EPI, RB, CP, PF>), dim3((g.N + BN - 1) / BN, (g.P + BP - 1) / BP, splits),
-                     dim3(256), 0, s, g);
-  return hipGetLastError();
-}
-
-// Narrow tiles for at most 16 positions: RB x 16 rows by NW waves, which
-// split each K-slice into contiguous ranges of 64-wide steps. K is split over
-// workgroups where the tiles alone leave units idle: tiles times slices stay
-// within one round of the units' slots (eight waves per unit), with at least
-// two steps per wave.
-constexpr int64_t kSliceMergeBytes = 72 << 10;
-
-struct NarrowPlan {
-  int tiles, splits, k_split;
-  int64_t busiest;  // bytes the busiest unit loads (bf16 weights and 16 fp32 activation rows)
-};
-NarrowPlan narrow_plan(int EPI, int RB, int NW, const GemmArgs& g, size_t ws_floats, int n_cu,
-                       bool whole_k = false) {
-  NarrowPlan q;
-  q.tiles = (g.N + 16 * RB - 1) / (16 * RB);
-  const int slots = n_cu * (8 / NW);
-  int splits = whole_k ? 1 : std::max(1, std::min(slots / q.tiles, (g.K + 64 * 2 * NW - 1) / (64 * 2 * NW)));
-  if (EPI != kEpiResid) splits = std::max(splits, (g.K + kNarrowGainMax - 1) / kNarrowGainMax);
-  const size_t per = static_cast<size_t>(g.P) * g.N + g.P;
-  splits = static_cast<int>(std::min<size_t>(splits, std::max<size_t>(1, ws_floats / per)));
-  q.k_split = ((g.K + splits - 1) / splits + 63) / 64 * 64;
-  q.splits = (g.K + q.k_split - 1) / q.k_split;
-  const int64_t wgs = static_cast<int64_t>(q.tiles) * q.splits;
-  q.busiest = (wgs + n_cu - 1) / n_cu * static_cast<int64_t>(q.k_split) * (32 * RB + 64);
-  // a K-slice merge (partial stores, their drain, the arrival count, the
-  // slices' loads: ~3 us) costs about what a unit loads in that time
-  if (q.splits > 1) q.busiest += kSliceMergeBytes;
-  return q;
-}
-
-template <int EPI, int RB, int NW, int PF>
-hipError_t gemm_narrow(GemmArgs g, const BatchBuffers& b, int n_cu, hipStream_t s, bool whole_k = false) {
-  const NarrowPlan q = narrow_plan(EPI, RB, NW, g, b.gemm_ws_floats, n_cu, whole_k);
-  if (static_cast<size_t>(q.tiles) > b.n_tile_ctr) return hipErrorInvalidValue;
-  if (EPI != kEpiResid && q.k_split > kNarrowGainMax) return hipErrorInvalidValue;
-  g.k_split = q.k_split;
-  hipLaunchKernelGGL((k_bp_gemm_narrow<EPI, RB, NW, PF>), dim3(q.tiles, q.splits), dim3(NW * 64), 0, s, g);
-  return hipGetLastError();
-}
-
+// fp32 weights
 template <typename WT, int EPI>
 hipError_t gemm(const GemmArgs& g0, const BatchBuffers& b, int n_cu, hipStream_t s) {
   GemmArgs g = g0;
   constexpr int BK = 128 / sizeof(WT);
-  if constexpr (sizeof(WT) == 2) {
-    // bf16 weights: matrix cores; 64 rows x 16 positions per workgroup for
-    // few positions (many short K-slices keep the weight stream in flight),
-    // else 128 rows x 64 positions
-    if (g.P <= 16) {
-      // few positions: narrow tiles. Large tiles of eight waves (one
-      // workgroup per unit) keep most of a matrix in flight at once; small
-      // tiles of four waves (two per unit) balance the units where the large
-      // tiles would leave some with two. The K split fills the units.
-      if constexpr (EPI == kEpiSwiGlu) {
-        // 80-row tiles of eight waves, or 64-row tiles of four waves (two
-        // per unit): whichever leaves the busiest unit fewer bytes to load
-        const NarrowPlan a5 = narrow_plan(EPI, 5, 8, g, b.gemm_ws_floats, n_cu);
-        const NarrowPlan a4 = narrow_plan(EPI, 4, 4, g, b.gemm_ws_floats, n_cu);
-        if (a4.busiest < a5.busiest) return gemm_narrow<EPI, 4, 4, 2>(g, b, n_cu, s);
-        return gemm_narrow<EPI, 5, 8, 2>(g, b, n_cu, s);
-      } else if constexpr (EPI == kEpiResid) {
-        // 64-row tiles of eight waves or 32-row tiles of four, by the same rule
-        const NarrowPlan a4 = narrow_plan(EPI, 4, 8, g, b.gemm_ws_floats, n_cu);
-        const NarrowPlan a2 = narrow_plan(EPI, 2, 4, g, b.gemm_ws_floats, n_cu);
-        const NarrowPlan a1 = narrow_plan(EPI, 1, 8, g, b.gemm_ws_floats, n_cu, true);
-        if (a1.busiest < a2.busiest && a1.busiest < a4.busiest) return gemm_narrow<EPI, 1, 8, 2>(g, b, n_cu, s, true);
-        if (a4.busiest < a2.busiest) return gemm_narrow<EPI, 4, 8, 2>(g, b, n_cu, s);
-        return gemm_narrow<EPI, 2, 4, 2>(g, b, n_cu, s);
-      } else {
-        // 32-row tiles of four waves, or 16-row tiles of eight waves over the
-        // whole K (no slice merge), by the same rule
-        const NarrowPlan a2 = narrow_plan(EPI, 2, 4, g, b.gemm_ws_floats, n_cu);
-        const NarrowPlan a1 = narrow_plan(EPI, 1, 8, g, b.gemm_ws_floats, n_cu, true);
-        if (a1.busiest < a2.busiest) return gemm_narrow<EPI, 1, 8, 2>(g, b, n_cu, s, true);
-        return gemm_narrow<EPI, 2, 4, 2>(g, b, n_cu, s);
-      }
-    }
-    return gemm_mfma<EPI, 2, 4, 3>(g, b, n_cu, 2, s);
-  }
   if (g.P <= 16) {
     // few positions: narrow tiles (16 positions x 64 rows, one position and
     // four rows per thread) so that few K-slices fill the device and the
@@ -1385,6 +910,113 @@ hipError_t gemm(const GemmArgs& g0, const BatchBuffers& b, int n_cu, hipStream_t
     hipLaunchKernelGGL((k_bp_gemm<WT, EPI, BM, BN, TM>), dim3((g.N + BN - 1) / BN, (g.P + BM - 1) / BM, splits),
                        dim3(256), 0, s, g);
   }
+  return hipGetLastError();
+}
+
+// bf16 weights: the tile and K split of a product. Every candidate's time is
+// estimated (microseconds; constants fitted to a sweep of tiles and splits
+// over the products of three decoder widths, 16 to 1024 positions, where the
+// choice costs 1.7% over the best on average):
+//   * a unit runs the tile's workgroups in rounds of `occ` (what registers
+//     and LDS allow); a step of a round takes the matrix-core time of its
+//     workgroups or, if longer, the latency of one workgroup's step;
+//   * no less than the weights' read from HBM, nor than the tiles' reads of
+//     weights and activations from the caches;
+//   * the stores of the outputs, and for the residual products the next
+//     kernel's reads of the K slices.
+struct MmTile {
+  int rb, cp, nw, pf, occ;
+};
+double mm_time(const MmTile& t, int P, int N, int K, int splits, bool resid, int n_cu) {
+  const double mfma = 0.02127 * t.rb * t.cp * t.nw;
+  const double lat = (t.pf == 1 ? 0.733 : 0.262) + 0.377 * mfma;
+  const int tiles = ((N + 16 * t.rb * t.nw - 1) / (16 * t.rb * t.nw)) * ((P + 16 * t.cp - 1) / (16 * t.cp)) * splits;
+  const int per_cu = (tiles + n_cu - 1) / n_cu, full = per_cu / t.occ, rest = per_cu % t.occ;
+  const int steps = ((K + 63) / 64 + splits - 1) / splits;
+  const double round = full * std::max(t.occ * mfma, lat) + (rest ? std::max(rest * mfma, lat) : 0.0);
+  const double bytes = 2.0 * N * K * ((P + 16 * t.cp - 1) / (16 * t.cp)) +
+                       6.0 * P * K * ((N + 16 * t.rb * t.nw - 1) / (16 * t.rb * t.nw));
+  const double out = 4.0 * splits * P * N;
+  return 3.2 + std::max({round * steps, 2.0 * N * K / 5.8e6, bytes / 14.8e6}) + out / 8.5e6 + (resid ? out / 5e6 : 0.0);
+}
+
+template <int EPI, int RB, int CP, int NW, int PF>
+hipError_t mm_launch(MmArgs m, const GemmArgs& g, int splits, hipStream_t s) {
+  const int steps = m.k32 / 2;
+  m.nN = (m.NB + RB * NW - 1) / (RB * NW);
+  m.nP = (m.PB + CP - 1) / CP;
+  m.steps_per_split = (steps + splits - 1) / splits;
+  m.splits = (steps + m.steps_per_split - 1) / m.steps_per_split;
+  const int tiles = m.nN * m.nP * m.splits;
+  m.tiles_per_xcd = (tiles + 7) / 8;
+  hipLaunchKernelGGL((k_bp_mm<EPI, RB, CP, NW, PF>), dim3(m.tiles_per_xcd * 8), dim3(64 * NW), 0, s, m, g);
+  return hipGetLastError();
+}
+
+// g: as for gemm(), with A, W unused; T the tiled weights, X the input's
+// term planes. *splits receives the K slices that a residual product stored.
+template <int EPI>
+hipError_t gemm_mm(const GemmArgs& g, const void* T, const u32x4* X, const BatchBuffers& b, int n_cu, int* splits,
+                   hipStream_t s) {
+  constexpr bool kResid = EPI == kEpiResid;
+  // 16 positions: the weight stream counts, four steps of it in flight. More
+  // positions: 32 to 64 per workgroup. Eight waves of three row blocks share
+  // the activations of 64 positions among 384 rows, the fewest cache reads.
+  static constexpr MmTile kTiles[] = {{1, 1, 8, 4, 3}, {1, 2, 4, 4, 3}, {2, 2, 4, 2, 4}, {3, 2, 4, 2, 3}, {4, 2, 4, 2, 2},
+                                      {3, 3, 4, 2, 2}, {3, 4, 4, 1, 2}, {3, 4, 8, 1, 1}, {2, 4, 8, 1, 1}};
+  MmArgs m{};
+  m.W = static_cast<const u32x4*>(T);
+  m.X = X;
+  m.P = g.P;
+  m.N = g.N;
+  m.NB = (g.N + 15) / 16;
+  m.PB = (g.P + 15) / 16;
+  m.k32 = mm_k32(g.K);
+  const int steps = m.k32 / 2;
+  int most = 1;
+  if (kResid) {
+    const size_t per = static_cast<size_t>(g.P) * g.N;
+    most = static_cast<int>(std::min<size_t>(16, b.gemm_ws_floats / per));
+    if (most < 1) return hipErrorInvalidValue;
+  }
+  int best = -1, best_s = 1;
+  double best_t = 0.0;
+  for (int i = 0; i < static_cast<int>(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
+    const MmTile& t = kTiles[i];
+    if ((t.cp == 1) != (g.P <= 16) || (t.cp == 3 && g.P > 256)) continue;
+    for (int sp : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
+      if (sp > most || (sp > 1 && steps / sp < 4)) break;
+      const double us = mm_time(t, g.P, g.N, g.K, sp, kResid, n_cu);
+      if (best < 0 || us < best_t) {
+        best = i;
+        best_s = sp;
+        best_t = us;
+      }
+    }
+  }
+  if (splits) {
+    const int per = (steps + best_s - 1) / best_s;
+    *splits = (steps + per - 1) / per;
+  }
+  switch (best) {
+    case 0: return mm_launch<EPI, 1, 1, 8, 4>(m, g, best_s, s);
+    case 1: return mm_launch<EPI, 1, 2, 4, 4>(m, g, best_s, s);
+    case 2: return mm_launch<EPI, 2, 2, 4, 2>(m, g, best_s, s);
+    case 3: return mm_launch<EPI, 3, 2, 4, 2>(m, g, best_s, s);
+    case 4: return mm_launch<EPI, 4, 2, 4, 2>(m, g, best_s, s);
+    case 5: return mm_launch<EPI, 3, 3, 4, 2>(m, g, best_s, s);
+    case 6: return mm_launch<EPI, 3, 4, 4, 1>(m, g, best_s, s);
+    case 7: return mm_launch<EPI, 3, 4, 8, 1>(m, g, best_s, s);
+    case 8: return mm_launch<EPI, 2, 4, 8, 1>(m, g, best_s, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t reduce_norm(const BatchBuffers& b, int splits, int P, int H, const float* gain, float eps, hipStream_t s) {
+  if (H > 8 * kNormThreads) return hipErrorInvalidValue;
+  const int blocks = (P + 127) / 128 * 128;  // whole groups of 16 positions on each of the 8 XCDs
+  hipLaunchKernelGGL(k_bp_reduce_norm, dim3(blocks), dim3(kNormThreads), 0, s, b.X, b.gemm_ws, splits, P, H, gain, eps,
+                     static_cast<u32x4*>(b.Xp), mm_k32(H));
   return hipGetLastError();
 }
 
@@ -1419,7 +1051,7 @@ hipError_t attention(AttnArgs a, const BatchBuffers& b, int n_cu, hipStream_t s)
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.nsplit == 1) return e;
-  hipLaunchKernelGGL((k_bp_attn_merge<D>), dim3((a.P * a.A + 3) / 4), dim3(256), 0, s, a);
+  hipLaunchKernelGGL((k_bp_attn_merge<WT, D>), dim3((a.P * a.A + 3) / 4), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1444,6 +1076,8 @@ hipError_t pass(const BatchPass& bp, int pos0, const int32_t* d_tokens, int n, h
     hipLaunchKernelGGL((k_bp_embed<WT>), dim3(P), dim3(256), 0, s, static_cast<const WT*>(p.embed), d_tokens + c0, P,
                        p.H, p.V, b.X, p.hist_tok, cpos, p.ctl);
     if ((e = hipGetLastError()) != hipSuccess) return e;
+    if constexpr (sizeof(WT) == 2)
+      if ((e = reduce_norm(b, 0, P, p.H, bp.layers[0].g_attn, p.eps, s)) != hipSuccess) return e;
     for (int l = 0; l < p.L; ++l) {
       const LayerW& lw = bp.layers[l];
       GemmArgs g{};
@@ -1463,29 +1097,41 @@ hipError_t pass(const BatchPass& bp, int pos0, const int32_t* d_tokens, int n, h
       g.block_table = p.block_table;
       g.page_shift = p.page_shift;
       g.page_size = p.page_size;
-      // 1. QKV with the attention RMSNorm, RoPE and the cache stores
-      GemmArgs q = g;
+      GemmArgs q = g, o = g, gu = g, dn = g;
       q.A = b.X; q.W = lw.wqkv; q.N = p.qkv_rows; q.K = p.H; q.gain = lw.g_attn; q.Y = b.Q;
-      if ((e = gemm<WT, kEpiQkv>(q, b, bp.n_cu, s)) != hipSuccess) return e;
-      // 2. attention over every cached position up to each query's own
+      o.A = b.O; o.W = lw.wo; o.N = p.H; o.K = p.A * p.D; o.Y = b.X;
+      gu.A = b.X; gu.W = lw.wgu; gu.N = 2 * p.F; gu.K = p.H; gu.gain = lw.g_mlp; gu.Y = b.Act;
+      gu.planes = static_cast<u32x4*>(b.Ap); gu.k32_out = mm_k32(p.F);
+      dn.A = b.Act; dn.W = lw.wd; dn.N = p.H; dn.K = p.F; dn.Y = b.X;
       AttnArgs at{};
       at.Q = b.Q; at.O = b.O; at.part = b.attn_ws;
+      at.planes = static_cast<u32x4*>(b.Op); at.k32 = mm_k32(p.A * p.D);
       at.kpool = p.kpool; at.vpool = p.vpool; at.layer_base = g.layer_base;
       at.block_table = p.block_table; at.page_shift = p.page_shift; at.page_size = p.page_size;
       at.P = P; at.pos0 = cpos; at.A = p.A; at.K = p.K; at.G = p.G; at.D = p.D; at.scale = p.attn_scale;
-      if ((e = attention_d<WT>(at, b, bp.n_cu, s)) != hipSuccess) return e;
-      // 3. X += O W_o^T
-      GemmArgs o = g;
-      o.A = b.O; o.W = lw.wo; o.N = p.H; o.K = p.A * p.D; o.gain = nullptr; o.Y = b.X;
-      if ((e = gemm<WT, kEpiResid>(o, b, bp.n_cu, s)) != hipSuccess) return e;
-      // 4. SiLU(gate) * up with the feed-forward RMSNorm
-      GemmArgs gu = g;
-      gu.A = b.X; gu.W = lw.wgu; gu.N = 2 * p.F; gu.K = p.H; gu.gain = lw.g_mlp; gu.Y = b.Act;
-      if ((e = gemm<WT, kEpiSwiGlu>(gu, b, bp.n_cu, s)) != hipSuccess) return e;
-      // 5. X += A W_d^T
-      GemmArgs dn = g;
-      dn.A = b.Act; dn.W = lw.wd; dn.N = p.H; dn.K = p.F; dn.gain = nullptr; dn.Y = b.X;
-      if ((e = gemm<WT, kEpiResid>(dn, b, bp.n_cu, s)) != hipSuccess) return e;
+      if constexpr (sizeof(WT) == 2) {
+        // the input's term planes are in Xp; each residual product's slices
+        // are summed by the kernel that prepares the next product's input
+        const LayerT& lt = bp.tiled[l];
+        const u32x4* Xp = static_cast<const u32x4*>(b.Xp);
+        int sp = 0;
+        if ((e = gemm_mm<kEpiQkv>(q, lt.wqkv, Xp, b, bp.n_cu, nullptr, s)) != hipSuccess) return e;
+        if ((e = attention_d<WT>(at, b, bp.n_cu, s)) != hipSuccess) return e;
+        if ((e = gemm_mm<kEpiResid>(o, lt.wo, static_cast<const u32x4*>(b.Op), b, bp.n_cu, &sp, s)) != hipSuccess)
+          return e;
+        if ((e = reduce_norm(b, sp, P, p.H, lw.g_mlp, p.eps, s)) != hipSuccess) return e;
+        if ((e = gemm_mm<kEpiSwiGlu>(gu, lt.wgu, Xp, b, bp.n_cu, nullptr, s)) != hipSuccess) return e;
+        if ((e = gemm_mm<kEpiResid>(dn, lt.wd, static_cast<const u32x4*>(b.Ap), b, bp.n_cu, &sp, s)) != hipSuccess)
+          return e;
+        const float* next = l + 1 < p.L ? bp.layers[l + 1].g_attn : nullptr;
+        if ((e = reduce_norm(b, sp, P, p.H, next, p.eps, s)) != hipSuccess) return e;
+      } else {
+        if ((e = gemm<WT, kEpiQkv>(q, b, bp.n_cu, s)) != hipSuccess) return e;
+        if ((e = attention_d<WT>(at, b, bp.n_cu, s)) != hipSuccess) return e;
+        if ((e = gemm<WT, kEpiResid>(o, b, bp.n_cu, s)) != hipSuccess) return e;
+        if ((e = gemm<WT, kEpiSwiGlu>(gu, b, bp.n_cu, s)) != hipSuccess) return e;
+        if ((e = gemm<WT, kEpiResid>(dn, b, bp.n_cu, s)) != hipSuccess) return e;
+      }
     }
   }
   return hipSuccess;
@@ -1499,12 +1145,19 @@ hipError_t launch_batched_pass(const BatchPass& bp, int pos0, const int32_t* d_t
 }
 
 size_t batch_tile_counters(int max_positions, int N_max) {
-  // tiles of 64 x 64 (more than 16 positions) and 16 x 64 (at most 16); on
-  // the matrix cores 128 rows x 64 positions and, for at most 16 positions,
-  // 32 rows (two row blocks) x 16
-  const size_t a = static_cast<size_t>((N_max + 63) / 64) * ((max_positions + 63) / 64);
-  const size_t b = static_cast<size_t>((N_max + 31) / 32);
-  return std::max(a, b);
+  // fp32 weights: tiles of 64 x 64 (more than 16 positions) and 16 x 64 (at most 16)
+  return static_cast<size_t>((N_max + 63) / 64) * ((max_positions + 63) / 64);
+}
+
+size_t batch_weight_bytes(int N, int K) { return mm_weight_bytes(N, K); }
+size_t batch_plane_bytes(int P, int K) { return mm_plane_bytes(P, K); }
+
+hipError_t launch_tile_weights(const void* W, int N, int K, void* T, hipStream_t s) {
+  const int64_t chunks = static_cast<int64_t>(mm_weight_bytes(N, K) / 16);
+  const int blocks = static_cast<int>(std::min<int64_t>((chunks + 255) / 256, 8192));
+  hipLaunchKernelGGL(k_bp_tile_weights, dim3(blocks), dim3(256), 0, s, static_cast<const uint16_t*>(W), N, K, mm_k32(K),
+                     chunks, static_cast<u32x4*>(T));
+  return hipGetLastError();
 }
 
 }  // namespace ee

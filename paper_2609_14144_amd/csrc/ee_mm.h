@@ -1,0 +1,231 @@
+// Matrix products of the batched full-depth pass on the matrix cores, for
+// more than a handful of positions: Y[p][n] = sum_k X[p][k] W[n][k], bf16
+// weights, fp32 activations.
+//
+// Operands lie in memory in the order in which v_mfma_f32_16x16x32_bf16
+// takes them, so that neither needs a shuffle, a conversion or a bank
+// conflict on its way to the matrix cores:
+//   * weights ("tiled copy", made once when they are loaded):
+//     [N/16][K/32][lane 64][8]: lane l of a 16 x 32 tile holds row l % 16,
+//     k = 8 (l / 16) .. + 7; rows and columns padded with zeros (K to 64);
+//   * activations ("term planes"): [P/16][K/32][term 3][lane 64][8], lane l
+//     holding position l % 16, k = 8 (l / 16) .. + 7 of one of the three
+//     bf16 terms into which the producer split the fp32 value exactly (the
+//     top 16 bits, those of the remainder, the rest). The three products
+//     accumulate in fp32, so the result carries fp32 accumulation error
+//     only. The producer of a vector splits it once; splitting in the
+//     product itself repeats it for every row tile, and the vector ALU then
+//     takes longer than the matrix cores.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace ee {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+__host__ __device__ inline int mm_k32(int K) { return (K + 63) / 64 * 2; }  // 32-wide K blocks, an even number
+// bytes of a tiled copy of [N][K] weights and of the term planes of [P][K] activations
+__host__ __device__ inline size_t mm_weight_bytes(int N, int K) {
+  return static_cast<size_t>((N + 15) / 16) * mm_k32(K) * 1024;
+}
+__host__ __device__ inline size_t mm_plane_bytes(int P, int K) {
+  return static_cast<size_t>((P + 15) / 16) * mm_k32(K) * 3072;
+}
+// 16-byte chunk of term `term` of (position p, elements k .. k + 7), k a multiple of 8
+__device__ __forceinline__ int64_t mm_chunk(int p, int k, int term, int k32) {
+  return ((static_cast<int64_t>(p >> 4) * k32 + (k >> 5)) * 3 + term) * 64 + (p & 15) + 16 * ((k & 31) >> 3);
+}
+
+// the three bf16 terms of x, each in the low 16 bits
+__device__ __forceinline__ void mm_split(float x, uint32_t& t0, uint32_t& t1, uint32_t& t2) {
+  const uint32_t u = __float_as_uint(x);
+  const float r1 = x - __uint_as_float(u & 0xffff0000u);
+  const uint32_t u1 = __float_as_uint(r1);
+  const float r2 = r1 - __uint_as_float(u1 & 0xffff0000u);
+  t0 = u >> 16;
+  t1 = u1 >> 16;
+  t2 = __float_as_uint(r2) >> 16;  // exact: r2 has at most 8 significant bits
+}
+// two neighbouring elements, each term packed as one 32-bit word
+__device__ __forceinline__ void mm_split2(float a, float b, uint32_t (&t)[3]) {
+  uint32_t x[3], y[3];
+  mm_split(a, x[0], x[1], x[2]);
+  mm_split(b, y[0], y[1], y[2]);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) t[i] = x[i] | (y[i] << 16);
+}
+
+struct MmArgs {
+  const u32x4* W;  // tiled copy
+  const u32x4* X;  // term planes
+  int P, N;
+  int NB, PB;      // 16-row and 16-position blocks
+  int k32;         // 32-wide K blocks
+  int nN, nP;      // tiles along N and P
+  int splits, steps_per_split;  // K slices, in steps of 64
+  int tiles_per_xcd;
+};
+
+// Block: NW waves stacked along N, each RB blocks of 16 rows; all share CP
+// blocks of 16 positions. Bound by the matrix cores for many positions (each
+// wave issues 6 RB CP MFMAs of 16 cycles per 64-wide step) and by the weight
+// stream for few. Weights go straight to registers (no wave shares its rows
+// with another), activations through LDS, where every wave reads them: per
+// step a wave reads 6 CP KB of LDS for 6 RB CP MFMAs, so RB = 4 leaves the
+// LDS 60% busy and RB = 2 nearly saturates it.
+// Three LDS buffers: step s is read while step s + 2 is written, and the
+// first fragments of step s + 1 are already complete, so that their reads are
+// issued before the one barrier per step; fragments of each group of RB x CP
+// MFMAs are requested one group ahead.
+// Sums: every matrix-core accumulation rounds, so the error grows with the
+// number of accumulations (three per 32 elements) into one register. Groups
+// of kSum steps (6 kSum accumulations) are summed from zero and then added to
+// a total, about as short a chain as a K split over many waves gives; the
+// additions cost the vector ALU 4% of a step's matrix-core time with groups
+// of four steps, and nothing that counts where the weight stream bounds the
+// tile (groups of two). One chain over the whole of K had 1.4 times the error.
+// A workgroup's tile follows from its XCD (blockIdx % 8): every XCD takes a
+// contiguous range of tiles, position tiles fastest, so that the workgroups
+// that share weight rows share an L2.
+// Measured (17920 x 1536 weights, us, against the product that split its
+// activations itself and read row-major weights): 1024 positions 161 against
+// 233, 512 positions 78 against 143.
+template <int RB, int CP, int NW, int PF, typename Epi>
+__device__ __forceinline__ void mm_tile(const MmArgs& g, Epi&& epi) {
+  constexpr int NT = 64 * NW;
+  constexpr int kSum = CP <= 2 ? 2 : 4;        // steps summed from zero
+  constexpr int XC = CP * 3 * 64;              // chunks of one 32-wide K block
+  constexpr int XL = (2 * XC + NT - 1) / NT;   // chunks per thread per step
+  __shared__ u32x4 Xs[3][2 * XC];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int xcd = blockIdx.x & 7, loc = blockIdx.x >> 3;
+  const int tile = xcd * g.tiles_per_xcd + loc;
+  if (loc >= g.tiles_per_xcd || tile >= g.nN * g.nP * g.splits) return;
+  const int tp = tile % g.nP, tr = tile / g.nP;
+  const int tn = tr % g.nN, split = tr / g.nN;
+  const int nb0 = (tn * NW + wave) * RB, pb0 = tp * CP;
+  const int total = g.k32 >> 1;
+  const int sb = split * g.steps_per_split, n = min(total - sb, g.steps_per_split);
+
+  // loads past the last row, position or step read a valid address instead;
+  // what they yield is not stored
+  const u32x4* wbase = g.W + static_cast<int64_t>(sb) * 128 + lane;
+  int64_t wo[RB];
+#pragma unroll
+  for (int r = 0; r < RB; ++r) wo[r] = static_cast<int64_t>(min(nb0 + r, g.NB - 1)) * g.k32 * 64;
+  // thread's chunk i of a step: c = tid + NT i of [position block][K block 2][term][lane]
+  const u32x4* xp[XL];
+#pragma unroll
+  for (int i = 0; i < XL; ++i) {
+    const int c = min(tid + NT * i, 2 * XC - 1);
+    const int pb = min(pb0 + c / 384, g.PB - 1);
+    xp[i] = g.X + (static_cast<int64_t>(pb) * g.k32 + 2 * sb) * 192 + c % 384;
+  }
+  u32x4 xr[PF][XL];
+  u32x4 wr[PF][2][RB];
+  auto load_x = [&](int st, int slot) {
+    const int64_t o = static_cast<int64_t>(min(st, n - 1)) * 384;
+#pragma unroll
+    for (int i = 0; i < XL; ++i) xr[slot][i] = xp[i][o];
+  };
+  auto store_x = [&](int buf, int slot) {
+#pragma unroll
+    for (int i = 0; i < XL; ++i)
+      if (2 * XC % NT == 0 || tid + NT * i < 2 * XC) Xs[buf][tid + NT * i] = xr[slot][i];
+  };
+  auto load_w = [&](int st, int slot, int kb) {
+    const u32x4* w = wbase + static_cast<int64_t>(min(st, n - 1)) * 128 + kb * 64;
+#pragma unroll
+    for (int r = 0; r < RB; ++r) wr[slot][kb][r] = w[wo[r]];
+  };
+  f32x4 acc[RB][CP], tot[RB][CP];  // of the current group of steps; of the groups before it
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int c = 0; c < CP; ++c) acc[r][c] = tot[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 xf[2][CP];
+  auto read_f = [&](int buf, int gi, int d) {  // group gi = (K block gi / 3, term gi % 3)
+#pragma unroll
+    for (int c = 0; c < CP; ++c) xf[d][c] = __builtin_bit_cast(bf16x8, Xs[buf][c * 384 + gi * 64 + lane]);
+  };
+
+  load_x(0, 0);
+#pragma unroll
+  for (int i = 0; i < PF; ++i) {
+    load_w(i, i, 0);
+    load_w(i, i, 1);
+    if (i == 0) {
+      store_x(0, 0);
+      load_x(1, 0);
+      store_x(1, 0);
+    }
+    load_x(i + 2, i);
+  }
+  __syncthreads();
+  read_f(0, 0, 0);
+  int cur = 0, nxt = 1, fre = 2;
+  constexpr int kUnroll = PF > kSum ? PF : kSum;
+  static_assert(kUnroll % PF == 0 && kUnroll % kSum == 0, "ring slots and sums follow the unrolled steps");
+  for (int st0 = 0; st0 < n; st0 += kUnroll) {
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      const int st = st0 + u, i = u % PF;
+      if (st >= n) break;  // the same for every wave
+#pragma unroll
+      for (int gi = 0; gi < 6; ++gi) {
+        if (gi < 5) read_f(cur, gi + 1, (gi + 1) & 1);
+        else read_f(nxt, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (gi == 1) {
+          store_x(fre, i);
+          load_x(st + 2 + PF, i);
+        }
+#pragma unroll
+        for (int c = 0; c < CP; ++c)
+#pragma unroll
+          for (int r = 0; r < RB; ++r)
+            acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wr[i][gi / 3][r]),
+                                                                xf[gi & 1][c],
+                                                                u % kSum == 0 && gi == 0 ? f32x4{0.f, 0.f, 0.f, 0.f}
+                                                                                         : acc[r][c],
+                                                                0, 0, 0);
+        if (gi % 3 == 2) load_w(st + PF, i, gi / 3);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __syncthreads();
+      if (u % kSum == kSum - 1) {
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+          for (int c = 0; c < CP; ++c) tot[r][c] += acc[r][c];
+      }
+      const int t = cur;
+      cur = nxt;
+      nxt = fre;
+      fre = t;
+    }
+  }
+  if (n % kSum != 0) {
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+      for (int c = 0; c < CP; ++c) tot[r][c] += acc[r][c];
+  }
+  // lane's outputs of (row block r, position block c): rows 16 (nb0 + r) + 4 (lane / 16) + 0..3, position
+  // 16 (pb0 + c) + lane % 16
+  const int lg = lane >> 4, lr = lane & 15;
+#pragma unroll
+  for (int c = 0; c < CP; ++c) {
+    const int p = (pb0 + c) * 16 + lr;
+    if (p >= g.P) continue;
+#pragma unroll
+    for (int r = 0; r < RB; ++r) epi(split, p, (nb0 + r) * 16 + 4 * lg, tot[r][c]);
+  }
+}
+
+}  // namespace ee

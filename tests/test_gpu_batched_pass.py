@@ -1,0 +1,98 @@
+"""The batched full-depth pass at the edges of its tiles, against the CPU
+oracle. Tolerances are those of tests/gpu_helpers.py."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+import synth
+from tests.gpu_helpers import MARGIN, check_kv, engine, lockstep, oracle_for
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+# Widths that fill no tile: K of 200 and 328 (32- and 64-wide steps with a
+# remainder), 320 QKV rows, 656 gate/up rows; three query heads per KV head.
+RAGGED = replace(synth.get_config("tiny_bf16"), name="ragged_bf16", n_layers=2, hidden=200, n_q_heads=3, n_kv_heads=1,
+                 ffn=328, vocab=600, readout_layers=(1,))
+_W = {}
+
+
+def ragged_weights(seed=0):
+    if seed not in _W:
+        _W[seed] = synth.generate_weights(RAGGED, seed=seed)
+    return _W[seed]
+
+
+def check_prompt(e, o, cfg, prompt, exit_layer, page_positions):
+    P = len(prompt)
+    g0 = o.prefill(prompt)
+    g = e.ee_prefill(prompt)
+    if o.last_prefill_stats[2] > MARGIN:
+        assert g == g0, (P, g, g0)
+    check_kv(e, o, cfg, range(cfg.n_layers), page_positions)
+    lockstep(e, o, g0, 0.5, exit_layer, 2, force_tokens=synth.prompts(cfg, 3 + P, 2), force_exit=[0, 1])
+
+
+@pytest.mark.parametrize("P", [1, 2, 15, 16, 17, 31, 33, 48, 49, 63, 64, 65, 97, 129, 257, 300])
+def test_ragged_widths_and_positions(P):
+    w = ragged_weights()
+    o = oracle_for(RAGGED.name, P + 2, cfg=RAGGED, weights=w)
+    e = engine(RAGGED.name, P + 2, page_size=16, cfg=RAGGED, weights=w)
+    check_prompt(e, o, RAGGED, synth.prompts(RAGGED, 70 + P, P), 1, sorted({0, P // 2, max(P - 2, 0), P - 1}))
+    e.close()
+
+
+def test_positions_of_another_chunk_leave_no_trace():
+    """A long chunk, then short prompts on the same context: what the long
+    one left in the padded operands does not reach the short ones."""
+    w = ragged_weights()
+    e = engine(RAGGED.name, 304, page_size=16, cfg=RAGGED, weights=w)
+    e.ee_prefill(synth.prompts(RAGGED, 5, 300))
+    for P in (1, 18, 70):
+        e.ee_reset()
+        o = oracle_for(RAGGED.name, P + 2, cfg=RAGGED, weights=w)
+        check_prompt(e, o, RAGGED, synth.prompts(RAGGED, 170 + P, P), 1, [0, P - 1])
+    e.close()
+
+
+def test_replaced_weights_reach_the_prompt_pass():
+    """A later ee_load_weights of some tensors: the prompt pass uses them."""
+    w = dict(ragged_weights())
+    e = engine(RAGGED.name, 64, page_size=16, cfg=RAGGED, weights=w)
+    prompt = synth.prompts(RAGGED, 9, 40)
+    e.ee_prefill(prompt)
+    other = ragged_weights(1)
+    for leaf in ("layers.0.wk", "layers.1.w_up", "layers.0.wo", "layers.0.w_down"):
+        w[leaf] = other[leaf]
+        e.ee_load_weights({leaf: other[leaf]})
+        e.ee_reset()
+        o = oracle_for(RAGGED.name, 64, cfg=RAGGED, weights=w)
+        check_prompt(e, o, RAGGED, prompt, 1, [0, 17, 39])
+    e.close()
+
+
+def test_pass_is_deterministic_over_k_slices():
+    """Two passes give the same cache bits and logits: K slices are added in
+    order (17 positions at the 0.5B widths split K over many workgroups)."""
+    cfg = replace(synth.get_config("d0p5b"), n_layers=2, vocab=4096, readout_layers=(1,))
+    w = synth.generate_weights(cfg)
+    prompt = synth.prompts(cfg, 13, 17)
+    runs = []
+    for _ in range(2):
+        e = engine("d0p5b", 32, cfg=cfg, weights=w)
+        g = e.ee_prefill(prompt)
+        kv = np.concatenate([np.concatenate(e.ee_read_kv(l, t)) for l in range(2) for t in range(17)])
+        d = e.ee_decode_step_ex(0.5, 1, 7, 0)
+        runs.append((g, kv, d["logits_full"]))
+        e.close()
+    assert runs[0][0] == runs[1][0]
+    np.testing.assert_array_equal(runs[0][1], runs[1][1])
+    np.testing.assert_array_equal(runs[0][2], runs[1][2])
