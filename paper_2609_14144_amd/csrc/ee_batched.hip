@@ -68,7 +68,6 @@ struct St;
 
 template <>
 struct St<uint16_t> {  // bf16 bit patterns
-  static constexpr int N = 8;
   __device__ static inline void unpack(const uint4& w, float* f) {
     f[0] = __uint_as_float(w.x << 16);
     f[1] = __uint_as_float(w.x & 0xffff0000u);
@@ -478,30 +477,74 @@ __global__ __launch_bounds__(256) void k_bp_tile_weights(const uint16_t* __restr
   }
 }
 
+// What the store of rows n .. n + 3 (of one head, n a multiple of 4) of the
+// repacked QKV matrix at position p reads: the rotations of the two RoPE
+// pairs and the cache row.
+struct QkvEpi {
+  float2 c, s;
+  int64_t off;
+};
+__device__ __forceinline__ QkvEpi qkv_epi(const GemmArgs& g, int p, int n) {
+  const int AD = g.Aq * g.D, KD = g.Kh * g.D;
+  const int pos = g.pos0 + p;
+  QkvEpi e{make_float2(1.f, 1.f), make_float2(0.f, 0.f), 0};
+  if (n < AD + KD) {
+    const int64_t i = static_cast<int64_t>(pos) * (g.D >> 1) + ((n % g.D) >> 1);
+    e.c = *reinterpret_cast<const float2*>(g.rope_cos + i);
+    e.s = *reinterpret_cast<const float2*>(g.rope_sin + i);
+  }
+  if (n >= AD) {
+    const int kvh = (n - AD) % KD / g.D;
+    e.off = cache_off(g.block_table, g.page_shift, g.page_size, g.Kh, g.D, g.layer_base, pos, kvh) + (n - AD) % g.D;
+  }
+  return e;
+}
+__device__ __forceinline__ void qkv_store(const GemmArgs& g, const QkvEpi& e, int p, int n, const f32x4& y) {
+  const int AD = g.Aq * g.D, KD = g.Kh * g.D;
+  if (n >= AD + KD) {
+    uint16_t* v = static_cast<uint16_t*>(g.vpool) + e.off;
+    *reinterpret_cast<uint2*>(v) = make_uint2(St<uint16_t>::bits(y[0]) | (St<uint16_t>::bits(y[1]) << 16),
+                                              St<uint16_t>::bits(y[2]) | (St<uint16_t>::bits(y[3]) << 16));
+    return;
+  }
+  const float r0 = y[0] * e.c.x - y[1] * e.s.x, r1 = y[1] * e.c.x + y[0] * e.s.x;
+  const float r2 = y[2] * e.c.y - y[3] * e.s.y, r3 = y[3] * e.c.y + y[2] * e.s.y;
+  if (n < AD)
+    *reinterpret_cast<f32x4*>(g.Y + static_cast<int64_t>(p) * AD + n) = f32x4{r0, r1, r2, r3};
+  else
+    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(g.kpool) + e.off) =
+        make_uint2(St<uint16_t>::bits(r0) | (St<uint16_t>::bits(r1) << 16),
+                   St<uint16_t>::bits(r2) | (St<uint16_t>::bits(r3) << 16));
+}
+
 // Epilogue targets of a product on the matrix cores (GemmArgs, with kEpiResid
 // storing its K slices' partial sums in g.part [split][P][N] for
 // k_bp_reduce_norm, and kEpiSwiGlu storing term planes).
-template <int EPI, int RB, int CP, int NW, int PF>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bp_mm(MmArgs m, GemmArgs g) {
-  mm_tile<RB, CP, NW, PF>(m, [&](int split, int p, int n, const f32x4& y) {
-    if (n >= m.N) return;
-    if constexpr (EPI == kEpiResid) {
-      *reinterpret_cast<f32x4*>(g.part + (static_cast<int64_t>(split) * m.P + p) * m.N + n) = y;
-    } else if constexpr (EPI == kEpiSwiGlu) {
-      // interleaved rows: n = 2j gate row j, n + 1 up row j
-      const float a0 = y[0] / (1.f + exp_hw(-y[0])) * y[1];
-      const float a1 = y[2] / (1.f + exp_hw(-y[2])) * y[3];
-      const int j = n >> 1;
-      uint32_t t[3];
-      mm_split2(a0, a1, t);
+template <int EPI, int RB, int CP, int NW, int PF, int KG>
+__global__ __launch_bounds__(64 * NW * KG) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bp_mm(MmArgs m, GemmArgs g) {
+  if constexpr (EPI == kEpiQkv) {
+    mm_tile<RB, CP, NW, PF, KG>(
+        m, [&](int p, int n) { return qkv_epi(g, p, n); },
+        [&](int, int p, int n, const f32x4& y, const QkvEpi& e) { qkv_store(g, e, p, n, y); });
+  } else {
+    mm_tile<RB, CP, NW, PF, KG>(
+        m, [](int, int) { return 0; },
+        [&](int split, int p, int n, const f32x4& y, int) {
+          if constexpr (EPI == kEpiResid) {
+            *reinterpret_cast<f32x4*>(g.part + (static_cast<int64_t>(split) * m.P + p) * m.N + n) = y;
+          } else {
+            // interleaved rows: n = 2j gate row j, n + 1 up row j
+            const float a0 = y[0] / (1.f + exp_hw(-y[0])) * y[1];
+            const float a1 = y[2] / (1.f + exp_hw(-y[2])) * y[3];
+            const int j = n >> 1;
+            uint32_t t[3];
+            mm_split2(a0, a1, t);
 #pragma unroll
-      for (int i = 0; i < 3; ++i)
-        *(reinterpret_cast<uint32_t*>(g.planes + mm_chunk(p, j & ~7, i, g.k32_out)) + ((j & 7) >> 1)) = t[i];
-    } else {
-      epi_pair<uint16_t>(g, EPI, p, n, y[0], y[1]);
-      epi_pair<uint16_t>(g, EPI, p, n + 2, y[2], y[3]);
-    }
-  });
+            for (int i = 0; i < 3; ++i)
+              *(reinterpret_cast<uint32_t*>(g.planes + mm_chunk(p, j & ~7, i, g.k32_out)) + ((j & 7) >> 1)) = t[i];
+          }
+        });
+  }
 }
 
 // The residual stream after a product, and the input of the next: X += the
@@ -804,10 +847,227 @@ __attribute__((amdgpu_waves_per_eu(sizeof(WT) == 4 ? 1 : ((QT * (G / GW) + 3) / 
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same attention on the matrix cores, for bf16 caches. Workgroup = (KV
+// head, QB blocks of 16 query positions, key split); wave = (one of the KV
+// head's G query heads, one block of 16 positions), so that all G heads share
+// the key and value tiles staged in LDS. Per tile of 64 keys a wave computes
+// S^T = K Q^T (rows keys, columns positions) and O^T += V^T P^T: a lane then
+// holds one position's scores for 16 keys, the softmax needs two exchanges
+// between lanes, the scores' layout is already the second product's operand
+// (the key order of its K slots is permuted alike on both sides), and the
+// output's layout that of the term planes. Values are read transposed from
+// LDS (ds_read_b64_tr_b16). Keys and values are exact bf16 operands; queries
+// and probabilities are split exactly into three bf16 terms, so both products
+// carry fp32 accumulation error only.
+// A tile is 96 MFMAs (1536 cycles) per wave at D = 128 and about as much
+// vector work (exponentials, the split of the probabilities), which other
+// waves overlap. The vector-ALU form above is bound by its FMAs and serial
+// LDS reads: 1024 queries over 1024 to 8192 keys (six heads of 128 per KV
+// head) took 595 us a layer on average, this 104 (172 for the last 1024, 840
+// TFLOP/s of term products); 512 queries over 512 keys 47 us, this 24 in one
+// pass over the keys and less with key splits.
+// ---------------------------------------------------------------------------
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ float max_groups(float v) {  // over the four 16-lane groups
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_groups(float v) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+template <int D, int G, int QB>
+__global__ __launch_bounds__(64 * G * QB) __attribute__((amdgpu_waves_per_eu(2))) void k_bp_attn_mfma(AttnArgs a) {
+  constexpr int NT = 64 * G * QB;
+  constexpr int CPK = D / 8;        // 16-byte chunks per cache row
+  constexpr int KST = CPK + 1;      // padded LDS rows: 16 lanes reading a column of 16 rows, and the
+  constexpr int VST = CPK + 2;      // transposed reads of 4 rows x 32 bytes, each touch every bank once
+  constexpr int KS = D / 32, DB = D / 16;
+  constexpr int CPT = (kKT * CPK + NT - 1) / NT;  // chunks of K (and of V) per thread per tile
+  __shared__ u32x4 Ks[kKT * KST];
+  __shared__ u32x4 Vs[kKT * VST];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lg = lane >> 4, lr = lane & 15;
+  const int h = wave % G, qb = wave / G;
+  const int nqt = (a.P + 16 * QB - 1) / (16 * QB);
+  // the last query tiles, which have the most keys, go first
+  const int item = blockIdx.x;
+  const int sp = item % a.nsplit, r1 = item / a.nsplit;
+  const int kvh = r1 % a.K, qt = nqt - 1 - r1 / a.K;
+  const int q0 = (qt * QB + qb) * 16;           // the wave's first query
+  const int qi = q0 + lr, qpos = a.pos0 + qi;   // the lane's query and its position
+  const int head = kvh * G + h;
+  const int t_end = a.pos0 + min(a.P, (qt + 1) * QB * 16);  // keys needed by the tile: [0, t_end)
+  const int kb = sp * a.keys_per_split;
+  const int ke = min(t_end, kb + a.keys_per_split);
+
+  auto offset = [&](int k0, int c) {
+    const int j = c / CPK, q = c - j * CPK;
+    return cache_off(a.block_table, a.page_shift, a.page_size, a.K, D, a.layer_base, min(k0 + j, ke - 1), kvh) + q * 8;
+  };
+  const uint16_t* kp = static_cast<const uint16_t*>(a.kpool);
+  const uint16_t* vp = static_cast<const uint16_t*>(a.vpool);
+  u32x4 kv[CPT], vv[CPT];
+  auto load_tile = [&](int k0) {  // keys past ke repeat key ke - 1; their scores are masked
+    int64_t off[CPT];
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) off[i] = offset(k0, min(tid + NT * i, kKT * CPK - 1));
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) {
+      kv[i] = *reinterpret_cast<const u32x4*>(kp + off[i]);
+      vv[i] = *reinterpret_cast<const u32x4*>(vp + off[i]);
+    }
+  };
+  if (kb < ke) load_tile(kb);
+
+  // the query's terms: k slots 8 lg .. + 7 of each 32 dimensions
+  bf16x8 qf[KS][3];
+  {
+    const float* q = a.Q + static_cast<int64_t>(min(qi, a.P - 1)) * a.A * D + head * D;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const f32x4 x0 = *reinterpret_cast<const f32x4*>(q + 32 * s + 8 * lg);
+      const f32x4 x1 = *reinterpret_cast<const f32x4*>(q + 32 * s + 8 * lg + 4);
+      uint32_t w[4][3];
+      mm_split2(x0[0], x0[1], w[0]);
+      mm_split2(x0[2], x0[3], w[1]);
+      mm_split2(x1[0], x1[1], w[2]);
+      mm_split2(x1[2], x1[3], w[3]);
+#pragma unroll
+      for (int t = 0; t < 3; ++t) qf[s][t] = __builtin_bit_cast(bf16x8, u32x4{w[0][t], w[1][t], w[2][t], w[3][t]});
+    }
+  }
+  const float scale2 = a.scale * 1.44269504088896341f;  // scores in units of log2
+  float m = -INFINITY, l = 0.f;  // running maximum of the query, the lane's share of the sum
+  f32x4 o[DB];
+#pragma unroll
+  for (int d = 0; d < DB; ++d) o[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  for (int k0 = kb; k0 < ke; k0 += kKT) {
+    __syncthreads();  // the previous tile is consumed
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) {
+      const int c = tid + NT * i;
+      if (kKT * CPK % NT == 0 || c < kKT * CPK) {
+        const int j = c / CPK, q = c - j * CPK;
+        Ks[j * KST + q] = kv[i];
+        Vs[j * VST + q] = vv[i];
+      }
+    }
+    __syncthreads();
+    if (k0 + kKT < ke) load_tile(k0 + kKT);
+    if (k0 > a.pos0 + q0 + 15) continue;  // every key of the tile is past the wave's queries
+    // scores: block b holds keys k0 + 16 b + 4 lg + 0..3 of the lane's query
+    f32x4 s[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      bf16x8 kf[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) kf[b] = __builtin_bit_cast(bf16x8, Ks[(16 * b + lr) * KST + 4 * ks + lg]);
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) s[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[b], qf[ks][t], s[b], 0, 0, 0);
+    }
+    if (k0 + kKT > min(ke, a.pos0 + q0 + 1)) {  // some key of the tile is past the split or a query
+      const int last = min(ke - 1, qpos);
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (k0 + 16 * b + 4 * lg + i > last) s[b][i] = -INFINITY;
+    }
+    float mt = s[0][0];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mt = fmaxf(mt, s[b][i]);
+    const float mn = fmaxf(m, max_groups(mt) * scale2);
+    const float ms = mn == -INFINITY ? 0.f : mn;  // no key yet: every exponential is zero
+    const float alpha = __builtin_amdgcn_exp2f(m - ms);
+    m = mn;
+    l *= alpha;
+    // probabilities, split: operand word of keys (i, i + 1) of block b: [2 (b & 1) + i / 2] of K slots b / 2
+    uint32_t pw[2][4][3];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; i += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[b][i], scale2, -ms));
+        const float p1 = __builtin_amdgcn_exp2f(fmaf(s[b][i + 1], scale2, -ms));
+        l += p0 + p1;
+        mm_split2(p0, p1, pw[b >> 1][2 * (b & 1) + (i >> 1)]);
+      }
+#pragma unroll
+    for (int d = 0; d < DB; ++d) o[d] *= alpha;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      bf16x8 vf[DB];
+#pragma unroll
+      for (int d = 0; d < DB; ++d) {
+        // 16 lanes read keys 4 lg .. + 3 (of block 2 ks, then 2 ks + 1) x dimensions 16 d .. + 15; lane lr
+        // receives dimension 16 d + lr of the four keys
+        s16x4 v[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int key = 32 * ks + 16 * u + 4 * lg + (lr >> 2);
+          const uint16_t* src = reinterpret_cast<const uint16_t*>(&Vs[key * VST]) + 16 * d + 4 * (lr & 3);
+          v[u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src));
+        }
+        vf[d] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v[0], v[1], 0, 1, 2, 3, 4, 5, 6, 7));
+      }
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        const bf16x8 pf =
+            __builtin_bit_cast(bf16x8, u32x4{pw[ks][0][t], pw[ks][1][t], pw[ks][2][t], pw[ks][3][t]});
+#pragma unroll
+        for (int d = 0; d < DB; ++d) o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[d], pf, o[d], 0, 0, 0);
+      }
+    }
+  }
+  const float lsum = sum_groups(l);
+  if (qi >= a.P) return;
+  if (a.nsplit == 1) {
+    const float inv = 1.f / lsum;
+#pragma unroll
+    for (int d = 0; d < DB; ++d) {
+      const int e = head * D + 16 * d + 4 * lg;
+      uint32_t w[2][3];
+      mm_split2(o[d][0] * inv, o[d][1] * inv, w[0]);
+      mm_split2(o[d][2] * inv, o[d][3] * inv, w[1]);
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+        *(reinterpret_cast<uint2*>(a.planes + mm_chunk(qi, e & ~7, t, a.k32)) + ((e & 7) >> 2)) =
+            make_uint2(w[0][t], w[1][t]);
+    }
+  } else {
+    float* r = a.part + ((static_cast<int64_t>(qi) * a.A + head) * a.nsplit + sp) * (D + 2);
+#pragma unroll
+    for (int d = 0; d < DB; ++d) {
+      *reinterpret_cast<float2*>(r + 16 * d + 4 * lg) = make_float2(o[d][0], o[d][1]);
+      *reinterpret_cast<float2*>(r + 16 * d + 4 * lg + 2) = make_float2(o[d][2], o[d][3]);
+    }
+    if (lg == 0) *reinterpret_cast<float2*>(r + D) = make_float2(m, lsum);
+  }
+}
+
 // one wave per (query, head): the splits' partial records in split order
+// (maxima in units of log2 with bf16 caches, of e with fp32 caches)
 template <typename WT, int D>
 __global__ __launch_bounds__(256) void k_bp_attn_merge(AttnArgs a) {
   constexpr int DPL = D / 64;
+  auto ex = [](float x) { return sizeof(WT) == 2 ? __builtin_amdgcn_exp2f(x) : exp_hw(x); };
   const int w = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (w >= a.P * a.A) return;
   const float* r = a.part + static_cast<int64_t>(w) * a.nsplit * (D + 2);
@@ -833,14 +1093,14 @@ __global__ __launch_bounds__(256) void k_bp_attn_merge(AttnArgs a) {
 #pragma unroll
     for (int u = 0; u < kSG; ++u) cm = fmaxf(cm, ms[u]);
     if (cm != -INFINITY) {
-      const float sc = exp_hw(M - cm);  // 0 while nothing has been merged
+      const float sc = ex(M - cm);  // 0 while nothing has been merged
       den *= sc;
 #pragma unroll
       for (int e = 0; e < DPL; ++e) num[e] *= sc;
 #pragma unroll
       for (int u = 0; u < kSG; ++u) {
         if (ms[u] == -INFINITY) continue;  // absent, or a split wholly past the query's position
-        const float f = exp_hw(ms[u] - cm);
+        const float f = ex(ms[u] - cm);
         den = fmaf(f, ls[u], den);
 #pragma unroll
         for (int e = 0; e < DPL; ++e) num[e] = fmaf(f, vs[u][e], num[e]);
@@ -925,14 +1185,14 @@ hipError_t gemm(const GemmArgs& g0, const BatchBuffers& b, int n_cu, hipStream_t
 //   * the stores of the outputs, and for the residual products the next
 //     kernel's reads of the K slices.
 struct MmTile {
-  int rb, cp, nw, pf, occ;
+  int rb, cp, nw, pf, kg, occ;
 };
 double mm_time(const MmTile& t, int P, int N, int K, int splits, bool resid, int n_cu) {
-  const double mfma = 0.02127 * t.rb * t.cp * t.nw;
-  const double lat = (t.pf == 1 ? 0.733 : 0.262) + 0.377 * mfma;
+  const double mfma = 0.02127 * t.rb * t.cp * t.nw * t.kg;
+  const double lat = (t.pf == 1 ? 0.733 : 0.262) + 0.377 * mfma / t.kg;
   const int tiles = ((N + 16 * t.rb * t.nw - 1) / (16 * t.rb * t.nw)) * ((P + 16 * t.cp - 1) / (16 * t.cp)) * splits;
   const int per_cu = (tiles + n_cu - 1) / n_cu, full = per_cu / t.occ, rest = per_cu % t.occ;
-  const int steps = ((K + 63) / 64 + splits - 1) / splits;
+  const int steps = ((K + 63) / 64 + splits * t.kg - 1) / (splits * t.kg);
   const double round = full * std::max(t.occ * mfma, lat) + (rest ? std::max(rest * mfma, lat) : 0.0);
   const double bytes = 2.0 * N * K * ((P + 16 * t.cp - 1) / (16 * t.cp)) +
                        6.0 * P * K * ((N + 16 * t.rb * t.nw - 1) / (16 * t.rb * t.nw));
@@ -940,7 +1200,7 @@ double mm_time(const MmTile& t, int P, int N, int K, int splits, bool resid, int
   return 3.2 + std::max({round * steps, 2.0 * N * K / 5.8e6, bytes / 14.8e6}) + out / 8.5e6 + (resid ? out / 5e6 : 0.0);
 }
 
-template <int EPI, int RB, int CP, int NW, int PF>
+template <int EPI, int RB, int CP, int NW, int PF, int KG>
 hipError_t mm_launch(MmArgs m, const GemmArgs& g, int splits, hipStream_t s) {
   const int steps = m.k32 / 2;
   m.nN = (m.NB + RB * NW - 1) / (RB * NW);
@@ -949,7 +1209,7 @@ hipError_t mm_launch(MmArgs m, const GemmArgs& g, int splits, hipStream_t s) {
   m.splits = (steps + m.steps_per_split - 1) / m.steps_per_split;
   const int tiles = m.nN * m.nP * m.splits;
   m.tiles_per_xcd = (tiles + 7) / 8;
-  hipLaunchKernelGGL((k_bp_mm<EPI, RB, CP, NW, PF>), dim3(m.tiles_per_xcd * 8), dim3(64 * NW), 0, s, m, g);
+  hipLaunchKernelGGL((k_bp_mm<EPI, RB, CP, NW, PF, KG>), dim3(m.tiles_per_xcd * 8), dim3(64 * NW * KG), 0, s, m, g);
   return hipGetLastError();
 }
 
@@ -962,8 +1222,11 @@ hipError_t gemm_mm(const GemmArgs& g, const void* T, const u32x4* X, const Batch
   // 16 positions: the weight stream counts, four steps of it in flight. More
   // positions: 32 to 64 per workgroup. Eight waves of three row blocks share
   // the activations of 64 positions among 384 rows, the fewest cache reads.
-  static constexpr MmTile kTiles[] = {{1, 1, 8, 4, 3}, {1, 2, 4, 4, 3}, {2, 2, 4, 2, 4}, {3, 2, 4, 2, 3}, {4, 2, 4, 2, 2},
-                                      {3, 3, 4, 2, 2}, {3, 4, 4, 1, 2}, {3, 4, 8, 1, 1}, {2, 4, 8, 1, 1}};
+  // The QKV product of few positions has few tiles and whole sums to finish:
+  // four groups of waves share a tile's K.
+  static constexpr MmTile kTiles[] = {{1, 1, 8, 4, 1, 3}, {1, 2, 4, 4, 1, 3}, {2, 2, 4, 2, 1, 4}, {3, 2, 4, 2, 1, 3},
+                                      {4, 2, 4, 2, 1, 2}, {3, 3, 4, 2, 1, 2}, {3, 4, 4, 1, 1, 2}, {3, 4, 8, 1, 1, 1},
+                                      {2, 4, 8, 1, 1, 1}, {1, 1, 2, 2, 4, 2}, {1, 2, 2, 2, 4, 1}};
   MmArgs m{};
   m.W = static_cast<const u32x4*>(T);
   m.X = X;
@@ -983,9 +1246,9 @@ hipError_t gemm_mm(const GemmArgs& g, const void* T, const u32x4* X, const Batch
   double best_t = 0.0;
   for (int i = 0; i < static_cast<int>(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
     const MmTile& t = kTiles[i];
-    if ((t.cp == 1) != (g.P <= 16) || (t.cp == 3 && g.P > 256)) continue;
+    if ((t.cp == 1) != (g.P <= 16) || (t.cp == 3 && g.P > 256) || (t.kg > 1 && EPI != kEpiQkv)) continue;
     for (int sp : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
-      if (sp > most || (sp > 1 && steps / sp < 4)) break;
+      if (sp > most || (sp > 1 && steps / sp < 4) || (t.kg > 1 && steps < 2 * t.kg)) break;
       const double us = mm_time(t, g.P, g.N, g.K, sp, kResid, n_cu);
       if (best < 0 || us < best_t) {
         best = i;
@@ -999,15 +1262,21 @@ hipError_t gemm_mm(const GemmArgs& g, const void* T, const u32x4* X, const Batch
     *splits = (steps + per - 1) / per;
   }
   switch (best) {
-    case 0: return mm_launch<EPI, 1, 1, 8, 4>(m, g, best_s, s);
-    case 1: return mm_launch<EPI, 1, 2, 4, 4>(m, g, best_s, s);
-    case 2: return mm_launch<EPI, 2, 2, 4, 2>(m, g, best_s, s);
-    case 3: return mm_launch<EPI, 3, 2, 4, 2>(m, g, best_s, s);
-    case 4: return mm_launch<EPI, 4, 2, 4, 2>(m, g, best_s, s);
-    case 5: return mm_launch<EPI, 3, 3, 4, 2>(m, g, best_s, s);
-    case 6: return mm_launch<EPI, 3, 4, 4, 1>(m, g, best_s, s);
-    case 7: return mm_launch<EPI, 3, 4, 8, 1>(m, g, best_s, s);
-    case 8: return mm_launch<EPI, 2, 4, 8, 1>(m, g, best_s, s);
+    case 0: return mm_launch<EPI, 1, 1, 8, 4, 1>(m, g, best_s, s);
+    case 1: return mm_launch<EPI, 1, 2, 4, 4, 1>(m, g, best_s, s);
+    case 2: return mm_launch<EPI, 2, 2, 4, 2, 1>(m, g, best_s, s);
+    case 3: return mm_launch<EPI, 3, 2, 4, 2, 1>(m, g, best_s, s);
+    case 4: return mm_launch<EPI, 4, 2, 4, 2, 1>(m, g, best_s, s);
+    case 5: return mm_launch<EPI, 3, 3, 4, 2, 1>(m, g, best_s, s);
+    case 6: return mm_launch<EPI, 3, 4, 4, 1, 1>(m, g, best_s, s);
+    case 7: return mm_launch<EPI, 3, 4, 8, 1, 1>(m, g, best_s, s);
+    case 8: return mm_launch<EPI, 2, 4, 8, 1, 1>(m, g, best_s, s);
+    case 9:
+      if constexpr (EPI == kEpiQkv) return mm_launch<EPI, 1, 1, 2, 2, 4>(m, g, best_s, s);
+      break;
+    case 10:
+      if constexpr (EPI == kEpiQkv) return mm_launch<EPI, 1, 2, 2, 2, 4>(m, g, best_s, s);
+      break;
   }
   return hipErrorInvalidValue;
 }
@@ -1017,6 +1286,46 @@ hipError_t reduce_norm(const BatchBuffers& b, int splits, int P, int H, const fl
   const int blocks = (P + 127) / 128 * 128;  // whole groups of 16 positions on each of the 8 XCDs
   hipLaunchKernelGGL(k_bp_reduce_norm, dim3(blocks), dim3(kNormThreads), 0, s, b.X, b.gemm_ws, splits, P, H, gain, eps,
                      static_cast<u32x4*>(b.Xp), mm_k32(H));
+  return hipGetLastError();
+}
+
+// Key splits for blocks whose longest has key_tiles tiles: units run two
+// workgroups at a time, a tile takes ~2.8 us (the same for one workgroup and
+// for two side by side), splits add the merging launch (4.5 us) and their
+// records' stores and loads.
+template <int D>
+hipError_t attention_mfma(AttnArgs a, const BatchBuffers& b, int n_cu, hipStream_t s) {
+  const int qb = a.G >= 4 ? 1 : a.G >= 2 ? 2 : 4;  // 4 to 8 waves per workgroup
+  const int blocks = a.K * ((a.P + 16 * qb - 1) / (16 * qb));
+  const int t_max = a.pos0 + a.P, key_tiles = (t_max + kKT - 1) / kKT;
+  const double rec = 4.0 * a.P * a.A * (D + 2);
+  const int most = static_cast<int>(std::min<size_t>(key_tiles, std::max<size_t>(1, static_cast<size_t>(b.attn_ws_floats * 4.0 / rec))));
+  int ns = 1;
+  double best = 0.0;
+  for (int n = 1; n <= std::min(most, 64); ++n) {
+    const int tiles = (key_tiles + n - 1) / n;
+    const double us = static_cast<double>((blocks * n + 2 * n_cu - 1) / (2 * n_cu)) * tiles * 2.8 +
+                      (n > 1 ? 4.5 + 2.0 * n * rec / 4e6 : 0.0);
+    if (n == 1 || us < best) {
+      best = us;
+      ns = n;
+    }
+  }
+  a.keys_per_split = (key_tiles + ns - 1) / ns * kKT;
+  a.nsplit = (t_max + a.keys_per_split - 1) / a.keys_per_split;
+  const dim3 grid(blocks * a.nsplit), block(64 * a.G * qb);
+  switch (a.G) {
+#define EE_ATTN_G(GG)                                                                                         \
+  case GG:                                                                                                    \
+    hipLaunchKernelGGL((k_bp_attn_mfma<D, GG, (GG >= 4 ? 1 : GG >= 2 ? 2 : 4)>), grid, block, 0, s, a);        \
+    break;
+    EE_ATTN_G(1) EE_ATTN_G(2) EE_ATTN_G(3) EE_ATTN_G(4) EE_ATTN_G(5) EE_ATTN_G(6) EE_ATTN_G(7) EE_ATTN_G(8)
+#undef EE_ATTN_G
+    default: return hipErrorInvalidValue;
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.nsplit == 1) return e;
+  hipLaunchKernelGGL((k_bp_attn_merge<uint16_t, D>), dim3((a.P * a.A + 3) / 4), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1059,8 +1368,11 @@ template <typename WT>
 hipError_t attention_d(const AttnArgs& a, const BatchBuffers& b, int n_cu, hipStream_t s) {
   switch (a.D) {
     case 32: return hipErrorInvalidValue;  // rows of at least 64 dimensions (one per lane)
-    case 64: return attention<WT, 64>(a, b, n_cu, s);
-    case 128: return attention<WT, 128>(a, b, n_cu, s);
+    case 64:
+      if constexpr (sizeof(WT) == 2) return attention_mfma<64>(a, b, n_cu, s);
+      else return attention<WT, 64>(a, b, n_cu, s);
+    case 128:
+      if constexpr (sizeof(WT) == 2) return attention_mfma<128>(a, b, n_cu, s);
   }
   return hipErrorInvalidValue;
 }

@@ -70,13 +70,16 @@ struct MmArgs {
   int tiles_per_xcd;
 };
 
-// Block: NW waves stacked along N, each RB blocks of 16 rows; all share CP
-// blocks of 16 positions. Bound by the matrix cores for many positions (each
-// wave issues 6 RB CP MFMAs of 16 cycles per 64-wide step) and by the weight
-// stream for few. Weights go straight to registers (no wave shares its rows
-// with another), activations through LDS, where every wave reads them: per
-// step a wave reads 6 CP KB of LDS for 6 RB CP MFMAs, so RB = 4 leaves the
-// LDS 60% busy and RB = 2 nearly saturates it.
+// Block: KG groups of NW waves. A group's waves are stacked along N, each RB
+// blocks of 16 rows; all share CP blocks of 16 positions. The groups take
+// parts of the block's K slice, and their sums meet in LDS (for products with
+// too few tiles to fill the device whose epilogue wants finished sums). Bound
+// by the matrix cores for many positions (each wave issues 6 RB CP MFMAs of 16
+// cycles per 64-wide step) and by the weight stream for few. Weights go
+// straight to registers (no wave shares its rows with another of its group),
+// activations through LDS, where every wave reads them: per step a wave reads
+// 6 CP KB of LDS for 6 RB CP MFMAs, so RB = 3 leaves the LDS 60 to 70% busy
+// and RB = 2 nearly saturates it.
 // Three LDS buffers: step s is read while step s + 2 is written, and the
 // first fragments of step s + 1 are already complete, so that their reads are
 // issued before the one barrier per step; fragments of each group of RB x CP
@@ -94,15 +97,19 @@ struct MmArgs {
 // Measured (17920 x 1536 weights, us, against the product that split its
 // activations itself and read row-major weights): 1024 positions 161 against
 // 233, 512 positions 78 against 143.
-template <int RB, int CP, int NW, int PF, typename Epi>
-__device__ __forceinline__ void mm_tile(const MmArgs& g, Epi&& epi) {
-  constexpr int NT = 64 * NW;
+template <int RB, int CP, int NW, int PF, int KG, typename Pre, typename Epi>
+__device__ __forceinline__ void mm_tile(const MmArgs& g, Pre&& pre, Epi&& epi) {
+  constexpr int NT = 64 * NW;                  // threads of a K group
   constexpr int kSum = CP <= 2 ? 2 : 4;        // steps summed from zero
   constexpr int XC = CP * 3 * 64;              // chunks of one 32-wide K block
   constexpr int XL = (2 * XC + NT - 1) / NT;   // chunks per thread per step
-  __shared__ u32x4 Xs[3][2 * XC];
-  const int tid = threadIdx.x, lane = tid & 63;
+  static_assert((KG - 1) * NW * RB * CP * 64 <= KG * 3 * 2 * XC, "the groups' sums fit the buffers");
+  __shared__ u32x4 Xsm[KG][3][2 * XC];
+  const int lane = threadIdx.x & 63;
+  const int kg = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / NT);
+  const int tid = static_cast<int>(threadIdx.x) - kg * NT;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  u32x4 (*Xs)[2 * XC] = Xsm[kg];
   const int xcd = blockIdx.x & 7, loc = blockIdx.x >> 3;
   const int tile = xcd * g.tiles_per_xcd + loc;
   if (loc >= g.tiles_per_xcd || tile >= g.nN * g.nP * g.splits) return;
@@ -110,7 +117,10 @@ __device__ __forceinline__ void mm_tile(const MmArgs& g, Epi&& epi) {
   const int tn = tr % g.nN, split = tr / g.nN;
   const int nb0 = (tn * NW + wave) * RB, pb0 = tp * CP;
   const int total = g.k32 >> 1;
-  const int sb = split * g.steps_per_split, n = min(total - sb, g.steps_per_split);
+  const int s0 = split * g.steps_per_split, slice = min(total - s0, g.steps_per_split);
+  // the K group's steps; every group passes every barrier of nmax steps
+  const int nmax = (slice + KG - 1) / KG;
+  const int sb = s0 + slice * kg / KG, n = s0 + slice * (kg + 1) / KG - sb;
 
   // loads past the last row, position or step read a valid address instead;
   // what they yield is not stored
@@ -154,6 +164,19 @@ __device__ __forceinline__ void mm_tile(const MmArgs& g, Epi&& epi) {
     for (int c = 0; c < CP; ++c) xf[d][c] = __builtin_bit_cast(bf16x8, Xs[buf][c * 384 + gi * 64 + lane]);
   };
 
+  // what the epilogue reads (pre(p, n)): requested here by the small tiles,
+  // where a round trip after the last step would count
+  constexpr bool kEarly = RB * CP <= 2;
+  const int lg = lane >> 4, lr = lane & 15;
+  auto out_p = [&](int c) { return (pb0 + c) * 16 + lr; };
+  auto out_n = [&](int r) { return (nb0 + r) * 16 + 4 * lg; };
+  decltype(pre(0, 0)) ep[kEarly ? RB : 1][kEarly ? CP : 1];
+  if constexpr (kEarly) {
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+#pragma unroll
+      for (int c = 0; c < CP; ++c) ep[r][c] = pre(min(out_p(c), g.P - 1), min(out_n(r), g.N - 4));
+  }
   load_x(0, 0);
 #pragma unroll
   for (int i = 0; i < PF; ++i) {
@@ -171,11 +194,11 @@ __device__ __forceinline__ void mm_tile(const MmArgs& g, Epi&& epi) {
   int cur = 0, nxt = 1, fre = 2;
   constexpr int kUnroll = PF > kSum ? PF : kSum;
   static_assert(kUnroll % PF == 0 && kUnroll % kSum == 0, "ring slots and sums follow the unrolled steps");
-  for (int st0 = 0; st0 < n; st0 += kUnroll) {
+  for (int st0 = 0; st0 < nmax; st0 += kUnroll) {
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const int st = st0 + u, i = u % PF;
-      if (st >= n) break;  // the same for every wave
+      if (st >= nmax) break;  // the same for every wave
 #pragma unroll
       for (int gi = 0; gi < 6; ++gi) {
         if (gi < 5) read_f(cur, gi + 1, (gi + 1) & 1);
@@ -185,6 +208,7 @@ __device__ __forceinline__ void mm_tile(const MmArgs& g, Epi&& epi) {
           store_x(fre, i);
           load_x(st + 2 + PF, i);
         }
+        if (KG == 1 || st < n) {
 #pragma unroll
         for (int c = 0; c < CP; ++c)
 #pragma unroll
@@ -194,11 +218,12 @@ __device__ __forceinline__ void mm_tile(const MmArgs& g, Epi&& epi) {
                                                                 u % kSum == 0 && gi == 0 ? f32x4{0.f, 0.f, 0.f, 0.f}
                                                                                          : acc[r][c],
                                                                 0, 0, 0);
+        }
         if (gi % 3 == 2) load_w(st + PF, i, gi / 3);
         __builtin_amdgcn_sched_barrier(0);
       }
       __syncthreads();
-      if (u % kSum == kSum - 1) {
+      if (u % kSum == kSum - 1 && (KG == 1 || st < n)) {
 #pragma unroll
         for (int r = 0; r < RB; ++r)
 #pragma unroll
@@ -216,15 +241,34 @@ __device__ __forceinline__ void mm_tile(const MmArgs& g, Epi&& epi) {
 #pragma unroll
       for (int c = 0; c < CP; ++c) tot[r][c] += acc[r][c];
   }
-  // lane's outputs of (row block r, position block c): rows 16 (nb0 + r) + 4 (lane / 16) + 0..3, position
-  // 16 (pb0 + c) + lane % 16
-  const int lg = lane >> 4, lr = lane & 15;
+  if constexpr (KG > 1) {  // the groups' sums, in order (the last barrier ended every read of the buffers)
+    f32x4* sums = reinterpret_cast<f32x4*>(&Xsm[0][0][0]);
+    if (kg > 0) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int c = 0; c < CP; ++c) sums[(((kg - 1) * NW + wave) * RB * CP + r * CP + c) * 64 + lane] = tot[r][c];
+    }
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll
+    for (int q = 0; q < KG - 1; ++q)
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int c = 0; c < CP; ++c) tot[r][c] += sums[((q * NW + wave) * RB * CP + r * CP + c) * 64 + lane];
+  }
+  // lane's outputs of (row block r, position block c): rows out_n(r) + 0..3, position out_p(c); N is a
+  // multiple of 4
 #pragma unroll
   for (int c = 0; c < CP; ++c) {
-    const int p = (pb0 + c) * 16 + lr;
-    if (p >= g.P) continue;
+    if (out_p(c) >= g.P) continue;
 #pragma unroll
-    for (int r = 0; r < RB; ++r) epi(split, p, (nb0 + r) * 16 + 4 * lg, tot[r][c]);
+    for (int r = 0; r < RB; ++r) {
+      if (out_n(r) >= g.N) continue;
+      if constexpr (kEarly) epi(split, out_p(c), out_n(r), tot[r][c], ep[r][c]);
+      else epi(split, out_p(c), out_n(r), tot[r][c], pre(out_p(c), out_n(r)));
+    }
   }
 }
 

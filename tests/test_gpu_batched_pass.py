@@ -96,3 +96,39 @@ def test_pass_is_deterministic_over_k_slices():
     assert runs[0][0] == runs[1][0]
     np.testing.assert_array_equal(runs[0][1], runs[1][1])
     np.testing.assert_array_equal(runs[0][2], runs[1][2])
+
+
+# Query heads per KV head 1..8 and both head sizes: the waves of a workgroup,
+# its blocks of query positions and the staging of key tiles follow from them.
+HEADS = [(1, 1, 64), (2, 1, 128), (6, 2, 64), (4, 1, 64), (5, 1, 128), (6, 1, 128), (7, 1, 64), (16, 2, 128)]
+
+
+@pytest.mark.parametrize("heads", HEADS, ids=lambda h: "A%d_K%d_D%d" % h)
+def test_attention_head_groups(heads):
+    """Prompts about the edges of the 16-position query blocks and 64-key
+    tiles, in one chunk and in chunks of 48 (later chunks attend to the
+    earlier ones through the cache)."""
+    A, K, D = heads
+    cfg = replace(synth.get_config("tiny_bf16"), name="heads", n_layers=2, hidden=max(128, A * D), n_q_heads=A,
+                  n_kv_heads=K, head_dim=D, ffn=256, vocab=512, readout_layers=(1,))
+    w = synth.generate_weights(cfg)
+    for P, chunk in ((3, None), (64, None), (65, 48), (130, 48), (197, None)):
+        o = oracle_for(cfg.name, P + 2, cfg=cfg, weights=w)
+        e = engine(cfg.name, P + 2, page_size=16, cfg=cfg, weights=w)
+        if chunk:
+            e.ee_set_prefill_chunk(chunk)
+        check_prompt(e, o, cfg, synth.prompts(cfg, 90 + P, P), 1, sorted({0, 15, 16, 63, 64, P // 2, P - 2, P - 1} & set(range(P))))
+        e.close()
+
+
+def test_attention_key_splits():
+    """1500 positions: a second chunk whose query blocks take several key
+    splits, merged in split order; later cache entries match the oracle's."""
+    cfg = replace(synth.get_config("tiny_bf16"), name="splits", n_layers=2, hidden=128, n_q_heads=2, n_kv_heads=1,
+                  ffn=256, vocab=512, readout_layers=(1,))
+    w = synth.generate_weights(cfg)
+    P = 1500
+    o = oracle_for(cfg.name, P + 2, cfg=cfg, weights=w)
+    e = engine(cfg.name, P + 2, page_size=64, cfg=cfg, weights=w)
+    check_prompt(e, o, cfg, synth.prompts(cfg, 91, P), 1, [0, 1023, 1024, 1100, 1279, 1280, 1498, 1499])
+    e.close()
