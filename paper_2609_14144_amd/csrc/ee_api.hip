@@ -79,6 +79,13 @@ struct ee_ctx {
   bool nucleus = false;   // steps also measure the readout token's nucleus rank (calibration, debug)
   int force_cap = 0;
   int32_t *d_force_tok = nullptr, *d_force_exit = nullptr;
+  int32_t* h_force = nullptr;          // pinned: tokens, then exits, force_cap entries each
+  int up_tok = 0, up_exit = 0;         // entries of them the next call's kernels need on the device
+  int pages_uploaded = 0;              // block-table entries the device has
+  // pinned: the step record, then what a call returns (results of the latest call)
+  char* mail = nullptr;
+  size_t mail_cap = 0;
+  void* d_params = nullptr;            // the slot's parameter block in constant memory
   float *d_dbg_r = nullptr, *d_dbg_f = nullptr, *d_x = nullptr;
 
   std::set<std::string> loaded;
@@ -280,20 +287,62 @@ int ensure_pages(ee_ctx* c, int pos_end) {
     return fail(c, EE_ECAPACITY, "KV capacity exceeded: need " + std::to_string(pos_end) +
                                      " positions, max_seq " + std::to_string(c->cfg.max_seq));
   const int need = (pos_end + c->cfg.page_size - 1) / c->cfg.page_size;
-  const int first = c->pages_mapped;
   while (c->pages_mapped < need) {
     c->h_block_table[c->pages_mapped++] = c->free_pages.back();
     c->free_pages.pop_back();
   }
-  if (c->pages_mapped > first)
-    HIPCHK(c, hipMemcpyAsync(c->d_block_table + first, c->h_block_table + first,
-                             sizeof(int32_t) * (c->pages_mapped - first), hipMemcpyHostToDevice,
-                             c->stream));
+  return EE_OK;
+}
+
+// The call's first kernel: the step record's per-call fields cleared, and
+// the imposed inputs and new pages (pinned host memory) copied to the device
+// together with whatever the caller has put into b.
+int begin_call(ee_ctx* c, ee::IoBatch& b) {
+  b.ctl = c->d_ctl;
+  b.add(c->d_force_tok, c->h_force, c->up_tok);
+  b.add(c->d_force_exit, c->h_force + c->force_cap, c->up_exit);
+  b.add(c->d_block_table + c->pages_uploaded, c->h_block_table + c->pages_uploaded, c->pages_mapped - c->pages_uploaded);
+  c->up_tok = c->up_exit = 0;
+  const hipError_t e = ee::launch_io(b, c->stream);
+  if (e != hipSuccess) return hip_fail(c, e, "call preparation launch");
+  c->pages_uploaded = c->pages_mapped;
+  return EE_OK;
+}
+
+// Room for a call's results behind the step record, in pinned host memory.
+constexpr size_t kMailHead = 256;
+static_assert(sizeof(ee::StepCtl) <= kMailHead, "the step record fits its place");
+int ensure_mail(ee_ctx* c, size_t bytes) {
+  if (kMailHead + bytes <= c->mail_cap) return EE_OK;
+  if (c->mail) (void)hipHostFree(c->mail);
+  c->mail = nullptr;
+  c->mail_cap = 0;
+  const size_t cap = std::max<size_t>(kMailHead + bytes, 64 << 10);
+  void* p = nullptr;
+  if (hipHostMalloc(&p, cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(c, EE_ENOMEM, "hipHostMalloc of " + std::to_string(cap) + " bytes failed");
+  }
+  c->mail = static_cast<char*>(p);
+  c->mail_cap = cap;
+  return EE_OK;
+}
+template <typename T>
+T* mail_at(const ee_ctx* c, size_t off) { return reinterpret_cast<T*>(c->mail + kMailHead + off); }
+
+// The call's last kernel: the step record and b's copies; then wait.
+int end_call(ee_ctx* c, ee::IoBatch& b, ee::StepCtl* ctl) {
+  b.add(c->mail, c->d_ctl, sizeof(ee::StepCtl) / 4);
+  const hipError_t e = ee::launch_io(b, c->stream);
+  if (e != hipSuccess) return hip_fail(c, e, "call results launch");
+  HIPCHK(c, hipStreamSynchronize(c->stream));
+  memcpy(ctl, c->mail, sizeof(*ctl));
   return EE_OK;
 }
 
 void reset_pages(ee_ctx* c) {
   c->pages_mapped = 0;
+  c->pages_uploaded = 0;
   c->free_pages.resize(c->n_pages);
   for (int i = 0; i < c->n_pages; ++i) c->free_pages[i] = i;
   // A fixed scrambled order: physical page order differs from logical order.
@@ -321,9 +370,16 @@ int ensure_ring(ee_ctx* c, int n) {
 int ensure_force(ee_ctx* c, int n) {
   if (n <= c->force_cap) return EE_OK;
   dfree(c->d_force_tok); dfree(c->d_force_exit);
-  c->d_force_tok = c->d_force_exit = nullptr;
+  if (c->h_force) (void)hipHostFree(c->h_force);
+  c->d_force_tok = c->d_force_exit = c->h_force = nullptr;
   c->force_cap = 0;
   int r;
+  void* h = nullptr;
+  if (hipHostMalloc(&h, 2 * sizeof(int32_t) * n) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(c, EE_ENOMEM, "hipHostMalloc of imposed inputs failed");
+  }
+  c->h_force = static_cast<int32_t*>(h);
   if ((r = dalloc(c, &c->d_force_tok, sizeof(int32_t) * n))) return r;
   if ((r = dalloc(c, &c->d_force_exit, sizeof(int32_t) * n))) return r;
   c->force_cap = n;
@@ -382,15 +438,35 @@ int bind_scratch(ee_ctx* c, DevParams& p) {
   return EE_OK;
 }
 
-// Launch n steps (decode, or prompt positions when prefill) and wait. With
-// na set, the outputs go to the caller's device arrays and the working set
-// to the library-resident scratch: nothing is allocated.
+// Results of n decode steps in the mail: [tokens n][exited n][conf n][would n][mass n], then the debug
+// vectors [h_exit H][h_final H][logits_readout V][logits_full V] as far as collected.
+struct Collect {
+  bool vectors = false;  // h_exit, h_final
+  bool logits = false;   // both heads' logits
+};
+size_t ring_off(int n, int which) { return static_cast<size_t>(which) * n * 4; }
+size_t debug_off(const ee_ctx* c, int n, int which) {
+  const size_t H = c->cfg.hidden, V = c->cfg.vocab;
+  const size_t at[4] = {0, H * 4, 2 * H * 4, 2 * H * 4 + V * 4};
+  return ring_off(n, 5) + at[which];
+}
+
+// Launch n steps (decode, or prompt positions when prefill), collect their
+// results in the mail and wait. With na set, the outputs go to the caller's
+// device arrays and the working set to the library-resident scratch: nothing
+// is allocated.
 int run_steps(ee_ctx* c, float tau, int exit_layer, int n, const int32_t* d_force_tok,
-              const int32_t* d_force_exit, bool prefill, bool debug, const NoAlloc* na = nullptr) {
+              const int32_t* d_force_exit, bool prefill, const Collect& want = Collect{},
+              const NoAlloc* na = nullptr, ee::StepCtl* out_ctl = nullptr) {
   int r;
   DevParams p = make_params(c, tau, prefill ? 0 : exit_layer);
   if (na && (r = bind_scratch(c, p))) return r;
   if (!na && (r = ensure_ring(c, n))) return r;
+  if (!na && !prefill) {
+    const size_t V = c->cfg.vocab, H = c->cfg.hidden;
+    const size_t bytes = want.logits ? debug_off(c, n, 3) + V * 4 : want.vectors ? debug_off(c, n, 1) + H * 4 : ring_off(n, 5);
+    if ((r = ensure_mail(c, bytes))) return r;
+  }
   if ((r = ensure_pages(c, c->pos + n))) return r;
   if (na) {
     p.ring_tok = na->tok; p.ring_exit = na->exited; p.ring_conf = na->conf;
@@ -403,24 +479,24 @@ int run_steps(ee_ctx* c, float tau, int exit_layer, int n, const int32_t* d_forc
   p.nucleus = c->nucleus && !prefill;
   p.force_tok = d_force_tok;
   p.force_exit = d_force_exit;
-  if (debug) {
+  if (want.logits) {
     p.dbg_logits_r = c->d_dbg_r;
     p.dbg_logits_f = c->d_dbg_f;
   }
-  // Clear the step record except next_token, the first step's input.
-  if (na) {
-    hipError_t ce = ee::launch_clear_step(c->d_ctl, c->stream);
-    if (ce != hipSuccess) return hip_fail(c, ce, "step record clear");
-  } else {
-    HIPCHK(c, hipMemsetAsync(reinterpret_cast<char*>(c->d_ctl) + offsetof(ee::StepCtl, exited), 0,
-                             offsetof(ee::StepCtl, pad) - offsetof(ee::StepCtl, exited), c->stream));
-  }
   HIPCHK(c, hipEventRecord(c->ev0, c->stream));
-  hipError_t e;
   const bool pers = c->persistent && c->nwg_persistent > 0 && c->slot >= 0;
+  ee::IoBatch in{};
   if (pers) {
     p.lazy_fill = (c->fill_lazy && c->fill_slots > 1) ? c->fill_slots : 0;
     *c->params_pinned = p;
+    in.counters = p.counters;
+    in.tw = p.tw_all;
+    in.tw_words = p.tw_words;
+    in.add(c->d_params, c->params_pinned, sizeof(DevParams) / 4);
+  }
+  if ((r = begin_call(c, in))) return r;
+  hipError_t e;
+  if (pers) {
     const ee::PersistentLaunch L{c->params_pinned, c->slot, c->wbf16, c->nwg_persistent, c->lds, c->stream};
     e = prefill ? ee::launch_prefill_persistent(L, c->pos, n) : ee::launch_decode_persistent(L, c->pos, n);
   } else if (prefill) {
@@ -430,10 +506,27 @@ int run_steps(ee_ctx* c, float tau, int exit_layer, int n, const int32_t* d_forc
   }
   if (e != hipSuccess) return hip_fail(c, e, "kernel launch");
   HIPCHK(c, hipEventRecord(c->ev1, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  HIPCHK(c, hipEventElapsedTime(&c->last_ms, c->ev0, c->ev1));
+  ee::IoBatch out{};
+  if (!na && !prefill) {
+    out.add(mail_at<int32_t>(c, ring_off(n, 0)), c->d_ring_tok, n);
+    out.add(mail_at<int32_t>(c, ring_off(n, 1)), c->d_ring_exit, n);
+    out.add(mail_at<float>(c, ring_off(n, 2)), c->d_ring_conf, n);
+    out.add(mail_at<int32_t>(c, ring_off(n, 3)), c->d_ring_would, n);
+    if (c->nucleus) out.add(mail_at<float>(c, ring_off(n, 4)), c->d_ring_mass, n);
+    const int64_t H = c->cfg.hidden, V = c->cfg.vocab;
+    if (want.vectors) {
+      out.add(mail_at<float>(c, debug_off(c, n, 0)), c->d_hexit, H, 1);
+      out.add(mail_at<float>(c, debug_off(c, n, 1)), c->d_h, H, 1);
+    }
+    if (want.logits) {
+      out.add(mail_at<float>(c, debug_off(c, n, 2)), c->d_dbg_r, V);
+      out.add(mail_at<float>(c, debug_off(c, n, 3)), c->d_dbg_f, V);
+    }
+  }
   ee::StepCtl ctl;
-  HIPCHK(c, hipMemcpy(&ctl, c->d_ctl, sizeof(ctl), hipMemcpyDeviceToHost));
+  if ((r = end_call(c, out, &ctl))) return r;
+  if (out_ctl) *out_ctl = ctl;
+  HIPCHK(c, hipEventElapsedTime(&c->last_ms, c->ev0, c->ev1));
   if (ctl.error != ee::kErrNone || ctl.abort) {
     c->have_next = false;
     return fail(c, EE_EDEVICE, ctl.error == ee::kErrToken  ? "device: token id out of range"
@@ -445,46 +538,39 @@ int run_steps(ee_ctx* c, float tau, int exit_layer, int n, const int32_t* d_forc
   return EE_OK;
 }
 
-// fp32 values of n tagged device words into host memory
-int copy_untag(ee_ctx* c, float* dst, const uint64_t* src, size_t n) {
-  std::vector<uint64_t> w(n);
-  HIPCHK(c, hipMemcpy(w.data(), src, n * 8, hipMemcpyDeviceToHost));
-  for (size_t i = 0; i < n; ++i) {
-    const uint32_t b = static_cast<uint32_t>(w[i]);
-    memcpy(dst + i, &b, 4);
-  }
-  return EE_OK;
+// The results of the latest decode call (n steps), from the mail.
+void copy_ring(ee_ctx* c, int n, int32_t* tokens, int32_t* exited, float* conf, int32_t* would) {
+  if (tokens) memcpy(tokens, mail_at<int32_t>(c, ring_off(n, 0)), sizeof(int32_t) * n);
+  if (exited) memcpy(exited, mail_at<int32_t>(c, ring_off(n, 1)), sizeof(int32_t) * n);
+  if (conf) memcpy(conf, mail_at<float>(c, ring_off(n, 2)), sizeof(float) * n);
+  if (would) memcpy(would, mail_at<int32_t>(c, ring_off(n, 3)), sizeof(int32_t) * n);
 }
 
-int copy_ring(ee_ctx* c, int n, int32_t* tokens, int32_t* exited, float* conf, int32_t* would) {
-  if (tokens) HIPCHK(c, hipMemcpy(tokens, c->d_ring_tok, sizeof(int32_t) * n, hipMemcpyDeviceToHost));
-  if (exited) HIPCHK(c, hipMemcpy(exited, c->d_ring_exit, sizeof(int32_t) * n, hipMemcpyDeviceToHost));
-  if (conf) HIPCHK(c, hipMemcpy(conf, c->d_ring_conf, sizeof(float) * n, hipMemcpyDeviceToHost));
-  if (would) HIPCHK(c, hipMemcpy(would, c->d_ring_would, sizeof(int32_t) * n, hipMemcpyDeviceToHost));
-  return EE_OK;
-}
-
+// Imposed inputs, checked and staged for the call's first kernel.
 int upload_force(ee_ctx* c, int n, const int32_t* force_tokens, const int32_t* force_exit) {
   int r;
+  c->up_tok = c->up_exit = 0;
   if (!force_tokens && !force_exit) return EE_OK;
   if ((r = ensure_force(c, n))) return r;
   if (force_tokens) {
     for (int i = 0; i < n; ++i)
       if (force_tokens[i] < 0 || force_tokens[i] >= c->cfg.vocab)
         return fail(c, EE_EINVAL, "force_tokens[" + std::to_string(i) + "] out of range");
-    HIPCHK(c, hipMemcpy(c->d_force_tok, force_tokens, sizeof(int32_t) * n, hipMemcpyHostToDevice));
+    memcpy(c->h_force, force_tokens, sizeof(int32_t) * n);
   }
   if (force_exit) {
     for (int i = 0; i < n; ++i)
       if (force_exit[i] < -1 || force_exit[i] > 1)
         return fail(c, EE_EINVAL, "force_exit values must be -1, 0 or 1");
-    HIPCHK(c, hipMemcpy(c->d_force_exit, force_exit, sizeof(int32_t) * n, hipMemcpyHostToDevice));
+    memcpy(c->h_force + c->force_cap, force_exit, sizeof(int32_t) * n);
   }
+  if (force_tokens) c->up_tok = n;
+  if (force_exit) c->up_exit = n;
   return EE_OK;
 }
 
 int decode_common(ee_ctx* c, float tau, int exit_layer, int n, const int32_t* force_tokens,
-                  const int32_t* force_exit, bool debug) {
+                  const int32_t* force_exit, const Collect& want = Collect{}, ee::StepCtl* out_ctl = nullptr) {
   int r;
   if (!c) return EE_EINVAL;
   c->err.clear();
@@ -494,7 +580,7 @@ int decode_common(ee_ctx* c, float tau, int exit_layer, int n, const int32_t* fo
     return fail(c, EE_ESTATE, "no input token: run ee_prefill first (or force the input tokens)");
   if ((r = upload_force(c, n, force_tokens, force_exit))) return r;
   return run_steps(c, tau, exit_layer, n, force_tokens ? c->d_force_tok : nullptr,
-                   force_exit ? c->d_force_exit : nullptr, false, debug);
+                   force_exit ? c->d_force_exit : nullptr, false, want, nullptr, out_ctl);
 }
 
 // Copy a matrix given in canonical layout into a row range of a repacked one.
@@ -793,6 +879,9 @@ static int create_body(ee_ctx* c, const ee_config* cfg, void* hip_stream, ee_ctx
   c->slot = take_slot();
   if ((he = hipHostMalloc(reinterpret_cast<void**>(&c->params_pinned), sizeof(DevParams))) != hipSuccess)
     return bail(hip_fail(c, he, "hipHostMalloc parameter block"));
+  if (c->slot >= 0 && (he = ee::params_address(c->slot, &c->d_params)) != hipSuccess)
+    return bail(hip_fail(c, he, "hipGetSymbolAddress of the parameter blocks"));
+  if ((r = ensure_mail(c, 0))) return bail(r);
   // without a free parameter slot the context uses the one-kernel-per-operation program
   c->nwg_persistent = (c->max_wgs_per_cu > 0 && c->slot >= 0) ? c->n_cu * c->max_wgs_per_cu : 0;
   c->persistent = c->nwg_persistent > 0;
@@ -824,7 +913,7 @@ static int load_weights_impl(ee_ctx* c, const ee_tensor* tensors, int32_t n_tens
 // d_tokens, batched (chunks of positions through each layer together); with
 // head, the final head of the last position sets the next input token.
 // Advances the position; synchronous.
-static int batched_full_depth(ee_ctx* c, const int32_t* d_tokens, int n, bool head) {
+static int batched_full_depth(ee_ctx* c, const int32_t* d_tokens, int n, bool head, int32_t* first) {
   int r;
   if ((r = ensure_pages(c, c->pos + n))) return r;
   ee::BatchPass bp{};
@@ -835,9 +924,9 @@ static int batched_full_depth(ee_ctx* c, const int32_t* d_tokens, int n, bool he
   if (c->prefill_chunk > 0) bp.buf.max_positions = std::min(c->prefill_chunk, c->bbuf.max_positions);
   bp.wbf16 = c->wbf16;
   bp.n_cu = c->n_cu;
-  HIPCHK(c, hipMemsetAsync(reinterpret_cast<char*>(c->d_ctl) + offsetof(ee::StepCtl, exited), 0,
-                           offsetof(ee::StepCtl, pad) - offsetof(ee::StepCtl, exited), c->stream));
   HIPCHK(c, hipEventRecord(c->ev0, c->stream));
+  ee::IoBatch in{}, out{};
+  if ((r = begin_call(c, in))) return r;
   hipError_t e = ee::launch_batched_pass(bp, c->pos, d_tokens, n, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "batched pass launch");
   if (head) {
@@ -848,10 +937,10 @@ static int batched_full_depth(ee_ctx* c, const int32_t* d_tokens, int n, bool he
     if (e != hipSuccess) return hip_fail(c, e, "prompt head launch");
   }
   HIPCHK(c, hipEventRecord(c->ev1, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  HIPCHK(c, hipEventElapsedTime(&c->last_ms, c->ev0, c->ev1));
   ee::StepCtl ctl;
-  HIPCHK(c, hipMemcpy(&ctl, c->d_ctl, sizeof(ctl), hipMemcpyDeviceToHost));
+  if ((r = end_call(c, out, &ctl))) return r;
+  HIPCHK(c, hipEventElapsedTime(&c->last_ms, c->ev0, c->ev1));
+  if (first) *first = ctl.next_token;
   if (ctl.error != ee::kErrNone) {
     c->have_next = false;
     return fail(c, EE_EDEVICE, "device: token id out of range");
@@ -867,14 +956,15 @@ static int prefill_impl(ee_ctx* c, const int32_t* tokens, int32_t n, int32_t* ou
   if (!tokens || n <= 0) return fail(c, EE_EINVAL, "prefill needs at least one token");
   int r;
   if ((r = upload_force(c, n, tokens, nullptr))) return r;
-  if (c->prefill_chunk != 0) {
-    if ((r = batched_full_depth(c, c->d_force_tok, n, true))) return r;
-    c->have_next = true;
-  } else if ((r = run_steps(c, INFINITY, 0, n, c->d_force_tok, nullptr, true, false))) {
-    return r;
-  }
   int32_t tok = -1;
-  HIPCHK(c, hipMemcpy(&tok, &c->d_ctl->next_token, sizeof(tok), hipMemcpyDeviceToHost));
+  if (c->prefill_chunk != 0) {
+    if ((r = batched_full_depth(c, c->d_force_tok, n, true, &tok))) return r;
+    c->have_next = true;
+  } else {
+    ee::StepCtl ctl;
+    if ((r = run_steps(c, INFINITY, 0, n, c->d_force_tok, nullptr, true, Collect{}, nullptr, &ctl))) return r;
+    tok = ctl.next_token;
+  }
   if (out_first_token) *out_first_token = tok;
   return EE_OK;
 }
@@ -885,15 +975,24 @@ static int refresh_impl(ee_ctx* c, int32_t n) {
   if (!weights_ready(c)) return fail(c, EE_ESTATE, "weights not fully loaded");
   if (n < 1 || n > c->pos) return fail(c, EE_EINVAL, "refresh needs 1 <= n <= position");
   int r;
+  const bool had = c->have_next;
+  if (c->prefill_chunk != 0) {
+    // the batched pass reads the positions' tokens from the history and, without a head, leaves the next input
+    c->pos -= n;
+    r = batched_full_depth(c, c->d_hist + c->pos, n, false, nullptr);
+    if (r) {
+      c->pos += n;
+      c->have_next = false;
+    }
+    return r;
+  }
   if ((r = ensure_force(c, n))) return r;
   HIPCHK(c, hipMemcpyAsync(c->d_force_tok, c->d_hist + (c->pos - n), sizeof(int32_t) * n,
                            hipMemcpyDeviceToDevice, c->stream));
   int32_t next = 0;
   HIPCHK(c, hipMemcpy(&next, &c->d_ctl->next_token, sizeof(next), hipMemcpyDeviceToHost));
-  const bool had = c->have_next;
   c->pos -= n;
-  r = c->prefill_chunk != 0 ? batched_full_depth(c, c->d_force_tok, n, false)
-                            : run_steps(c, INFINITY, 0, n, c->d_force_tok, nullptr, true, false);
+  r = run_steps(c, INFINITY, 0, n, c->d_force_tok, nullptr, true);
   if (r) {
     c->pos += n;
     c->have_next = false;
@@ -908,9 +1007,10 @@ static int refresh_impl(ee_ctx* c, int32_t n) {
 static int decode_n_ex_impl(ee_ctx* c, float tau, int32_t exit_layer, int32_t n, const int32_t* force_tokens,
                    const int32_t* force_exit, int32_t* tokens, int32_t* exited, float* conf,
                    int32_t* would_exit) {
-  int r = decode_common(c, tau, exit_layer, n, force_tokens, force_exit, false);
+  int r = decode_common(c, tau, exit_layer, n, force_tokens, force_exit);
   if (r) return r;
-  return copy_ring(c, n, tokens, exited, conf, would_exit);
+  copy_ring(c, n, tokens, exited, conf, would_exit);
+  return EE_OK;
 }
 
 static int decode_n_impl(ee_ctx* c, float tau, int32_t exit_layer, int32_t n, int32_t* tokens,
@@ -929,7 +1029,7 @@ static int decode_n_noalloc_impl(ee_ctx* c, float tau, int32_t exit_layer, int32
   if (!c->have_next) return fail(c, EE_ESTATE, "no input token: run ee_prefill first");
   if (!c->scratch) return fail(c, EE_ESTATE, "no library scratch on this device");
   const NoAlloc na{d_tokens, d_exited, d_conf};
-  return run_steps(c, tau, exit_layer, n, nullptr, nullptr, false, false, &na);
+  return run_steps(c, tau, exit_layer, n, nullptr, nullptr, false, Collect{}, &na);
 }
 
 static int decode_step_impl(ee_ctx* c, float tau, int32_t exit_layer, int32_t* out_token,
@@ -951,16 +1051,18 @@ static int decode_step_ex_impl(ee_ctx* c, float tau, int32_t exit_layer, int32_t
   const int32_t ft[1] = {input_token};
   const int32_t fe[1] = {force_exit};
   c->nucleus = dbg != nullptr;
+  Collect want;
+  want.logits = want_logits;
+  want.vectors = want_logits || (dbg && (dbg->h_exit || dbg->h_final));
+  ee::StepCtl ctl;
   r = decode_common(c, tau, exit_layer, 1, input_token >= 0 ? ft : nullptr,
-                    force_exit >= 0 ? fe : nullptr, want_logits);
+                    force_exit >= 0 ? fe : nullptr, want, &ctl);
   c->nucleus = false;
   if (r) return r;
   if (!dbg) return EE_OK;
-  ee::StepCtl ctl;
-  HIPCHK(c, hipMemcpy(&ctl, c->d_ctl, sizeof(ctl), hipMemcpyDeviceToHost));
   int32_t tok = 0, ex = 0, would = 0;
   float cf = 0.f;
-  if ((r = copy_ring(c, 1, &tok, &ex, &cf, &would))) return r;
+  copy_ring(c, 1, &tok, &ex, &cf, &would);
   const size_t H = c->cfg.hidden, V = c->cfg.vocab;
   dbg->token = tok;
   dbg->exited = ex;
@@ -970,14 +1072,12 @@ static int decode_step_ex_impl(ee_ctx* c, float tau, int32_t exit_layer, int32_t
   dbg->full_token = ex ? -1 : ctl.full_token;
   dbg->conf_full = ex ? NAN : ctl.conf_full;
   dbg->nucleus_mass = NAN;
-  if (!ex && exit_layer > 0)
-    HIPCHK(c, hipMemcpy(&dbg->nucleus_mass, c->d_ring_mass, sizeof(float), hipMemcpyDeviceToHost));
-  if (dbg->h_exit && exit_layer > 0 && (r = copy_untag(c, dbg->h_exit, c->d_hexit, H))) return r;
-  if (dbg->h_final && !ex && (r = copy_untag(c, dbg->h_final, c->d_h, H))) return r;
-  if (dbg->logits_readout && exit_layer > 0)
-    HIPCHK(c, hipMemcpy(dbg->logits_readout, c->d_dbg_r, V * 4, hipMemcpyDeviceToHost));
-  if (dbg->logits_full && !ex)
-    HIPCHK(c, hipMemcpy(dbg->logits_full, c->d_dbg_f, V * 4, hipMemcpyDeviceToHost));
+  if (!ex && exit_layer > 0) memcpy(&dbg->nucleus_mass, mail_at<float>(c, ring_off(1, 4)), sizeof(float));
+  auto take = [&](float* dst, int which, size_t count) { memcpy(dst, mail_at<float>(c, debug_off(c, 1, which)), count * 4); };
+  if (dbg->h_exit && exit_layer > 0) take(dbg->h_exit, 0, H);
+  if (dbg->h_final && !ex) take(dbg->h_final, 1, H);
+  if (dbg->logits_readout && exit_layer > 0) take(dbg->logits_readout, 2, V);
+  if (dbg->logits_full && !ex) take(dbg->logits_full, 3, V);
   return EE_OK;
 }
 
@@ -1009,7 +1109,7 @@ static int calibrate_threshold_impl(ee_ctx* c, const int32_t* prompts, const int
     if (r) return r;
     confs.insert(confs.end(), buf.begin(), buf.end());
     if (mode == EE_CAL_NUCLEUS) {
-      HIPCHK(c, hipMemcpy(mbuf.data(), c->d_ring_mass, sizeof(float) * n_gen, hipMemcpyDeviceToHost));
+      memcpy(mbuf.data(), mail_at<float>(c, ring_off(n_gen, 4)), sizeof(float) * n_gen);
       masses.insert(masses.end(), mbuf.begin(), mbuf.end());
     }
     off += prompt_lens[i];
@@ -1142,28 +1242,29 @@ static int head_eval_impl(ee_ctx* c, int32_t readout_layer, const float* x, int3
     if ((r = dalloc(c, &c->d_dbg_r, static_cast<size_t>(c->cfg.vocab) * 4))) return r;
     if ((r = dalloc(c, &c->d_dbg_f, static_cast<size_t>(c->cfg.vocab) * 4))) return r;
   }
-  HIPCHK(c, hipMemcpyAsync(c->d_x, x, sizeof(float) * c->cfg.hidden, hipMemcpyHostToDevice, c->stream));
+  // mail: [x H][logits V]
+  const int64_t H = c->cfg.hidden, V = c->cfg.vocab;
+  if ((r = ensure_mail(c, (H + (out_logits ? V : 0)) * 4))) return r;
+  memcpy(mail_at<float>(c, 0), x, H * 4);
+  ee::IoBatch in{}, out{};
+  in.add(c->d_x, mail_at<float>(c, 0), H);
+  // the eval's head writes next_token: the sequence's is kept aside and put back
+  in.add(&c->d_ctl->pad[0], &c->d_ctl->next_token, 1);
+  if ((r = begin_call(c, in))) return r;
   DevParams p = make_params(c, INFINITY, readout_layer);
   if (out_logits) {
     p.dbg_logits_r = c->d_dbg_r;
     p.dbg_logits_f = c->d_dbg_f;
   }
-  ee::StepCtl saved;
-  HIPCHK(c, hipMemcpy(&saved, c->d_ctl, sizeof(saved), hipMemcpyDeviceToHost));
-  HIPCHK(c, hipMemsetAsync(reinterpret_cast<char*>(c->d_ctl) + offsetof(ee::StepCtl, exited), 0,
-                           offsetof(ee::StepCtl, pad) - offsetof(ee::StepCtl, exited), c->stream));
   hipError_t e = ee::launch_head_eval(p, c->wbf16, c->d_x, readout_layer > 0, c->head_wgs, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "head eval launch");
-  HIPCHK(c, hipStreamSynchronize(c->stream));
+  out.add(&c->d_ctl->next_token, &c->d_ctl->pad[0], 1);
+  if (out_logits) out.add(mail_at<float>(c, H * 4), readout_layer > 0 ? c->d_dbg_r : c->d_dbg_f, V);
   ee::StepCtl ctl;
-  HIPCHK(c, hipMemcpy(&ctl, c->d_ctl, sizeof(ctl), hipMemcpyDeviceToHost));
-  // the eval's head wrote next_token: restore the sequence's
-  HIPCHK(c, hipMemcpy(&c->d_ctl->next_token, &saved.next_token, sizeof(int32_t), hipMemcpyHostToDevice));
+  if ((r = end_call(c, out, &ctl))) return r;
   if (out_token) *out_token = readout_layer > 0 ? ctl.readout_token : ctl.full_token;
   if (out_conf) *out_conf = readout_layer > 0 ? ctl.conf : ctl.conf_full;
-  if (out_logits)
-    HIPCHK(c, hipMemcpy(out_logits, readout_layer > 0 ? c->d_dbg_r : c->d_dbg_f,
-                        sizeof(float) * c->cfg.vocab, hipMemcpyDeviceToHost));
+  if (out_logits) memcpy(out_logits, mail_at<float>(c, H * 4), V * 4);
   return EE_OK;
 }
 
@@ -1272,10 +1373,7 @@ static int reset_impl(ee_ctx* c) {
   HIPCHK(c, hipStreamSynchronize(c->stream));
   c->pos = 0;
   c->have_next = false;
-  reset_pages(c);
-  HIPCHK(c, hipMemset(c->d_ctl, 0, sizeof(ee::StepCtl)));
-  HIPCHK(c, hipMemset(c->d_counters, 0, sizeof(ee::Counters)));
-  HIPCHK(c, hipDeviceSynchronize());
+  reset_pages(c);  // every call clears the step record and its counters itself
   return EE_OK;
 }
 
@@ -1317,6 +1415,8 @@ static void destroy_impl(ee_ctx* c) {
   if (c->ev1) (void)hipEventDestroy(c->ev1);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   if (c->params_pinned) (void)hipHostFree(c->params_pinned);
+  if (c->h_force) (void)hipHostFree(c->h_force);
+  if (c->mail) (void)hipHostFree(c->mail);
   give_slot(c->slot);
   delete c;
 }

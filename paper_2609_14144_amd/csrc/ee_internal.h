@@ -188,8 +188,35 @@ hipError_t launch_tile_weights(const void* W, int N, int K, void* T, hipStream_t
 // Host launchers (defined in ee_kernels.hip).
 hipError_t launch_decode_per_op(const DevParams& p, int wbf16, int pos0, int n, int head_wgs,
                                 hipStream_t s);
-// One persistent launch: the parameter block (pinned host memory) is copied
-// into constant-memory slot `slot` on `stream` before the kernel starts.
+// What a call moves before its first and after its last kernel: copies of
+// 32-bit words between device and pinned host memory (or, untag set, of the
+// values of tagged words), and the launch state the call starts from. One
+// kernel each, on the call's stream: a synchronous copy takes 25 to 35 us of
+// host and device time, and a decode call used to make nine of them.
+struct IoJob {
+  void* dst;
+  const void* src;
+  int64_t words;
+  int untag;
+};
+struct IoBatch {
+  static constexpr int kMax = 10;
+  IoJob job[kMax];
+  int n;
+  Counters* counters;  // cleared when set
+  uint64_t* tw;        // tw_words tagged words cleared
+  int64_t tw_words;
+  StepCtl* ctl;        // when set: the per-call fields cleared (all but next_token)
+  void add(void* dst, const void* src, int64_t words, int untag = 0) {
+    if (words > 0) job[n++] = IoJob{dst, src, words, untag};
+  }
+};
+hipError_t launch_io(const IoBatch& b, hipStream_t s);
+// Device address of the constant-memory parameter block of a slot.
+hipError_t params_address(int slot, void** out);
+
+// One persistent launch: the parameter block is in constant-memory slot
+// `slot`, counters and tagged words are cleared (IoBatch).
 struct PersistentLaunch {
   const DevParams* params_host;
   int slot;
@@ -204,10 +231,6 @@ hipError_t launch_prefill_per_op(const DevParams& p, int wbf16, int pos0, const 
 hipError_t launch_prefill_persistent(const PersistentLaunch& L, int pos0, int n);
 hipError_t launch_head_eval(const DevParams& p, int wbf16, const float* d_x, int readout,
                             int head_wgs, hipStream_t s);
-// clear the per-call fields of the step record (all but next_token)
-hipError_t launch_clear_step(StepCtl* c, hipStream_t s);
-// copy the fp32 values of n tagged words to dst (device)
-hipError_t launch_untag(float* dst, const uint64_t* src, int n, hipStream_t s);
 // Device address of the library-resident scratch array (kScratchBytes) on
 // `device`, which must be the current device; looked up once per device.
 hipError_t scratch_address(int device, void** out);

@@ -2104,49 +2104,65 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   if (npend > 0 && !aborted(p)) run_fill_batch<WT, CPL>(p, npend, sh_pend_pos, sh_pend_tag, smem, tg);
 }
 
-// Launch state of the persistent kernel: barrier and last-arriver counters,
-// and every tagged word (tag 0 is never written inside a launch).
-__global__ __launch_bounds__(kWG) void k_reset_state(Counters* c, uint64_t* tw, int64_t nw) {
-  const int t = threadIdx.x;
+// Launch state of a program: barrier and last-arriver counters, and for the
+// persistent kernel every tagged word (tag 0 is never written inside a
+// launch); then the batch's copies.
+__global__ __launch_bounds__(kWG) void k_io(IoBatch b) {
+  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kWG + threadIdx.x, step = static_cast<int64_t>(gridDim.x) * kWG;
   if (blockIdx.x == 0) {
-    if (t < kBarGroups) c->group[t][0] = 0u;
-    if (t < 64) c->attn[t][0] = 0u;
-    if (t == 0) {
-      c->top[0] = 0u;
-      c->gen[0] = 0u;
-      c->head[0] = 0u;
+    const int t = threadIdx.x;
+    if (b.counters) {
+      if (t < kBarGroups) b.counters->group[t][0] = 0u;
+      if (t < 64) b.counters->attn[t][0] = 0u;
+      if (t == 0) {
+        b.counters->top[0] = 0u;
+        b.counters->gen[0] = 0u;
+        b.counters->head[0] = 0u;
+      }
+    }
+    if (b.ctl && t == 0) {
+      b.ctl->exited = 0;
+      b.ctl->would_exit = 0;
+      b.ctl->readout_token = 0;
+      b.ctl->full_token = 0;
+      b.ctl->conf = 0.f;
+      b.ctl->conf_full = 0.f;
+      b.ctl->error = 0;
+      b.ctl->abort = 0u;
     }
   }
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kWG + t; i < nw; i += static_cast<int64_t>(gridDim.x) * kWG)
-    tw[i] = 0ull;
-}
-
-// The per-call fields of the step record (everything but next_token, the
-// first step's input), cleared by a kernel rather than a memset node.
-__global__ __launch_bounds__(64) void k_clear_step(StepCtl* c) {
-  if (threadIdx.x == 0) {
-    c->exited = 0;
-    c->would_exit = 0;
-    c->readout_token = 0;
-    c->full_token = 0;
-    c->conf = 0.f;
-    c->conf_full = 0.f;
-    c->error = 0;
-    c->abort = 0u;
+  for (int64_t i = t0; i < b.tw_words; i += step) b.tw[i] = 0ull;
+  for (int j = 0; j < b.n; ++j) {
+    const IoJob q = b.job[j];
+    uint32_t* dst = static_cast<uint32_t*>(q.dst);
+    if (q.untag) {
+      const uint64_t* src = static_cast<const uint64_t*>(q.src);
+      for (int64_t i = t0; i < q.words; i += step) dst[i] = static_cast<uint32_t>(src[i]);
+    } else {
+      const uint32_t* src = static_cast<const uint32_t*>(q.src);
+      for (int64_t i = t0; i < q.words; i += step) dst[i] = src[i];
+    }
   }
 }
 
-hipError_t launch_clear_step(StepCtl* c, hipStream_t s) {
-  hipLaunchKernelGGL(k_clear_step, dim3(1), dim3(64), 0, s, c);
+hipError_t launch_io(const IoBatch& b, hipStream_t s) {
+  int64_t most = b.tw_words;
+  for (int i = 0; i < b.n; ++i) most = b.job[i].words > most ? b.job[i].words : most;
+  int64_t blocks = (most + 4 * kWG - 1) / (4 * kWG);  // about four words per thread
+  blocks = blocks < 1 ? 1 : blocks > 128 ? 128 : blocks;
+  hipLaunchKernelGGL(k_io, dim3(static_cast<unsigned>(blocks)), dim3(kWG), 0, s, b);
   return hipGetLastError();
+}
+
+hipError_t params_address(int slot, void** out) {
+  void* a = nullptr;
+  const hipError_t e = hipGetSymbolAddress(&a, HIP_SYMBOL(c_params));
+  if (e == hipSuccess) *out = static_cast<char*>(a) + sizeof(DevParams) * slot;
+  return e;
 }
 
 __global__ __launch_bounds__(kWG) void k_tag_vec(uint64_t* dst, const float* src, int n) {
   for (int i = blockIdx.x * kWG + threadIdx.x; i < n; i += gridDim.x * kWG) dst[i] = tw_pack(src[i], 0u);
-}
-
-__global__ __launch_bounds__(kWG) void k_untag(float* dst, const uint64_t* src, int n) {
-  for (int i = blockIdx.x * kWG + threadIdx.x; i < n; i += gridDim.x * kWG) dst[i] = tw_val(src[i]);
 }
 
 // ---------------------------------------------------------------------------
@@ -2182,12 +2198,6 @@ hipError_t scratch_address(int device, void** out) {
   return hipSuccess;
 }
 
-hipError_t launch_untag(float* dst, const uint64_t* src, int n, hipStream_t s) {
-  hipLaunchKernelGGL(k_untag, dim3(8), dim3(kWG), 0, s, dst, src, n);
-  return hipGetLastError();
-}
-
-
 // ---------------------------------------------------------------------------
 // host dispatch over (storage type, chunks per lane)
 // ---------------------------------------------------------------------------
@@ -2217,8 +2227,9 @@ static hipError_t dispatch(int wbf16, int cpl, F&& f) {
 // one kernel per operation relies on counters that start at zero (a
 // persistent launch leaves them counting)
 static hipError_t reset_counters(const DevParams& p, hipStream_t s) {
-  hipLaunchKernelGGL(k_reset_state, dim3(1), dim3(kWG), 0, s, p.counters, p.tw_all, int64_t(0));
-  return hipGetLastError();
+  IoBatch b{};
+  b.counters = p.counters;
+  return launch_io(b, s);
 }
 
 hipError_t launch_decode_per_op(const DevParams& p, int wbf16, int pos0, int n, int head_wgs,
@@ -2300,11 +2311,6 @@ static hipError_t persistent(const PersistentLaunch& L, int pos0, int n, int pre
   const DevParams& p = *L.params_host;
   const void* fn = persistent_fn(L.wbf16, chunks_per_lane(p, L.wbf16), pos0 + n);
   if (!fn || L.slot < 0 || L.slot >= kParamSlots) return hipErrorInvalidValue;
-  hipError_t e = hipMemcpyToSymbolAsync(HIP_SYMBOL(c_params), L.params_host, sizeof(DevParams),
-                                        sizeof(DevParams) * L.slot, hipMemcpyHostToDevice, L.stream);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_reset_state, dim3(16), dim3(kWG), 0, L.stream, p.counters, p.tw_all, p.tw_words);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   int slot = L.slot;
   void* args[] = {&slot, &pos0, &n, &prefill};
   return hipLaunchCooperativeKernel(fn, dim3(L.nwg), dim3(kWG), args, static_cast<unsigned>(L.lds),
