@@ -189,16 +189,17 @@ hipError_t launch_tile_weights(const void* W, int N, int K, void* T, hipStream_t
 hipError_t launch_decode_per_op(const DevParams& p, int wbf16, int pos0, int n, int head_wgs,
                                 hipStream_t s);
 // What a call moves before its first and after its last kernel: copies of
-// 32-bit words between device and pinned host memory (or, untag set, of the
-// values of tagged words), and the launch state the call starts from. One
+// 32-bit words between device and pinned host memory (or from or to the
+// values of tagged words, with tag 0), and the launch state the call starts from. One
 // kernel each, on the call's stream: a synchronous copy takes 25 to 35 us of
 // host and device time, and a decode call used to make nine of them.
 struct IoJob {
   void* dst;
   const void* src;
   int64_t words;
-  int untag;
+  int form;  // kIoPlain, kIoUntag (src tagged), kIoTag (dst tagged)
 };
+enum : int { kIoPlain = 0, kIoUntag = 1, kIoTag = 2 };
 struct IoBatch {
   static constexpr int kMax = 10;
   IoJob job[kMax];
@@ -207,8 +208,8 @@ struct IoBatch {
   uint64_t* tw;        // tw_words tagged words cleared
   int64_t tw_words;
   StepCtl* ctl;        // when set: the per-call fields cleared (all but next_token)
-  void add(void* dst, const void* src, int64_t words, int untag = 0) {
-    if (words > 0) job[n++] = IoJob{dst, src, words, untag};
+  void add(void* dst, const void* src, int64_t words, int form = kIoPlain) {
+    if (words > 0) job[n++] = IoJob{dst, src, words, form};
   }
 };
 hipError_t launch_io(const IoBatch& b, hipStream_t s);

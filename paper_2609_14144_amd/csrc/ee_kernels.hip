@@ -2135,7 +2135,10 @@ __global__ __launch_bounds__(kWG) void k_io(IoBatch b) {
   for (int j = 0; j < b.n; ++j) {
     const IoJob q = b.job[j];
     uint32_t* dst = static_cast<uint32_t*>(q.dst);
-    if (q.untag) {
+    if (q.form == kIoTag) {
+      uint64_t* tagged = static_cast<uint64_t*>(q.dst);
+      for (int64_t i = t0; i < q.words; i += step) tagged[i] = static_cast<const uint32_t*>(q.src)[i];
+    } else if (q.form == kIoUntag) {
       const uint64_t* src = static_cast<const uint64_t*>(q.src);
       for (int64_t i = t0; i < q.words; i += step) dst[i] = static_cast<uint32_t>(src[i]);
     } else {
@@ -2159,10 +2162,6 @@ hipError_t params_address(int slot, void** out) {
   const hipError_t e = hipGetSymbolAddress(&a, HIP_SYMBOL(c_params));
   if (e == hipSuccess) *out = static_cast<char*>(a) + sizeof(DevParams) * slot;
   return e;
-}
-
-__global__ __launch_bounds__(kWG) void k_tag_vec(uint64_t* dst, const float* src, int n) {
-  for (int i = blockIdx.x * kWG + threadIdx.x; i < n; i += gridDim.x * kWG) dst[i] = tw_pack(src[i], 0u);
 }
 
 // ---------------------------------------------------------------------------
@@ -2267,9 +2266,10 @@ hipError_t launch_prefill_per_op(const DevParams& p, int wbf16, int pos0, const 
 
 hipError_t launch_head_eval(const DevParams& p, int wbf16, const float* d_x, int readout, int head_wgs,
                             hipStream_t s) {
-  hipLaunchKernelGGL(k_tag_vec, dim3(8), dim3(kWG), 0, s, p.h, d_x, p.H);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = reset_counters(p, s);
+  IoBatch b{};
+  b.counters = p.counters;
+  b.add(p.h, d_x, p.H, kIoTag);
+  const hipError_t e = launch_io(b, s);
   if (e != hipSuccess) return e;
   return dispatch(wbf16, chunks_per_lane(p, wbf16), [&](auto wt, auto cpl) {
     using WT = decltype(wt);
