@@ -169,19 +169,30 @@ __device__ __noinline__ void raise_abort(const DevParams& p, int err) {
   atomicMax(&p.ctl->error, err);
 }
 
+// Whether a wait must end without its word: another wait has timed out, or
+// this one does. Looked at on every 32nd poll only: the abort flag is a round
+// trip to the coherence point of its own, and checked on every poll it
+// doubled the time between two looks at the word (five waits a layer).
+__device__ __forceinline__ bool wait_over(const DevParams& p, int pass, uint64_t& t0) {
+  if ((pass & 31) != 31) return false;
+  if (aborted(p)) return true;
+  if (pass == 31) t0 = wall_clock64();
+  else if (wall_clock64() - t0 > kWaitTicks) {
+    raise_abort(p, kErrWait);
+    return true;
+  }
+  return false;
+}
+
 // one word, waited for
 __device__ inline uint64_t tw_wait(const DevParams& p, const uint64_t* w, uint32_t tag, bool poll) {
   uint64_t v = ld_coh_u64(w);
   if (!poll || tw_ok(v, tag)) return v;
-  const uint64_t t0 = wall_clock64();
-  while (true) {
-    __builtin_amdgcn_s_sleep(2);
+  uint64_t t0 = 0;
+  for (int pass = 0;; ++pass) {
+    __builtin_amdgcn_s_sleep(1);
     v = ld_coh_u64(w);
-    if (tw_ok(v, tag) || aborted(p)) break;
-    if (wall_clock64() - t0 > kWaitTicks) {
-      raise_abort(p, kErrWait);
-      break;
-    }
+    if (tw_ok(v, tag) || wait_over(p, pass, t0)) break;
   }
   return v;
 }
@@ -199,13 +210,8 @@ __device__ inline uint64_t tw_wait(const DevParams& p, const uint64_t* w, uint32
       if (!poll) break;                                                           \
       bool ready_ = true;                                                         \
       _Pragma("unroll") for (int k = 0; k < (KB); ++k) ready_ = ready_ && tw_ok(v[k], tag); \
-      if (ready_ || aborted(p)) break;                                            \
-      if (pass_ == 0) t0_ = wall_clock64();                                       \
-      else if (wall_clock64() - t0_ > kWaitTicks) {                               \
-        raise_abort(p, kErrWait);                                                 \
-        break;                                                                    \
-      }                                                                           \
-      __builtin_amdgcn_s_sleep(2);                                                \
+      if (ready_ || wait_over(p, pass_, t0_)) break;                              \
+      __builtin_amdgcn_s_sleep(1);                                         \
     }                                                                             \
   }
 
@@ -358,6 +364,36 @@ __device__ inline void rmsnorm_stage(const DevParams& p, const uint64_t* x, cons
   for (int j = 0; j < kGR; ++j) {
     const int i = static_cast<int>(threadIdx.x) + j * kWG;
     gr[j] = (g && i < n) ? g[i] : 1.f;
+  }
+  if (n <= kGR * kWG) {
+    // the thread's words stay in registers until they are normalised: two
+    // barriers follow their arrival instead of five (same sums, same bits)
+    __syncthreads();  // xs and red may still be read by a previous phase
+    const uint32_t tag = sy.tin;
+    const bool poll = sy.poll;
+    uint64_t v[kGR];
+#pragma unroll
+    for (int k = 0; k < kGR; ++k)
+      v[k] = static_cast<int>(threadIdx.x) + k * kWG < n ? tw_pack(0.f, tag + 1u) : tw_pack(0.f, tag);
+    EE_TW_POLL(kGR, x + k * kWG + threadIdx.x, true)
+    float ss = 0.f;
+#pragma unroll
+    for (int k = 0; k < kGR; ++k)
+      if (static_cast<int>(threadIdx.x) + k * kWG < n) ss = fmaf(tw_val(v[k]), tw_val(v[k]), ss);
+    ss = wave_sum(ss);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+    __syncthreads();
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) sum += red[w];
+    const float r = rsqrtf(sum / static_cast<float>(n) + p.eps);
+#pragma unroll
+    for (int k = 0; k < kGR; ++k) {
+      const int i = static_cast<int>(threadIdx.x) + k * kWG;
+      if (i < n) xs[i] = tw_val(v[k]) * r * gr[k];
+    }
+    __syncthreads();
+    return;
   }
   __syncthreads();  // xs may still be read by a previous phase
   tw_stage<kB>(p, x, n, sy.tin, sy.poll, xs);
@@ -1848,15 +1884,17 @@ __device__ inline void bar_arrive(const DevParams& p, uint32_t& epoch, int wg, i
 __device__ inline void bar_wait(const DevParams& p, uint32_t epoch) {
   if (threadIdx.x == 0) {
     uint32_t* gen = &p.counters->gen[0];
-    const uint64_t t0 = wall_clock64();
-    while (true) {
+    uint64_t t0 = 0;
+    for (int pass = 0;; ++pass) {
       const uint32_t v = __hip_atomic_load(gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (static_cast<int32_t>(v - epoch) >= 0) break;
-      if (__hip_atomic_load(&p.ctl->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-      if (wall_clock64() - t0 > kWaitTicks) {
-        __hip_atomic_store(&p.ctl->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        atomicMax(&p.ctl->error, kErrBarrier);
-        break;
+      if ((pass & 31) == 31) {  // as in wait_over
+        if (aborted(p)) break;
+        if (pass == 31) t0 = wall_clock64();
+        else if (wall_clock64() - t0 > kWaitTicks) {
+          raise_abort(p, kErrBarrier);
+          break;
+        }
       }
       __builtin_amdgcn_s_sleep(1);
     }
