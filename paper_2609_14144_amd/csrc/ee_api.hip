@@ -941,6 +941,7 @@ static int batched_full_depth(ee_ctx* c, const int32_t* d_tokens, int n, bool he
   if (c->prefill_chunk > 0) bp.buf.max_positions = std::min(c->prefill_chunk, c->bbuf.max_positions);
   bp.wbf16 = c->wbf16;
   bp.n_cu = c->n_cu;
+  bp.head = head;
   HIPCHK(c, hipEventRecord(c->ev0, c->stream));
   ee::IoBatch in{}, out{};
   if ((r = begin_call(c, in))) return r;

@@ -1281,10 +1281,10 @@ hipError_t gemm_mm(const GemmArgs& g, const void* T, const u32x4* X, const Batch
   return hipErrorInvalidValue;
 }
 
-hipError_t reduce_norm(const BatchBuffers& b, int splits, int P, int H, const float* gain, float eps, hipStream_t s) {
+hipError_t reduce_norm(const BatchBuffers& b, float* X, int splits, int P, int H, const float* gain, float eps, hipStream_t s) {
   if (H > 8 * kNormThreads) return hipErrorInvalidValue;
   const int blocks = (P + 127) / 128 * 128;  // whole groups of 16 positions on each of the 8 XCDs
-  hipLaunchKernelGGL(k_bp_reduce_norm, dim3(blocks), dim3(kNormThreads), 0, s, b.X, b.gemm_ws, splits, P, H, gain, eps,
+  hipLaunchKernelGGL(k_bp_reduce_norm, dim3(blocks), dim3(kNormThreads), 0, s, X, b.gemm_ws, splits, P, H, gain, eps,
                      static_cast<u32x4*>(b.Xp), mm_k32(H));
   return hipGetLastError();
 }
@@ -1389,7 +1389,7 @@ hipError_t pass(const BatchPass& bp, int pos0, const int32_t* d_tokens, int n, h
                        p.H, p.V, b.X, p.hist_tok, cpos, p.ctl);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if constexpr (sizeof(WT) == 2)
-      if ((e = reduce_norm(b, 0, P, p.H, bp.layers[0].g_attn, p.eps, s)) != hipSuccess) return e;
+      if ((e = reduce_norm(b, b.X, 0, P, p.H, bp.layers[0].g_attn, p.eps, s)) != hipSuccess) return e;
     for (int l = 0; l < p.L; ++l) {
       const LayerW& lw = bp.layers[l];
       GemmArgs g{};
@@ -1421,6 +1421,20 @@ hipError_t pass(const BatchPass& bp, int pos0, const int32_t* d_tokens, int n, h
       at.kpool = p.kpool; at.vpool = p.vpool; at.layer_base = g.layer_base;
       at.block_table = p.block_table; at.page_shift = p.page_shift; at.page_size = p.page_size;
       at.P = P; at.pos0 = cpos; at.A = p.A; at.K = p.K; at.G = p.G; at.D = p.D; at.scale = p.attn_scale;
+      // After the last layer's cache entries only the final state of the
+      // pass's last position is ever read, if any: one query, one row.
+      float* X = b.X;
+      const bool last = l + 1 == p.L;
+      if (last) {
+        const int64_t row = P - 1;
+        X += row * p.H;
+        at.Q += row * p.A * p.D;
+        at.pos0 += P - 1;
+        at.P = o.P = gu.P = dn.P = 1;
+        o.Y = dn.Y = X;
+        gu.A = X;
+      }
+      const bool stop = last && !(bp.head && c0 + P == n);
       if constexpr (sizeof(WT) == 2) {
         // the input's term planes are in Xp; each residual product's slices
         // are summed by the kernel that prepares the next product's input
@@ -1428,17 +1442,19 @@ hipError_t pass(const BatchPass& bp, int pos0, const int32_t* d_tokens, int n, h
         const u32x4* Xp = static_cast<const u32x4*>(b.Xp);
         int sp = 0;
         if ((e = gemm_mm<kEpiQkv>(q, lt.wqkv, Xp, b, bp.n_cu, nullptr, s)) != hipSuccess) return e;
+        if (stop) break;
         if ((e = attention_d<WT>(at, b, bp.n_cu, s)) != hipSuccess) return e;
         if ((e = gemm_mm<kEpiResid>(o, lt.wo, static_cast<const u32x4*>(b.Op), b, bp.n_cu, &sp, s)) != hipSuccess)
           return e;
-        if ((e = reduce_norm(b, sp, P, p.H, lw.g_mlp, p.eps, s)) != hipSuccess) return e;
+        if ((e = reduce_norm(b, X, sp, at.P, p.H, lw.g_mlp, p.eps, s)) != hipSuccess) return e;
         if ((e = gemm_mm<kEpiSwiGlu>(gu, lt.wgu, Xp, b, bp.n_cu, nullptr, s)) != hipSuccess) return e;
         if ((e = gemm_mm<kEpiResid>(dn, lt.wd, static_cast<const u32x4*>(b.Ap), b, bp.n_cu, &sp, s)) != hipSuccess)
           return e;
         const float* next = l + 1 < p.L ? bp.layers[l + 1].g_attn : nullptr;
-        if ((e = reduce_norm(b, sp, P, p.H, next, p.eps, s)) != hipSuccess) return e;
+        if ((e = reduce_norm(b, X, sp, at.P, p.H, next, p.eps, s)) != hipSuccess) return e;
       } else {
         if ((e = gemm<WT, kEpiQkv>(q, b, bp.n_cu, s)) != hipSuccess) return e;
+        if (stop) break;
         if ((e = attention_d<WT>(at, b, bp.n_cu, s)) != hipSuccess) return e;
         if ((e = gemm<WT, kEpiResid>(o, b, bp.n_cu, s)) != hipSuccess) return e;
         if ((e = gemm<WT, kEpiSwiGlu>(gu, b, bp.n_cu, s)) != hipSuccess) return e;

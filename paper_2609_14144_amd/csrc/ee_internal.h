@@ -171,11 +171,14 @@ struct BatchPass {
   BatchBuffers buf;
   int wbf16;
   int n_cu;
+  int head;               // the last position's final state is wanted
 };
 
 // Full depth over positions pos0 .. pos0 + n - 1 with input tokens d_tokens
 // (device), in chunks of buf.max_positions: every layer's cache entries of
-// those positions; the residual stream of the last chunk stays in buf.X.
+// those positions and, with head, the last position's final residual stream
+// in its row of buf.X (nothing reads the other positions' final states: the
+// last layer stops at their cache entries).
 hipError_t launch_batched_pass(const BatchPass& bp, int pos0, const int32_t* d_tokens, int n, hipStream_t s);
 // tile counters the pass needs for chunks of max_positions and outputs of at most N_max rows
 size_t batch_tile_counters(int max_positions, int N_max);

@@ -112,7 +112,7 @@ def test_attention_head_groups(heads):
     cfg = replace(synth.get_config("tiny_bf16"), name="heads", n_layers=2, hidden=max(128, A * D), n_q_heads=A,
                   n_kv_heads=K, head_dim=D, ffn=256, vocab=512, readout_layers=(1,))
     w = synth.generate_weights(cfg)
-    for P, chunk in ((3, None), (64, None), (65, 48), (130, 48), (197, None)):
+    for P, chunk in ((3, None), (64, None), (65, 48), (97, 48), (130, 48), (197, None)):
         o = oracle_for(cfg.name, P + 2, cfg=cfg, weights=w)
         e = engine(cfg.name, P + 2, page_size=16, cfg=cfg, weights=w)
         if chunk:
