@@ -40,7 +40,7 @@ struct ee_ctx {
   std::map<int, std::pair<void*, float*>> readout;
   ee::LayerW* d_layers = nullptr;
   std::vector<ee::LayerW> h_layers;   // the same pointers, host side (batched pass)
-  std::vector<ee::LayerT> tiled;      // bf16 weights: the batched pass's copies of the layers' matrices
+  std::vector<ee::LayerT> tiled;      // the batched pass's copies of the layers' matrices
   std::set<const void*> untiled;      // matrices loaded since their copies were made
   ee::BatchBuffers bbuf{};            // batched full-depth pass (prompt, refresh)
   int prefill_chunk = -1;             // -1: batched in chunks of bbuf.max_positions; 0: one position per step
@@ -717,20 +717,17 @@ int load_one(ee_ctx* c, const ee_tensor& t) {
 int tile_weights(ee_ctx* c) {
   const ee_config& g = c->cfg;
   const int H = g.hidden, AD = g.n_q_heads * g.head_dim, QKV = AD + 2 * g.n_kv_heads * g.head_dim, F = g.ffn;
-  if (c->wbf16) {
-    for (size_t l = 0; l < c->tiled.size(); ++l) {
-      const ee::LayerT& t = c->tiled[l];
-      const struct { const void* w; int n, k; void* t; } m[4] = {
-          {c->wqkv[l], QKV, H, t.wqkv}, {c->wo[l], H, AD, t.wo}, {c->wgu[l], 2 * F, H, t.wgu}, {c->wd[l], H, F, t.wd}};
-      for (const auto& x : m) {
-        if (!c->untiled.count(x.w)) continue;
-        const hipError_t e = ee::launch_tile_weights(x.w, x.n, x.k, x.t, c->stream);
-        if (e != hipSuccess) return hip_fail(c, e, "weight tiling launch");
-        c->untiled.erase(x.w);
-      }
+  for (size_t l = 0; l < c->tiled.size(); ++l) {
+    const ee::LayerT& t = c->tiled[l];
+    const struct { const void* w; int n, k; void* t; } m[4] = {
+        {c->wqkv[l], QKV, H, t.wqkv}, {c->wo[l], H, AD, t.wo}, {c->wgu[l], 2 * F, H, t.wgu}, {c->wd[l], H, F, t.wd}};
+    for (const auto& x : m) {
+      if (!c->untiled.count(x.w)) continue;
+      const hipError_t e = ee::launch_tile_weights(c->wbf16, x.w, x.n, x.k, x.t, c->stream);
+      if (e != hipSuccess) return hip_fail(c, e, "weight tiling launch");
+      c->untiled.erase(x.w);
     }
   }
-  c->untiled.clear();
   return EE_OK;
 }
 
@@ -799,15 +796,14 @@ static int create_body(ee_ctx* c, const ee_config* cfg, void* hip_stream, ee_ctx
     if ((r = dalloc(c, &c->wo[l], H * A * D * es))) return bail(r);
     if ((r = dalloc(c, &c->wgu[l], 2 * F * H * es))) return bail(r);
     if ((r = dalloc(c, &c->wd[l], H * F * es))) return bail(r);
-    if (c->wbf16) {
-      c->tiled.push_back(ee::LayerT{});
-      ee::LayerT& t = c->tiled.back();
-      if ((r = dalloc(c, &t.wqkv, ee::batch_weight_bytes(static_cast<int>((A + 2 * K) * D), static_cast<int>(H)))) ||
-          (r = dalloc(c, &t.wo, ee::batch_weight_bytes(static_cast<int>(H), static_cast<int>(A * D)))) ||
-          (r = dalloc(c, &t.wgu, ee::batch_weight_bytes(static_cast<int>(2 * F), static_cast<int>(H)))) ||
-          (r = dalloc(c, &t.wd, ee::batch_weight_bytes(static_cast<int>(H), static_cast<int>(F)))))
-        return bail(r);
-    }
+    c->tiled.push_back(ee::LayerT{});
+    ee::LayerT& t = c->tiled.back();
+    const int h = static_cast<int>(H), ad = static_cast<int>(A * D), f = static_cast<int>(F);
+    if ((r = dalloc(c, &t.wqkv, ee::batch_weight_bytes(c->wbf16, static_cast<int>((A + 2 * K) * D), h))) ||
+        (r = dalloc(c, &t.wo, ee::batch_weight_bytes(c->wbf16, h, ad))) ||
+        (r = dalloc(c, &t.wgu, ee::batch_weight_bytes(c->wbf16, 2 * f, h))) ||
+        (r = dalloc(c, &t.wd, ee::batch_weight_bytes(c->wbf16, h, f))))
+      return bail(r);
     if ((r = dalloc(c, &c->g_attn[l], H * 4))) return bail(r);
     if ((r = dalloc(c, &c->g_mlp[l], H * 4))) return bail(r);
   }
@@ -867,14 +863,11 @@ static int create_body(ee_ctx* c, const ee_config* cfg, void* hip_stream, ee_ctx
     b.max_positions = static_cast<int>(Pm);
     b.gemm_ws_floats = std::min<size_t>(size_t(8) << 20, 32 * Pm * nmax);
     b.attn_ws_floats = std::min<size_t>(size_t(8) << 20, 16 * Pm * A * (D + 2));
-    b.n_tile_ctr = ee::batch_tile_counters(static_cast<int>(Pm), static_cast<int>(nmax));
     if ((r = dalloc(c, &b.X, Pm * H * 4)) || (r = dalloc(c, &b.Q, Pm * A * D * 4)) ||
-        (!c->wbf16 && ((r = dalloc(c, &b.O, Pm * A * D * 4)) || (r = dalloc(c, &b.Act, Pm * F * 4)))) ||
-        (c->wbf16 && ((r = dalloc(c, &b.Xp, ee::batch_plane_bytes(b.max_positions, static_cast<int>(H)))) ||
-                      (r = dalloc(c, &b.Op, ee::batch_plane_bytes(b.max_positions, static_cast<int>(A * D)))) ||
-                      (r = dalloc(c, &b.Ap, ee::batch_plane_bytes(b.max_positions, static_cast<int>(F)))))) ||
-        (r = dalloc(c, &b.gemm_ws, b.gemm_ws_floats * 4)) || (r = dalloc(c, &b.attn_ws, b.attn_ws_floats * 4)) ||
-        (r = dalloc(c, &b.tile_ctr, b.n_tile_ctr * 4)))
+        (r = dalloc(c, &b.Xp, ee::batch_plane_bytes(c->wbf16, b.max_positions, static_cast<int>(H)))) ||
+        (r = dalloc(c, &b.Op, ee::batch_plane_bytes(c->wbf16, b.max_positions, static_cast<int>(A * D)))) ||
+        (r = dalloc(c, &b.Ap, ee::batch_plane_bytes(c->wbf16, b.max_positions, static_cast<int>(F)))) ||
+        (r = dalloc(c, &b.gemm_ws, b.gemm_ws_floats * 4)) || (r = dalloc(c, &b.attn_ws, b.attn_ws_floats * 4)))
       return bail(r);
   }
   if ((r = dalloc(c, &c->d_counters, sizeof(ee::Counters)))) return bail(r);
@@ -936,7 +929,7 @@ static int batched_full_depth(ee_ctx* c, const int32_t* d_tokens, int n, bool he
   ee::BatchPass bp{};
   bp.p = make_params(c, INFINITY, 0);
   bp.layers = c->h_layers.data();
-  bp.tiled = c->wbf16 ? c->tiled.data() : nullptr;
+  bp.tiled = c->tiled.data();
   bp.buf = c->bbuf;
   if (c->prefill_chunk > 0) bp.buf.max_positions = std::min(c->prefill_chunk, c->bbuf.max_positions);
   bp.wbf16 = c->wbf16;
@@ -1431,9 +1424,9 @@ static void destroy_impl(ee_ctx* c) {
   dfree(c->d_ring_tok); dfree(c->d_ring_exit); dfree(c->d_ring_would); dfree(c->d_ring_conf); dfree(c->d_ring_mass);
   dfree(c->d_force_tok); dfree(c->d_force_exit); dfree(c->d_dbg_r); dfree(c->d_dbg_f);
   dfree(c->d_timeline);
-  dfree(c->bbuf.X); dfree(c->bbuf.Q); dfree(c->bbuf.O); dfree(c->bbuf.Act);
+  dfree(c->bbuf.X); dfree(c->bbuf.Q);
   dfree(c->bbuf.Xp); dfree(c->bbuf.Op); dfree(c->bbuf.Ap);
-  dfree(c->bbuf.gemm_ws); dfree(c->bbuf.attn_ws); dfree(c->bbuf.tile_ctr);
+  dfree(c->bbuf.gemm_ws); dfree(c->bbuf.attn_ws);
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);

@@ -15,17 +15,16 @@
 //   3. W_o:    X += O W_o^T;
 //   4. gate/up: A = SiLU(RMSNorm(X; g_mlp) W_g^T) * (RMSNorm(X; g_mlp) W_u^T);
 //   5. down:   X += A W_d^T.
-// With bf16 weights the products run on the matrix cores (ee_mm.h): the
-// producer of each vector splits it into bf16 terms once, and the residual
-// products store the partial sums of their K slices, which the kernel that
-// prepares the next product's input adds up in slice order. With fp32 weights
-// the vector ALU computes them (k_bp_gemm), the last workgroup to finish a
-// tile adding its K slices. Every result is independent of scheduling.
+// The products run on the matrix cores (ee_mm.h): the producer of each vector
+// writes it in operand order (for bf16 weights split into bf16 terms), and the
+// residual products store the partial sums of their K slices, which the kernel
+// that prepares the next product's input adds up in slice order. Every result
+// is independent of scheduling.
 //
 // Numerics follow the decode program: weights as stored (bf16 or fp32),
 // activations and accumulation fp32, cache entries rounded to the storage
 // type (round to nearest even), RMSNorm as x * rsqrt(mean(x^2) + eps) * g
-// (the row's scale is applied to the finished dot products), e^x in the
+// , e^x in the
 // softmax and SiLU on the hardware base-2 exponential.
 #include <math.h>
 #include <stdint.h>
@@ -43,69 +42,19 @@ namespace {
 // ---------------------------------------------------------------------------
 // helpers (this file's own; the decode kernels keep theirs)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void st_agent(float* p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float ld_agent(const float* p) {
-  return __hip_atomic_load(const_cast<float*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_agent2(float* p, float a, float b) {  // p 8-byte aligned
-  __hip_atomic_store(reinterpret_cast<uint64_t*>(p),
-                     static_cast<uint64_t>(__float_as_uint(a)) | (static_cast<uint64_t>(__float_as_uint(b)) << 32),
-                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float2 ld_agent2(const float* p) {
-  const uint64_t v = __hip_atomic_load(reinterpret_cast<uint64_t*>(const_cast<float*>(p)), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-  return make_float2(__uint_as_float(static_cast<uint32_t>(v)), __uint_as_float(static_cast<uint32_t>(v >> 32)));
-}
-__device__ __forceinline__ void drain_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 __device__ __forceinline__ float exp_hw(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896341f); }
 
-template <typename WT>
-struct St;
-
-template <>
-struct St<uint16_t> {  // bf16 bit patterns
-  __device__ static inline void unpack(const uint4& w, float* f) {
-    f[0] = __uint_as_float(w.x << 16);
-    f[1] = __uint_as_float(w.x & 0xffff0000u);
-    f[2] = __uint_as_float(w.y << 16);
-    f[3] = __uint_as_float(w.y & 0xffff0000u);
-    f[4] = __uint_as_float(w.z << 16);
-    f[5] = __uint_as_float(w.z & 0xffff0000u);
-    f[6] = __uint_as_float(w.w << 16);
-    f[7] = __uint_as_float(w.w & 0xffff0000u);
-  }
-  __device__ static inline uint32_t bits(float x) {  // round to nearest even
-    uint32_t u = __float_as_uint(x);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return u >> 16;
-  }
-  __device__ static inline void store_pair(uint16_t* p, float a, float b) {
-    *reinterpret_cast<uint32_t*>(p) = bits(a) | (bits(b) << 16);
-  }
-  __device__ static inline float2 load_pair(const uint16_t* p) {
-    const uint32_t u = *reinterpret_cast<const uint32_t*>(p);
-    return make_float2(__uint_as_float(u << 16), __uint_as_float(u & 0xffff0000u));
-  }
-};
-
-template <>
-struct St<float> {
-  static constexpr int N = 4;
-  __device__ static inline void unpack(const uint4& w, float* f) {
-    f[0] = __uint_as_float(w.x);
-    f[1] = __uint_as_float(w.y);
-    f[2] = __uint_as_float(w.z);
-    f[3] = __uint_as_float(w.w);
-  }
-  __device__ static inline void store_pair(float* p, float a, float b) {
-    *reinterpret_cast<float2*>(p) = make_float2(a, b);
-  }
-  __device__ static inline float2 load_pair(const float* p) { return *reinterpret_cast<const float2*>(p); }
-};
+// four neighbouring cache elements (p 8- or 16-byte aligned)
+__device__ __forceinline__ uint32_t bf16_bits(float x) {  // round to nearest even
+  uint32_t u = __float_as_uint(x);
+  u += 0x7fffu + ((u >> 16) & 1u);
+  return u >> 16;
+}
+__device__ __forceinline__ void store4(uint16_t* p, const f32x4& v) {
+  *reinterpret_cast<uint2*>(p) =
+      make_uint2(bf16_bits(v[0]) | (bf16_bits(v[1]) << 16), bf16_bits(v[2]) | (bf16_bits(v[3]) << 16));
+}
+__device__ __forceinline__ void store4(float* p, const f32x4& v) { *reinterpret_cast<f32x4*>(p) = v; }
 
 __device__ __forceinline__ int64_t cache_off(const int32_t* block_table, int page_shift, int page_size, int K,
                                              int D, int64_t layer_base, int pos, int kvh) {
@@ -114,21 +63,14 @@ __device__ __forceinline__ int64_t cache_off(const int32_t* block_table, int pag
   return layer_base + ((static_cast<int64_t>(page) * K + kvh) * page_size + slot) * D;
 }
 
-// Wave reductions: DPP within rows of 16 lanes, then the four row results
-// by readlane; every lane gets the same value, summed in a fixed order.
+// Wave sum: DPP within rows of 16 lanes, then the four row results by
+// readlane; every lane gets the same value, summed in a fixed order.
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
 __device__ __forceinline__ float lane_of(float v, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-__device__ __forceinline__ float wave_max64(float v) {
-  v = fmaxf(v, dpp_mov<0xB1>(v));   // lane ^ 1
-  v = fmaxf(v, dpp_mov<0x4E>(v));   // lane ^ 2
-  v = fmaxf(v, dpp_mov<0x141>(v));  // the other quad of the 8
-  v = fmaxf(v, dpp_mov<0x140>(v));  // the other 8 of the 16
-  return fmaxf(fmaxf(lane_of(v, 0), lane_of(v, 16)), fmaxf(lane_of(v, 32), lane_of(v, 48)));
 }
 __device__ __forceinline__ float wave_sum64(float v) {
   v += dpp_mov<0xB1>(v);
@@ -176,28 +118,17 @@ __global__ __launch_bounds__(256) void k_bp_embed(const WT* __restrict__ E, cons
 }
 
 // ---------------------------------------------------------------------------
-// tiled matrix product Y[P][N] = A[P][K] W[N][K]^T with fused RMSNorm of A
-// (when gain is set) and an epilogue. Block tile BM positions x BN weight
-// rows, 256 threads, each TM x 4 outputs; K in stages of BK (one 128-byte
-// line of a weight row), the next stage's tiles loaded into registers while
-// the current one is consumed from LDS.
+// the products' epilogues (ee_mm.h), and what runs between them
 // ---------------------------------------------------------------------------
 enum : int { kEpiQkv = 0, kEpiResid = 1, kEpiSwiGlu = 2 };
 
 struct GemmArgs {
-  const float* A;      // [P][K] fp32
-  const void* W;       // [N][K] storage type
   int P, N, K;
-  int k_split;         // K elements per split (multiple of BK), splits = gridDim.z
-  const float* gain;   // RMSNorm gain [K] (A is the raw residual stream) or null
-  float eps;
-  float* part;         // split partials [splits][P][N], then [splits][P] sums of squares
-  uint32_t* tile_ctr;  // arrivals per output tile (zero before, reset by the last arrival)
-  // epilogue targets
-  float* Y;            // kEpiResid: X [P][N] (+=); kEpiSwiGlu: A [P][N/2]; kEpiQkv: q [P][A*D]
-  u32x4* planes;       // kEpiSwiGlu on the matrix cores: term planes of A, k32_out K blocks
-  int k32_out;
-  // kEpiQkv: RoPE and cache
+  float* part;         // kEpiResid: partial sums of the K slices [split][P][N], for k_bp_reduce_norm
+  u32x4* planes;       // kEpiSwiGlu: planes of SiLU(gate) * up, `blocks` K blocks
+  int blocks;
+  // kEpiQkv: queries [P][A*D], RoPE and cache
+  float* Q;
   int pos0, Aq, Kh, D;
   const float* rope_cos;
   const float* rope_sin;
@@ -208,271 +139,16 @@ struct GemmArgs {
   int page_shift, page_size;
 };
 
-template <typename WT>
-__device__ __forceinline__ void epi_pair(const GemmArgs& g, int EPI, int m, int n, float y0, float y1) {
-  if (EPI == kEpiResid) {
-    float2* x = reinterpret_cast<float2*>(g.Y + static_cast<int64_t>(m) * g.N + n);
-    float2 v = *x;
-    v.x += y0;
-    v.y += y1;
-    *x = v;
-  } else if (EPI == kEpiSwiGlu) {
-    // interleaved rows: n = 2j gate row j, n + 1 up row j
-    const float s = y0 / (1.f + exp_hw(-y0));
-    g.Y[static_cast<int64_t>(m) * (g.N >> 1) + (n >> 1)] = s * y1;
-  } else {
-    // rows of the repacked QKV matrix: q heads, k heads (RoPE pairs
-    // interleaved: row 2i = dim i, row 2i+1 = dim i + D/2), v heads
-    const int AD = g.Aq * g.D, KD = g.Kh * g.D;
-    const int pos = g.pos0 + m;
-    if (n < AD + KD) {
-      const int head = n / g.D, rl = n - head * g.D, half = g.D >> 1;
-      const float c = g.rope_cos[static_cast<int64_t>(pos) * half + (rl >> 1)];
-      const float s = g.rope_sin[static_cast<int64_t>(pos) * half + (rl >> 1)];
-      const float r0 = y0 * c - y1 * s;
-      const float r1 = y1 * c + y0 * s;
-      if (n < AD) {
-        *reinterpret_cast<float2*>(g.Y + static_cast<int64_t>(m) * AD + n) = make_float2(r0, r1);
-      } else {
-        const int64_t off = cache_off(g.block_table, g.page_shift, g.page_size, g.Kh, g.D, g.layer_base, pos,
-                                      head - g.Aq);
-        St<WT>::store_pair(static_cast<WT*>(g.kpool) + off + rl, r0, r1);
-      }
-    } else {
-      const int j = n - AD - KD;
-      const int head = j / g.D, d = j - head * g.D;
-      const int64_t off = cache_off(g.block_table, g.page_shift, g.page_size, g.Kh, g.D, g.layer_base, pos, head);
-      St<WT>::store_pair(static_cast<WT*>(g.vpool) + off + d, y0, y1);
-    }
-  }
-}
-
-template <typename WT, int EPI, int BM, int BN, int TM>
-__global__ __launch_bounds__(256) void k_bp_gemm(GemmArgs g) {
-  constexpr int TN = 4;
-  constexpr int EPC = St<WT>::N;           // elements per 16-byte chunk
-  constexpr int BK = 128 / sizeof(WT);     // one 128-byte line of a weight row per stage
-  constexpr int CPR = BK / EPC;            // chunks per row per stage (8)
-  constexpr int TX = BN / TN;              // threads along N
-  static_assert((BM / TM) * TX == 256, "256 threads");
-  constexpr int WCH = BN * CPR / 256;      // weight chunks per thread per stage
-  constexpr int AQ = BM * BK / 4;          // float4 of A per stage
-  constexpr int ACH = (AQ + 255) / 256;    // float4 per thread per stage
-  constexpr int LW = BN + 4;               // LDS row strides (floats)
-  constexpr int LA = BM + 4;
-  __shared__ float Ws[BK * LW];
-  __shared__ float As[BK * LA];
-  __shared__ float ss_part[BM];
-  __shared__ int last_flag;
-
-  const int tid = threadIdx.x;
-  const int tx = tid % TX, ty = tid / TX;
-  const int n0 = blockIdx.x * BN, m0 = blockIdx.y * BM;
-  const int split = blockIdx.z, splits = gridDim.z;
-  const int kb = split * g.k_split, ke = min(g.K, kb + g.k_split);
-  const WT* W = static_cast<const WT*>(g.W);
-
-  uint4 wr[WCH];
-  float4 ar[ACH];
-  float ssq[ACH];
-#pragma unroll
-  for (int i = 0; i < ACH; ++i) ssq[i] = 0.f;
-
-  auto load_stage = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < WCH; ++i) {
-      const int c = tid + 256 * i;
-      const int r = c / CPR, q = c - r * CPR;
-      const int n = n0 + r, k = k0 + q * EPC;
-      wr[i] = (n < g.N && k < ke) ? *reinterpret_cast<const uint4*>(W + static_cast<int64_t>(n) * g.K + k)
-                                  : make_uint4(0u, 0u, 0u, 0u);
-    }
-#pragma unroll
-    for (int i = 0; i < ACH; ++i) {
-      const int c = tid + 256 * i;
-      const int m = c / (BK / 4), q = c - m * (BK / 4);
-      const int k = k0 + 4 * q;
-      ar[i] = (c < AQ && m0 + m < g.P && k < ke)
-                  ? *reinterpret_cast<const float4*>(g.A + static_cast<int64_t>(m0 + m) * g.K + k)
-                  : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  };
-  auto store_stage = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < WCH; ++i) {
-      const int c = tid + 256 * i;
-      const int r = c / CPR, q = c - r * CPR;
-      float f[EPC];
-      St<WT>::unpack(wr[i], f);
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) Ws[(q * EPC + e) * LW + r] = f[e];
-    }
-#pragma unroll
-    for (int i = 0; i < ACH; ++i) {
-      const int c = tid + 256 * i;
-      if (c < AQ) {
-        const int m = c / (BK / 4), q = c - m * (BK / 4);
-        const int k = k0 + 4 * q;
-        float4 a = ar[i];
-        if (g.gain) {
-          ssq[i] = fmaf(a.x, a.x, fmaf(a.y, a.y, fmaf(a.z, a.z, fmaf(a.w, a.w, ssq[i]))));
-          if (k < ke) {
-            const float4 gg = *reinterpret_cast<const float4*>(g.gain + k);
-            a.x *= gg.x; a.y *= gg.y; a.z *= gg.z; a.w *= gg.w;
-          }
-        }
-        As[(4 * q + 0) * LA + m] = a.x;
-        As[(4 * q + 1) * LA + m] = a.y;
-        As[(4 * q + 2) * LA + m] = a.z;
-        As[(4 * q + 3) * LA + m] = a.w;
-      }
-    }
-  };
-
-  float acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = 0.f;
-
-  if (kb < ke) load_stage(kb);
-  for (int k0 = kb; k0 < ke; k0 += BK) {
-    __syncthreads();
-    store_stage(k0);
-    __syncthreads();
-    if (k0 + BK < ke) load_stage(k0 + BK);
-#pragma unroll 8
-    for (int k = 0; k < BK; ++k) {
-      float a[TM];
-      if constexpr (TM == 4) {
-        const float4 av = *reinterpret_cast<const float4*>(&As[k * LA + ty * TM]);
-        a[0] = av.x; a[1] = av.y; a[2] = av.z; a[3] = av.w;
-      } else {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) a[i] = As[k * LA + ty * TM + i];
-      }
-      const float4 wv = *reinterpret_cast<const float4*>(&Ws[k * LW + tx * TN]);
-      const float w[TN] = {wv.x, wv.y, wv.z, wv.w};
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-    }
-  }
-
-  // per-row sums of squares of this K-slice: the BK/4 threads of a row are
-  // consecutive lanes; the first of them holds the row's sum
-  if (g.gain) {
-#pragma unroll
-    for (int i = 0; i < ACH; ++i) {
-      float v = ssq[i];
-#pragma unroll
-      for (int o = 1; o < BK / 4; o <<= 1) v += __shfl_xor(v, o);
-      const int c = tid + 256 * i;
-      if (c < AQ && (c % (BK / 4)) == 0) ss_part[c / (BK / 4)] = v;
-    }
-  }
-  __syncthreads();
-
-  const int64_t PN = static_cast<int64_t>(g.P) * g.N;
-  if (splits > 1) {
-    // publish this slice's partial tile; the last arrival merges all slices
-    float* part = g.part + split * PN;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int m = m0 + ty * TM + i;
-      if (m >= g.P) continue;
-#pragma unroll
-      for (int j = 0; j < TN; j += 2) {
-        const int n = n0 + tx * TN + j;
-        if (n < g.N) st_agent2(part + static_cast<int64_t>(m) * g.N + n, acc[i][j], acc[i][j + 1]);
-      }
-    }
-    if (g.gain && tid < BM && m0 + tid < g.P) st_agent(g.part + splits * PN + split * g.P + m0 + tid, ss_part[tid]);
-    drain_stores();
-    __syncthreads();
-    if (tid == 0) {
-      uint32_t* ctr = g.tile_ctr + blockIdx.y * gridDim.x + blockIdx.x;
-      const uint32_t old = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last_flag = old == static_cast<uint32_t>(splits - 1);
-      if (last_flag) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    if (!last_flag) return;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = 0.f;
-    // the slices' partial sums in slice order; each group of kSG slices has
-    // all its loads in flight before the first is added
-    constexpr int kSG = TM >= 4 ? 2 : 8;  // 16 pairs in flight per thread
-    for (int s0 = 0; s0 < splits; s0 += kSG) {
-      float2 v[kSG][TM][TN / 2];
-#pragma unroll
-      for (int u = 0; u < kSG; ++u) {
-        const float* ps = g.part + (s0 + u) * PN;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const int m = m0 + ty * TM + i;
-#pragma unroll
-          for (int j = 0; j < TN; j += 2) {
-            const int n = n0 + tx * TN + j;
-            v[u][i][j / 2] = (s0 + u < splits && m < g.P && n < g.N)
-                                 ? ld_agent2(ps + static_cast<int64_t>(m) * g.N + n)
-                                 : make_float2(0.f, 0.f);
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kSG; ++u)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; j += 2) {
-            acc[i][j] += v[u][i][j / 2].x;
-            acc[i][j + 1] += v[u][i][j / 2].y;
-          }
-    }
-    if (g.gain && tid < BM && m0 + tid < g.P) {
-      float t = 0.f;
-      for (int s0 = 0; s0 < splits; s0 += kSG) {
-        float v[kSG];
-#pragma unroll
-        for (int u = 0; u < kSG; ++u)
-          v[u] = s0 + u < splits ? ld_agent(g.part + splits * PN + (s0 + u) * g.P + m0 + tid) : 0.f;
-#pragma unroll
-        for (int u = 0; u < kSG; ++u) t += v[u];
-      }
-      ss_part[tid] = t;
-    }
-    __syncthreads();
-  }
-
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int ml = ty * TM + i, m = m0 + ml;
-    if (m >= g.P) continue;
-    const float rinv = g.gain ? rsqrtf(ss_part[ml] / static_cast<float>(g.K) + g.eps) : 1.f;
-#pragma unroll
-    for (int j = 0; j < TN; j += 2) {
-      const int n = n0 + tx * TN + j;
-      if (n < g.N) epi_pair<WT>(g, EPI, m, n, acc[i][j] * rinv, acc[i][j + 1] * rinv);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// bf16 weights: the products of ee_mm.h, their epilogues, and what runs
-// between them
-// ---------------------------------------------------------------------------
 // tiled copy of a row-major [N][K] matrix (K a multiple of 8), padded with zeros
-__global__ __launch_bounds__(256) void k_bp_tile_weights(const uint16_t* __restrict__ W, int N, int K, int k32,
+template <typename WT>
+__global__ __launch_bounds__(256) void k_bp_tile_weights(const WT* __restrict__ W, int N, int K, int blocks,
                                                          int64_t chunks, u32x4* __restrict__ T) {
+  using Op = MmOp<WT>;
   for (int64_t c = blockIdx.x * 256ll + threadIdx.x; c < chunks; c += gridDim.x * 256ll) {
     const int lane = static_cast<int>(c & 63);
     const int64_t t = c >> 6;
-    const int64_t n = t / k32 * 16 + (lane & 15);
-    const int k = static_cast<int>(t % k32) * 32 + 8 * (lane >> 4);
+    const int64_t n = t / blocks * 16 + (lane & 15);
+    const int k = static_cast<int>(t % blocks) * Op::kBK + Op::kEl * (lane >> 4);
     T[c] = n < N && k < K ? *reinterpret_cast<const u32x4*>(W + n * K + k) : u32x4{0u, 0u, 0u, 0u};
   }
 }
@@ -499,49 +175,35 @@ __device__ __forceinline__ QkvEpi qkv_epi(const GemmArgs& g, int p, int n) {
   }
   return e;
 }
+template <typename WT>
 __device__ __forceinline__ void qkv_store(const GemmArgs& g, const QkvEpi& e, int p, int n, const f32x4& y) {
   const int AD = g.Aq * g.D, KD = g.Kh * g.D;
   if (n >= AD + KD) {
-    uint16_t* v = static_cast<uint16_t*>(g.vpool) + e.off;
-    *reinterpret_cast<uint2*>(v) = make_uint2(St<uint16_t>::bits(y[0]) | (St<uint16_t>::bits(y[1]) << 16),
-                                              St<uint16_t>::bits(y[2]) | (St<uint16_t>::bits(y[3]) << 16));
+    store4(static_cast<WT*>(g.vpool) + e.off, y);
     return;
   }
-  const float r0 = y[0] * e.c.x - y[1] * e.s.x, r1 = y[1] * e.c.x + y[0] * e.s.x;
-  const float r2 = y[2] * e.c.y - y[3] * e.s.y, r3 = y[3] * e.c.y + y[2] * e.s.y;
-  if (n < AD)
-    *reinterpret_cast<f32x4*>(g.Y + static_cast<int64_t>(p) * AD + n) = f32x4{r0, r1, r2, r3};
-  else
-    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(g.kpool) + e.off) =
-        make_uint2(St<uint16_t>::bits(r0) | (St<uint16_t>::bits(r1) << 16),
-                   St<uint16_t>::bits(r2) | (St<uint16_t>::bits(r3) << 16));
+  const f32x4 r{y[0] * e.c.x - y[1] * e.s.x, y[1] * e.c.x + y[0] * e.s.x, y[2] * e.c.y - y[3] * e.s.y,
+                y[3] * e.c.y + y[2] * e.s.y};
+  if (n < AD) *reinterpret_cast<f32x4*>(g.Q + static_cast<int64_t>(p) * AD + n) = r;
+  else store4(static_cast<WT*>(g.kpool) + e.off, r);
 }
 
-// Epilogue targets of a product on the matrix cores (GemmArgs, with kEpiResid
-// storing its K slices' partial sums in g.part [split][P][N] for
-// k_bp_reduce_norm, and kEpiSwiGlu storing term planes).
-template <int EPI, int RB, int CP, int NW, int PF, int KG>
+template <typename WT, int EPI, int RB, int CP, int NW, int PF, int KG>
 __global__ __launch_bounds__(64 * NW * KG) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_bp_mm(MmArgs m, GemmArgs g) {
   if constexpr (EPI == kEpiQkv) {
-    mm_tile<RB, CP, NW, PF, KG>(
+    mm_tile<WT, RB, CP, NW, PF, KG>(
         m, [&](int p, int n) { return qkv_epi(g, p, n); },
-        [&](int, int p, int n, const f32x4& y, const QkvEpi& e) { qkv_store(g, e, p, n, y); });
+        [&](int, int p, int n, const f32x4& y, const QkvEpi& e) { qkv_store<WT>(g, e, p, n, y); });
   } else {
-    mm_tile<RB, CP, NW, PF, KG>(
+    mm_tile<WT, RB, CP, NW, PF, KG>(
         m, [](int, int) { return 0; },
         [&](int split, int p, int n, const f32x4& y, int) {
           if constexpr (EPI == kEpiResid) {
             *reinterpret_cast<f32x4*>(g.part + (static_cast<int64_t>(split) * m.P + p) * m.N + n) = y;
           } else {
             // interleaved rows: n = 2j gate row j, n + 1 up row j
-            const float a0 = y[0] / (1.f + exp_hw(-y[0])) * y[1];
-            const float a1 = y[2] / (1.f + exp_hw(-y[2])) * y[3];
-            const int j = n >> 1;
-            uint32_t t[3];
-            mm_split2(a0, a1, t);
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-              *(reinterpret_cast<uint32_t*>(g.planes + mm_chunk(p, j & ~7, i, g.k32_out)) + ((j & 7) >> 1)) = t[i];
+            const float a[2] = {y[0] / (1.f + exp_hw(-y[0])) * y[1], y[2] / (1.f + exp_hw(-y[2])) * y[3]};
+            mm_put<WT, 2>(g.planes, g.blocks, p, n >> 1, a);
           }
         });
   }
@@ -549,15 +211,16 @@ __global__ __launch_bounds__(64 * NW * KG) __attribute__((amdgpu_waves_per_eu(2,
 
 // The residual stream after a product, and the input of the next: X += the
 // product's K slices in slice order (splits may be 0), then, with a gain,
-// the term planes of x * rsqrt(mean(x^2) + eps) * gain. One workgroup per
+// the planes of x * rsqrt(mean(x^2) + eps) * gain. One workgroup per
 // position, thread = 8 elements (H <= 2048). The 16 positions of a block of
 // planes go to workgroups of one XCD, whose L2 then merges their 16-byte
 // pieces into whole lines. Bound by the reads of the slices.
 constexpr int kNormThreads = 256;
+template <typename WT>
 __global__ __launch_bounds__(kNormThreads) void k_bp_reduce_norm(float* __restrict__ X, const float* __restrict__ part,
                                                                  int splits, int P, int H,
                                                                  const float* __restrict__ gain, float eps,
-                                                                 u32x4* __restrict__ planes, int k32) {
+                                                                 u32x4* __restrict__ planes, int blocks) {
   __shared__ float red[kNormThreads / 64];
   const int b = blockIdx.x, loc = b >> 3;
   const int p = ((loc >> 4) * 8 + (b & 7)) * 16 + (loc & 15);
@@ -613,30 +276,22 @@ __global__ __launch_bounds__(kNormThreads) void k_bp_reduce_norm(float* __restri
   for (int w = 0; w < kNormThreads / 64; ++w) t += red[w];
   const float r = rsqrtf(t / static_cast<float>(H) + eps);
   if (!on) return;
-  uint32_t w[4][3];
+  float w[8];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int e = 2 * i;
-    mm_split2(x[e >> 2][e & 3] * r * gv[e >> 2][e & 3], x[e >> 2][(e & 3) + 1] * r * gv[e >> 2][(e & 3) + 1], w[i]);
-  }
-#pragma unroll
-  for (int i = 0; i < 3; ++i) planes[mm_chunk(p, k, i, k32)] = u32x4{w[0][i], w[1][i], w[2][i], w[3][i]};
+  for (int i = 0; i < 8; ++i) w[i] = x[i >> 2][i & 3] * r * gv[i >> 2][i & 3];
+  mm_put<WT, 8>(planes, blocks, p, k, w);
 }
 
 // ---------------------------------------------------------------------------
 // causal grouped-query attention of a chunk of queries (positions pos0 ..
-// pos0 + P - 1) over the cache. Block = (KV head, tile of 4 query
-// positions, key split); its waves split the tile's queries and the KV
-// head's query heads; keys in tiles of 64 staged in LDS, lane j = key j of
-// the tile; online softmax per head. One split writes o directly; several
-// write partial records (weighted V, max, sum) merged in split order by
-// k_bp_attn_merge.
+// pos0 + P - 1) over the cache, on the matrix cores. With one key split the
+// output's planes are written directly; several write partial records
+// (weighted V, max, sum) merged in split order by k_bp_attn_merge.
 // ---------------------------------------------------------------------------
 struct AttnArgs {
   const float* Q;      // [P][A*D], pair-interleaved within heads (as the cached keys)
-  float* O;            // [P][A*D], natural order (fp32 weights), or
-  u32x4* planes;       // its term planes (bf16 weights), k32 K blocks
-  int k32;
+  u32x4* planes;       // planes of the output [P][A*D], `blocks` K blocks
+  int blocks;
   float* part;         // [P][A][nsplit][D + 2]
   const void* kpool;
   const void* vpool;
@@ -650,224 +305,26 @@ struct AttnArgs {
 
 constexpr int kKT = 64;  // keys per LDS tile
 
-// DPL neighbouring elements (element e of query qi, e even for DPL = 2) of the attention output
-template <typename WT, int DPL>
-__device__ __forceinline__ void attn_store(const AttnArgs& a, int qi, int e, const float (&o)[DPL]) {
-  if constexpr (sizeof(WT) == 4) {
-#pragma unroll
-    for (int i = 0; i < DPL; ++i) a.O[static_cast<int64_t>(qi) * a.A * a.D + e + i] = o[i];
-  } else {
-    uint32_t t[3];
-    mm_split2(o[0], DPL == 2 ? o[DPL - 1] : 0.f, t);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      uint16_t* c = reinterpret_cast<uint16_t*>(a.planes + mm_chunk(qi, e & ~7, i, a.k32)) + (e & 7);
-      if constexpr (DPL == 2) *reinterpret_cast<uint32_t*>(c) = t[i];
-      else *c = static_cast<uint16_t>(t[i]);
-    }
-  }
-}
-
-// Block = (KV head, tile of QT query positions, key split); wave w takes
-// query position w % QT and the GW query heads (w / QT) GW .. + GW - 1 of the
-// KV head. With many blocks (a prompt) QT = 4 and each wave takes all G heads
-// (more waves would read each key tile from LDS once per wave), at most two
-// workgroups per compute unit (as LDS allows), so each wave may hold up to
-// 256 registers; with few blocks (a refresh) QT = 2 and one head per wave,
-// so that the G heads' dot products run on G waves per position. The first
-// four waves stage each key tile in LDS.
-// (fp32 caches of wide heads may need more registers: their lower bound is 1)
-template <typename WT, int D, int G, int GW, int QT>
-__global__ __launch_bounds__(64 * QT * (G / GW))
-__attribute__((amdgpu_waves_per_eu(sizeof(WT) == 4 ? 1 : ((QT * (G / GW) + 3) / 4 > 2 ? (QT * (G / GW) + 3) / 4 : 2),
-                                   (QT * (G / GW) + 3) / 4 > 2 ? (QT * (G / GW) + 3) / 4 : 2))) void k_bp_attn(AttnArgs a) {
-  static_assert(G % GW == 0, "head groups cover the KV head's query heads");
-  static_assert(QT * (G / GW) >= 4, "four waves stage the key tiles");
-  constexpr int kQT = QT;
-  constexpr int EPC = St<WT>::N;
-  constexpr int CPK = D / EPC;          // 16-byte chunks per cache row
-  constexpr int DPL = D / 64;           // output dimensions per lane (1 or 2)
-  constexpr int KST = CPK + 1;          // key rows padded by one chunk: lane j reads row j
-  __shared__ uint4 Ks[kKT * KST];
-  __shared__ uint4 Vs[kKT * CPK];
-  __shared__ float Qs[kQT][G][D];
-  __shared__ float Ps[kQT][G][kKT];
-
-  constexpr int HG = G / GW;            // waves per query position
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int qw = HG > 1 ? wave % kQT : wave, h0 = HG > 1 ? (wave / kQT) * GW : 0;
-  const bool loader = HG > 1 ? tid < 256 : true;  // the threads that stage key tiles
-  const int nqt = (a.P + kQT - 1) / kQT;
-  const int item = blockIdx.x;
-  const int kvh = item / (nqt * a.nsplit);
-  const int rem = item - kvh * nqt * a.nsplit;
-  const int qt = rem / a.nsplit, sp = rem - qt * a.nsplit;
-  const int qi = qt * kQT + qw;                 // query index within the chunk
-  const bool active = qi < a.P;
-  const int qpos = a.pos0 + qi;                 // its position
-  const int t_end = a.pos0 + min(a.P, (qt + 1) * kQT);  // keys needed by the tile: [0, t_end)
-  const int kb = sp * a.keys_per_split;
-  const int ke = min(t_end, kb + a.keys_per_split);
-
-  constexpr int CPT = kKT * CPK / 256;  // chunks of K (and of V) per loading thread per tile
-  // cache offsets of a tile's chunks (its page lookups)
-  auto offsets = [&](int k0, int64_t (&off)[CPT]) {
-#pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const int c = tid + 256 * i;
-      const int j = c / CPK, q = c - j * CPK;
-      const int key = min(k0 + j, ke - 1);
-      off[i] = cache_off(a.block_table, a.page_shift, a.page_size, a.K, D, a.layer_base, key, kvh) + q * EPC;
-    }
-  };
-  // the wave's query rows (its GW heads) and the first tile's page lookups,
-  // every load in flight at once
-  int64_t off[CPT];
-  if (loader && kb < ke) offsets(kb, off);
-  {
-    constexpr int QPL = GW * D / 64;
-    float qv[QPL];
-#pragma unroll
-    for (int u = 0; u < QPL; ++u) {
-      const int i = lane + 64 * u, h = h0 + i / D, d = i % D;
-      qv[u] = active ? a.Q[static_cast<int64_t>(qi) * a.A * D + (kvh * G + h) * D + d] : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < QPL; ++u) {
-      const int i = lane + 64 * u, h = h0 + i / D, d = i % D;
-      Qs[qw][h][d] = qv[u];
-    }
-  }
-  float m_run[GW], l_run[GW], acc[GW][DPL];
-#pragma unroll
-  for (int h = 0; h < GW; ++h) {
-    m_run[h] = -INFINITY;
-    l_run[h] = 0.f;
-#pragma unroll
-    for (int e = 0; e < DPL; ++e) acc[h][e] = 0.f;
-  }
-  const WT* kp = static_cast<const WT*>(a.kpool);
-  const WT* vp = static_cast<const WT*>(a.vpool);
-
-  for (int k0 = kb; k0 < ke; k0 += kKT) {
-    // native vectors: a copy of the uint4 struct from global memory to LDS
-    // through registers compiles to memory-to-memory copies through private
-    // memory, which serialise the loads
-    u32x4 kv[CPT], vv[CPT];
-    if (loader) {
-      if (k0 != kb) offsets(k0, off);
-#pragma unroll
-      for (int i = 0; i < CPT; ++i) {
-        kv[i] = *reinterpret_cast<const u32x4*>(kp + off[i]);
-        vv[i] = *reinterpret_cast<const u32x4*>(vp + off[i]);
-      }
-    }
-    __syncthreads();  // previous tile consumed (and Qs written before the first)
-    if (loader) {
-#pragma unroll
-      for (int i = 0; i < CPT; ++i) {
-        const int c = tid + 256 * i;
-        const int j = c / CPK, q = c - j * CPK;
-        *reinterpret_cast<u32x4*>(&Ks[j * KST + q]) = kv[i];  // keys past ke repeat key ke - 1; masked
-        *reinterpret_cast<u32x4*>(&Vs[c]) = vv[i];
-      }
-    }
-    __syncthreads();
-    const int key = k0 + lane;
-    const bool valid = active && key < ke && key <= qpos;
-    float s[GW];
-#pragma unroll
-    for (int h = 0; h < GW; ++h) s[h] = 0.f;
-#pragma unroll 2
-    for (int q = 0; q < CPK; ++q) {
-      float kf[EPC];
-      St<WT>::unpack(Ks[lane * KST + q], kf);
-#pragma unroll
-      for (int h = 0; h < GW; ++h) {
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) s[h] = fmaf(Qs[qw][h0 + h][q * EPC + e], kf[e], s[h]);
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < GW; ++h) {
-      const float sv = valid ? s[h] * a.scale : -INFINITY;
-      const float mt = wave_max64(sv);
-      const float mn = fmaxf(m_run[h], mt);
-      float p = 0.f, alpha = 1.f;
-      if (mn != -INFINITY) {
-        p = exp_hw(sv - mn);  // 0 for masked keys
-        alpha = exp_hw(m_run[h] - mn);
-      }
-      l_run[h] = l_run[h] * alpha + wave_sum64(p);
-      m_run[h] = mn;
-#pragma unroll
-      for (int e = 0; e < DPL; ++e) acc[h][e] *= alpha;
-      Ps[qw][h0 + h][lane] = p;
-    }
-    __builtin_amdgcn_wave_barrier();
-    // weighted values: lane owns dimensions DPL * lane .. + DPL - 1
-#pragma unroll 4
-    for (int j = 0; j < kKT; ++j) {
-      float v[DPL];
-      if constexpr (DPL == 2) {
-        const float2 vv2 = St<WT>::load_pair(reinterpret_cast<const WT*>(&Vs[j * CPK]) + 2 * lane);
-        v[0] = vv2.x;
-        v[1] = vv2.y;
-      } else {
-        const WT* vr = reinterpret_cast<const WT*>(&Vs[j * CPK]);
-        if constexpr (sizeof(WT) == 2) v[0] = __uint_as_float(static_cast<uint32_t>(vr[lane]) << 16);
-        else v[0] = vr[lane];
-      }
-#pragma unroll
-      for (int h = 0; h < GW; ++h) {
-        const float pj = Ps[qw][h0 + h][j];
-#pragma unroll
-        for (int e = 0; e < DPL; ++e) acc[h][e] = fmaf(pj, v[e], acc[h][e]);
-      }
-    }
-  }
-  if (!active) return;
-#pragma unroll
-  for (int h = 0; h < GW; ++h) {
-    const int head = kvh * G + h0 + h;
-    if (a.nsplit == 1) {
-      const float inv = 1.f / l_run[h];
-#pragma unroll
-      for (int e = 0; e < DPL; ++e) acc[h][e] *= inv;
-      attn_store<WT, DPL>(a, qi, head * D + DPL * lane, acc[h]);
-    } else {
-      float* r = a.part + ((static_cast<int64_t>(qi) * a.A + head) * a.nsplit + sp) * (D + 2);
-#pragma unroll
-      for (int e = 0; e < DPL; ++e) r[DPL * lane + e] = acc[h][e];
-      if (lane == 0) {
-        r[D] = m_run[h];
-        r[D + 1] = l_run[h];
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// The same attention on the matrix cores, for bf16 caches. Workgroup = (KV
-// head, QB blocks of 16 query positions, key split); wave = (one of the KV
-// head's G query heads, one block of 16 positions), so that all G heads share
-// the key and value tiles staged in LDS. Per tile of 64 keys a wave computes
-// S^T = K Q^T (rows keys, columns positions) and O^T += V^T P^T: a lane then
-// holds one position's scores for 16 keys, the softmax needs two exchanges
-// between lanes, the scores' layout is already the second product's operand
-// (the key order of its K slots is permuted alike on both sides), and the
-// output's layout that of the term planes. Values are read transposed from
-// LDS (ds_read_b64_tr_b16). Keys and values are exact bf16 operands; queries
-// and probabilities are split exactly into three bf16 terms, so both products
-// carry fp32 accumulation error only.
-// A tile is 96 MFMAs (1536 cycles) per wave at D = 128 and about as much
-// vector work (exponentials, the split of the probabilities), which other
-// waves overlap. The vector-ALU form above is bound by its FMAs and serial
-// LDS reads: 1024 queries over 1024 to 8192 keys (six heads of 128 per KV
-// head) took 595 us a layer on average, this 104 (172 for the last 1024, 840
-// TFLOP/s of term products); 512 queries over 512 keys 47 us, this 24 in one
-// pass over the keys and less with key splits.
-// ---------------------------------------------------------------------------
+// Workgroup = (KV head, QB blocks of 16 query positions, key split); wave =
+// (one of the KV head's G query heads, one block of 16 positions), so that all
+// G heads share the key and value tiles staged in LDS. Per tile of 64 keys a
+// wave computes S^T = K Q^T (rows keys, columns positions) and O^T += V^T P^T:
+// a lane then holds one position's scores for 16 keys, the softmax needs two
+// exchanges between lanes, the scores' layout is already the second product's
+// operand (the key order of its K slots is permuted alike on both sides), and
+// the output's layout that of the planes. Keys and values are exact operands;
+// with bf16 caches queries and probabilities are split exactly into three bf16
+// terms and values are read transposed from LDS (ds_read_b64_tr_b16), so both
+// products carry fp32 accumulation error only.
+// A tile is 96 MFMAs (1536 cycles) per wave at D = 128 in bf16 and about as
+// much vector work (exponentials, the split of the probabilities), which other
+// waves overlap. A vector-ALU form (dot products from LDS, one wave per
+// position) was bound by its FMAs and serial LDS reads: 1024 queries over 1024
+// to 8192 bf16 keys (six heads of 128 per KV head) took 595 us a layer on
+// average, this 104 (172 for the last 1024, 840 TFLOP/s of term products); 512
+// queries over 512 keys 47 us, this 24 in one pass over the keys and less with
+// key splits; 1024 queries over 1024 fp32 keys (two heads of 64) 46 us, this
+// 13.
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float max_groups(float v) {  // over the four 16-lane groups
@@ -883,13 +340,16 @@ __device__ __forceinline__ float sum_groups(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-template <int D, int G, int QB>
-__global__ __launch_bounds__(64 * G * QB) __attribute__((amdgpu_waves_per_eu(2))) void k_bp_attn_mfma(AttnArgs a) {
+template <typename WT, int D, int G, int QB>
+__global__ __launch_bounds__(64 * G * QB) __attribute__((amdgpu_waves_per_eu(2))) void k_bp_attn(AttnArgs a) {
+  using Op = MmOp<WT>;
+  constexpr bool kBf = sizeof(WT) == 2;
+  constexpr int TM = Op::kTerms;
   constexpr int NT = 64 * G * QB;
-  constexpr int CPK = D / 8;        // 16-byte chunks per cache row
+  constexpr int CPK = D / Op::kEl;  // 16-byte chunks per cache row
   constexpr int KST = CPK + 1;      // padded LDS rows: 16 lanes reading a column of 16 rows, and the
-  constexpr int VST = CPK + 2;      // transposed reads of 4 rows x 32 bytes, each touch every bank once
-  constexpr int KS = D / 32, DB = D / 16;
+  constexpr int VST = CPK + (kBf ? 2 : 1);  // reads of 4 rows x 32 (transposed) or 64 bytes, touch each bank once
+  constexpr int KS = CPK / 4, DB = D / 16;
   constexpr int CPT = (kKT * CPK + NT - 1) / NT;  // chunks of K (and of V) per thread per tile
   __shared__ u32x4 Ks[kKT * KST];
   __shared__ u32x4 Vs[kKT * VST];
@@ -912,10 +372,10 @@ __global__ __launch_bounds__(64 * G * QB) __attribute__((amdgpu_waves_per_eu(2))
 
   auto offset = [&](int k0, int c) {
     const int j = c / CPK, q = c - j * CPK;
-    return cache_off(a.block_table, a.page_shift, a.page_size, a.K, D, a.layer_base, min(k0 + j, ke - 1), kvh) + q * 8;
+    return cache_off(a.block_table, a.page_shift, a.page_size, a.K, D, a.layer_base, min(k0 + j, ke - 1), kvh) + q * Op::kEl;
   };
-  const uint16_t* kp = static_cast<const uint16_t*>(a.kpool);
-  const uint16_t* vp = static_cast<const uint16_t*>(a.vpool);
+  const WT* kp = static_cast<const WT*>(a.kpool);
+  const WT* vp = static_cast<const WT*>(a.vpool);
   u32x4 kv[CPT], vv[CPT];
   auto load_tile = [&](int k0) {  // keys past ke repeat key ke - 1; their scores are masked
     int64_t off[CPT];
@@ -929,21 +389,26 @@ __global__ __launch_bounds__(64 * G * QB) __attribute__((amdgpu_waves_per_eu(2))
   };
   if (kb < ke) load_tile(kb);
 
-  // the query's terms: k slots 8 lg .. + 7 of each 32 dimensions
-  bf16x8 qf[KS][3];
+  // the query's operands: chunk 4 s + lg of its row
+  u32x4 qf[KS][TM];
   {
     const float* q = a.Q + static_cast<int64_t>(min(qi, a.P - 1)) * a.A * D + head * D;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      const f32x4 x0 = *reinterpret_cast<const f32x4*>(q + 32 * s + 8 * lg);
-      const f32x4 x1 = *reinterpret_cast<const f32x4*>(q + 32 * s + 8 * lg + 4);
-      uint32_t w[4][3];
-      mm_split2(x0[0], x0[1], w[0]);
-      mm_split2(x0[2], x0[3], w[1]);
-      mm_split2(x1[0], x1[1], w[2]);
-      mm_split2(x1[2], x1[3], w[3]);
+      const float* x = q + (4 * s + lg) * Op::kEl;
+      const f32x4 x0 = *reinterpret_cast<const f32x4*>(x);
+      if constexpr (kBf) {
+        const f32x4 x1 = *reinterpret_cast<const f32x4*>(x + 4);
+        uint32_t w[4][3];
+        mm_split2(x0[0], x0[1], w[0]);
+        mm_split2(x0[2], x0[3], w[1]);
+        mm_split2(x1[0], x1[1], w[2]);
+        mm_split2(x1[2], x1[3], w[3]);
 #pragma unroll
-      for (int t = 0; t < 3; ++t) qf[s][t] = __builtin_bit_cast(bf16x8, u32x4{w[0][t], w[1][t], w[2][t], w[3][t]});
+        for (int t = 0; t < 3; ++t) qf[s][t] = u32x4{w[0][t], w[1][t], w[2][t], w[3][t]};
+      } else {
+        qf[s][0] = __builtin_bit_cast(u32x4, x0);
+      }
     }
   }
   const float scale2 = a.scale * 1.44269504088896341f;  // scores in units of log2
@@ -972,13 +437,13 @@ __global__ __launch_bounds__(64 * G * QB) __attribute__((amdgpu_waves_per_eu(2))
     for (int b = 0; b < 4; ++b) s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      bf16x8 kf[4];
+      u32x4 kf[4];
 #pragma unroll
-      for (int b = 0; b < 4; ++b) kf[b] = __builtin_bit_cast(bf16x8, Ks[(16 * b + lr) * KST + 4 * ks + lg]);
+      for (int b = 0; b < 4; ++b) kf[b] = Ks[(16 * b + lr) * KST + 4 * ks + lg];
 #pragma unroll
-      for (int t = 0; t < 3; ++t)
+      for (int t = 0; t < TM; ++t)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) s[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[b], qf[ks][t], s[b], 0, 0, 0);
+        for (int b = 0; b < 4; ++b) s[b] = Op::mma(kf[b], qf[ks][t], s[b]);
     }
     if (k0 + kKT > min(ke, a.pos0 + q0 + 1)) {  // some key of the tile is past the split or a query
       const int last = min(ke - 1, qpos);
@@ -998,8 +463,9 @@ __global__ __launch_bounds__(64 * G * QB) __attribute__((amdgpu_waves_per_eu(2))
     const float alpha = __builtin_amdgcn_exp2f(m - ms);
     m = mn;
     l *= alpha;
-    // probabilities, split: operand word of keys (i, i + 1) of block b: [2 (b & 1) + i / 2] of K slots b / 2
+    // probabilities; bf16: split, operand word of keys (i, i + 1) of block b: [2 (b & 1) + i / 2] of K slots b / 2
     uint32_t pw[2][4][3];
+    float pf[4][4];
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -1007,33 +473,52 @@ __global__ __launch_bounds__(64 * G * QB) __attribute__((amdgpu_waves_per_eu(2))
         const float p0 = __builtin_amdgcn_exp2f(fmaf(s[b][i], scale2, -ms));
         const float p1 = __builtin_amdgcn_exp2f(fmaf(s[b][i + 1], scale2, -ms));
         l += p0 + p1;
-        mm_split2(p0, p1, pw[b >> 1][2 * (b & 1) + (i >> 1)]);
+        if constexpr (kBf) {
+          mm_split2(p0, p1, pw[b >> 1][2 * (b & 1) + (i >> 1)]);
+        } else {
+          pf[b][i] = p0;
+          pf[b][i + 1] = p1;
+        }
       }
 #pragma unroll
     for (int d = 0; d < DB; ++d) o[d] *= alpha;
+    if constexpr (kBf) {
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      bf16x8 vf[DB];
+      for (int ks = 0; ks < 2; ++ks) {
+        u32x4 vf[DB];
 #pragma unroll
-      for (int d = 0; d < DB; ++d) {
-        // 16 lanes read keys 4 lg .. + 3 (of block 2 ks, then 2 ks + 1) x dimensions 16 d .. + 15; lane lr
-        // receives dimension 16 d + lr of the four keys
-        s16x4 v[2];
+        for (int d = 0; d < DB; ++d) {
+          // 16 lanes read keys 4 lg .. + 3 (of block 2 ks, then 2 ks + 1) x dimensions 16 d .. + 15; lane lr
+          // receives dimension 16 d + lr of the four keys
+          s16x4 v[2];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int key = 32 * ks + 16 * u + 4 * lg + (lr >> 2);
-          const uint16_t* src = reinterpret_cast<const uint16_t*>(&Vs[key * VST]) + 16 * d + 4 * (lr & 3);
-          v[u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src));
+          for (int u = 0; u < 2; ++u) {
+            const int key = 32 * ks + 16 * u + 4 * lg + (lr >> 2);
+            const uint16_t* src = reinterpret_cast<const uint16_t*>(&Vs[key * VST]) + 16 * d + 4 * (lr & 3);
+            v[u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(src));
+          }
+          vf[d] = __builtin_bit_cast(u32x4, __builtin_shufflevector(v[0], v[1], 0, 1, 2, 3, 4, 5, 6, 7));
         }
-        vf[d] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(v[0], v[1], 0, 1, 2, 3, 4, 5, 6, 7));
-      }
 #pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        const bf16x8 pf =
-            __builtin_bit_cast(bf16x8, u32x4{pw[ks][0][t], pw[ks][1][t], pw[ks][2][t], pw[ks][3][t]});
+        for (int t = 0; t < TM; ++t) {
+          const u32x4 pt{pw[ks][0][t], pw[ks][1][t], pw[ks][2][t], pw[ks][3][t]};
 #pragma unroll
-        for (int d = 0; d < DB; ++d) o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[d], pf, o[d], 0, 0, 0);
+          for (int d = 0; d < DB; ++d) o[d] = Op::mma(vf[d], pt, o[d]);
+        }
       }
+    } else {
+      // K slot lg of instruction i of block b: key 16 b + 4 lg + i
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float* src = reinterpret_cast<const float*>(&Vs[(16 * b + 4 * lg + i) * VST]) + lr;
+          float v[DB];
+#pragma unroll
+          for (int d = 0; d < DB; ++d) v[d] = src[16 * d];
+#pragma unroll
+          for (int d = 0; d < DB; ++d) o[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[d], pf[b][i], o[d], 0, 0, 0);
+        }
     }
   }
   const float lsum = sum_groups(l);
@@ -1042,14 +527,8 @@ __global__ __launch_bounds__(64 * G * QB) __attribute__((amdgpu_waves_per_eu(2))
     const float inv = 1.f / lsum;
 #pragma unroll
     for (int d = 0; d < DB; ++d) {
-      const int e = head * D + 16 * d + 4 * lg;
-      uint32_t w[2][3];
-      mm_split2(o[d][0] * inv, o[d][1] * inv, w[0]);
-      mm_split2(o[d][2] * inv, o[d][3] * inv, w[1]);
-#pragma unroll
-      for (int t = 0; t < 3; ++t)
-        *(reinterpret_cast<uint2*>(a.planes + mm_chunk(qi, e & ~7, t, a.k32)) + ((e & 7) >> 2)) =
-            make_uint2(w[0][t], w[1][t]);
+      const float w[4] = {o[d][0] * inv, o[d][1] * inv, o[d][2] * inv, o[d][3] * inv};
+      mm_put<WT, 4>(a.planes, a.blocks, qi, head * D + 16 * d + 4 * lg, w);
     }
   } else {
     float* r = a.part + ((static_cast<int64_t>(qi) * a.A + head) * a.nsplit + sp) * (D + 2);
@@ -1063,11 +542,10 @@ __global__ __launch_bounds__(64 * G * QB) __attribute__((amdgpu_waves_per_eu(2))
 }
 
 // one wave per (query, head): the splits' partial records in split order
-// (maxima in units of log2 with bf16 caches, of e with fp32 caches)
+// (maxima in units of log2)
 template <typename WT, int D>
 __global__ __launch_bounds__(256) void k_bp_attn_merge(AttnArgs a) {
   constexpr int DPL = D / 64;
-  auto ex = [](float x) { return sizeof(WT) == 2 ? __builtin_amdgcn_exp2f(x) : exp_hw(x); };
   const int w = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (w >= a.P * a.A) return;
   const float* r = a.part + static_cast<int64_t>(w) * a.nsplit * (D + 2);
@@ -1093,14 +571,14 @@ __global__ __launch_bounds__(256) void k_bp_attn_merge(AttnArgs a) {
 #pragma unroll
     for (int u = 0; u < kSG; ++u) cm = fmaxf(cm, ms[u]);
     if (cm != -INFINITY) {
-      const float sc = ex(M - cm);  // 0 while nothing has been merged
+      const float sc = __builtin_amdgcn_exp2f(M - cm);  // 0 while nothing has been merged
       den *= sc;
 #pragma unroll
       for (int e = 0; e < DPL; ++e) num[e] *= sc;
 #pragma unroll
       for (int u = 0; u < kSG; ++u) {
         if (ms[u] == -INFINITY) continue;  // absent, or a split wholly past the query's position
-        const float f = ex(ms[u] - cm);
+        const float f = __builtin_amdgcn_exp2f(ms[u] - cm);
         den = fmaf(f, ls[u], den);
 #pragma unroll
         for (int e = 0; e < DPL; ++e) num[e] = fmaf(f, vs[u][e], num[e]);
@@ -1112,7 +590,7 @@ __global__ __launch_bounds__(256) void k_bp_attn_merge(AttnArgs a) {
   const float inv = 1.f / den;
 #pragma unroll
   for (int e = 0; e < DPL; ++e) num[e] *= inv;
-  attn_store<WT, DPL>(a, qi, head * D + DPL * lane, num);
+  mm_put<WT, DPL>(a.planes, a.blocks, qi, head * D + DPL * lane, num);
 }
 
 // ---------------------------------------------------------------------------
@@ -1120,61 +598,7 @@ __global__ __launch_bounds__(256) void k_bp_attn_merge(AttnArgs a) {
 // ---------------------------------------------------------------------------
 namespace {
 
-// Splits of K so that the grid holds at least ~2 workgroups per compute unit,
-// bounded by the partial workspace and by one stage per split.
-void choose_split(int tiles, int P, int N, int K, int BK, size_t ws_floats, int wgs_per_cu, int n_cu, int* k_split,
-                  int* splits, int max_k_split = 1 << 30) {
-  // enough workgroups per compute unit (wgs_per_cu) that their weight loads
-  // in flight together cover the memory latency; at most 32 slices, and
-  // slices of at most max_k_split
-  int s = std::max(1, (wgs_per_cu * n_cu + tiles - 1) / tiles);
-  s = std::max(s, (K + max_k_split - 1) / max_k_split);
-  s = std::min({s, (K + BK - 1) / BK, 32});
-  const size_t per = static_cast<size_t>(P) * N + P;
-  if (per > 0) s = static_cast<int>(std::min<size_t>(s, std::max<size_t>(1, ws_floats / per)));
-  if (s <= 1) {
-    *k_split = K;
-    *splits = 1;
-    return;
-  }
-  int ks = (K + s - 1) / s;
-  ks = (ks + BK - 1) / BK * BK;
-  *k_split = ks;
-  *splits = (K + ks - 1) / ks;
-}
-
-// fp32 weights
-template <typename WT, int EPI>
-hipError_t gemm(const GemmArgs& g0, const BatchBuffers& b, int n_cu, hipStream_t s) {
-  GemmArgs g = g0;
-  constexpr int BK = 128 / sizeof(WT);
-  if (g.P <= 16) {
-    // few positions: narrow tiles (16 positions x 64 rows, one position and
-    // four rows per thread) so that few K-slices fill the device and the
-    // merge of a tile's slices stays short
-    constexpr int BM = 16, BN = 64, TM = 1;
-    const int tiles = ((g.N + BN - 1) / BN) * ((g.P + BM - 1) / BM);
-    int splits;
-    // a tile of 16 positions does little arithmetic per weight byte: many
-    // short K-slices, so that loads of several workgroups per unit overlap
-    choose_split(tiles, g.P, g.N, g.K, BK, b.gemm_ws_floats, 8, n_cu, &g.k_split, &splits);
-    if (static_cast<size_t>(tiles) > b.n_tile_ctr) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_bp_gemm<WT, EPI, BM, BN, TM>), dim3((g.N + BN - 1) / BN, (g.P + BM - 1) / BM, splits),
-                       dim3(256), 0, s, g);
-  } else {
-    constexpr int BM = 64, BN = 64, TM = 4;
-    const int tiles = ((g.N + BN - 1) / BN) * ((g.P + BM - 1) / BM);
-    int splits;
-    choose_split(tiles, g.P, g.N, g.K, BK, b.gemm_ws_floats, 2, n_cu, &g.k_split, &splits);
-    if (static_cast<size_t>(tiles) > b.n_tile_ctr) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_bp_gemm<WT, EPI, BM, BN, TM>), dim3((g.N + BN - 1) / BN, (g.P + BM - 1) / BM, splits),
-                       dim3(256), 0, s, g);
-  }
-  return hipGetLastError();
-}
-
-// bf16 weights: the tile and K split of a product. Every candidate's time is
-// estimated (microseconds; constants fitted to a sweep of tiles and splits
+// The tile and K split of a product. Every candidate's time is estimated (microseconds; constants fitted to a sweep of tiles and splits
 // over the products of three decoder widths, 16 to 1024 positions, where the
 // choice costs 1.7% over the best on average):
 //   * a unit runs the tile's workgroups in rounds of `occ` (what registers
@@ -1187,70 +611,96 @@ hipError_t gemm(const GemmArgs& g0, const BatchBuffers& b, int n_cu, hipStream_t
 struct MmTile {
   int rb, cp, nw, pf, kg, occ;
 };
+template <typename WT>
 double mm_time(const MmTile& t, int P, int N, int K, int splits, bool resid, int n_cu) {
-  const double mfma = 0.02127 * t.rb * t.cp * t.nw * t.kg;
+  constexpr double kStep = 0.02127 * (sizeof(WT) == 2 ? 1.0 : 512.0 / 96.0);  // cycles of a step's instructions
+  constexpr double wb = sizeof(WT), xb = sizeof(WT) == 2 ? 6.0 : 4.0;
+  const double mfma = kStep * t.rb * t.cp * t.nw * t.kg;
   const double lat = (t.pf == 1 ? 0.733 : 0.262) + 0.377 * mfma / t.kg;
   const int tiles = ((N + 16 * t.rb * t.nw - 1) / (16 * t.rb * t.nw)) * ((P + 16 * t.cp - 1) / (16 * t.cp)) * splits;
   const int per_cu = (tiles + n_cu - 1) / n_cu, full = per_cu / t.occ, rest = per_cu % t.occ;
   const int steps = ((K + 63) / 64 + splits * t.kg - 1) / (splits * t.kg);
   const double round = full * std::max(t.occ * mfma, lat) + (rest ? std::max(rest * mfma, lat) : 0.0);
-  const double bytes = 2.0 * N * K * ((P + 16 * t.cp - 1) / (16 * t.cp)) +
-                       6.0 * P * K * ((N + 16 * t.rb * t.nw - 1) / (16 * t.rb * t.nw));
+  const double bytes = wb * N * K * ((P + 16 * t.cp - 1) / (16 * t.cp)) +
+                       xb * P * K * ((N + 16 * t.rb * t.nw - 1) / (16 * t.rb * t.nw));
   const double out = 4.0 * splits * P * N;
-  return 3.2 + std::max({round * steps, 2.0 * N * K / 5.8e6, bytes / 14.8e6}) + out / 8.5e6 + (resid ? out / 5e6 : 0.0);
+  return 3.2 + std::max({round * steps, wb * N * K / 5.8e6, bytes / 14.8e6}) + out / 8.5e6 + (resid ? out / 5e6 : 0.0);
 }
 
-template <int EPI, int RB, int CP, int NW, int PF, int KG>
+template <typename WT, int EPI, int RB, int CP, int NW, int PF, int KG>
 hipError_t mm_launch(MmArgs m, const GemmArgs& g, int splits, hipStream_t s) {
-  const int steps = m.k32 / 2;
+  const int steps = m.blocks * MmOp<WT>::kBK / 64;
   m.nN = (m.NB + RB * NW - 1) / (RB * NW);
   m.nP = (m.PB + CP - 1) / CP;
   m.steps_per_split = (steps + splits - 1) / splits;
   m.splits = (steps + m.steps_per_split - 1) / m.steps_per_split;
   const int tiles = m.nN * m.nP * m.splits;
   m.tiles_per_xcd = (tiles + 7) / 8;
-  hipLaunchKernelGGL((k_bp_mm<EPI, RB, CP, NW, PF, KG>), dim3(m.tiles_per_xcd * 8), dim3(64 * NW * KG), 0, s, m, g);
+  hipLaunchKernelGGL((k_bp_mm<WT, EPI, RB, CP, NW, PF, KG>), dim3(m.tiles_per_xcd * 8), dim3(64 * NW * KG), 0, s, m, g);
   return hipGetLastError();
 }
 
-// g: as for gemm(), with A, W unused; T the tiled weights, X the input's
-// term planes. *splits receives the K slices that a residual product stored.
-template <int EPI>
-hipError_t gemm_mm(const GemmArgs& g, const void* T, const u32x4* X, const BatchBuffers& b, int n_cu, int* splits,
-                   hipStream_t s) {
+// 16 positions: the weight stream counts, four steps of it in flight. More
+// positions: 32 to 64 per workgroup. Eight waves of three row blocks share the
+// activations of 64 positions among 384 rows, the fewest cache reads. The QKV
+// product of few positions has few tiles and whole sums to finish: four groups
+// of waves share a tile's K. fp32 weights come with narrow models (at most 512
+// wide), whose few steps want many small tiles.
+template <typename WT>
+struct MmTiles;
+template <>
+struct MmTiles<uint16_t> {
+  static constexpr MmTile t[] = {{1, 1, 8, 4, 1, 3}, {1, 2, 4, 4, 1, 3}, {2, 2, 4, 2, 1, 4}, {3, 2, 4, 2, 1, 3},
+                                 {4, 2, 4, 2, 1, 2}, {3, 3, 4, 2, 1, 2}, {3, 4, 4, 1, 1, 2}, {3, 4, 8, 1, 1, 1},
+                                 {2, 4, 8, 1, 1, 1}, {1, 1, 2, 2, 4, 2}, {1, 2, 2, 2, 4, 1}};
+};
+template <>
+struct MmTiles<float> {
+  static constexpr MmTile t[] = {{1, 1, 4, 2, 1, 4}, {1, 1, 2, 2, 4, 2}, {1, 2, 4, 2, 1, 3}, {2, 2, 4, 2, 1, 2}};
+};
+template <typename WT, int EPI, size_t I = 0>
+hipError_t mm_launch_tile(size_t i, const MmArgs& m, const GemmArgs& g, int splits, hipStream_t s) {
+  constexpr size_t n = sizeof(MmTiles<WT>::t) / sizeof(MmTile);
+  if constexpr (I < n) {
+    if (i != I) return mm_launch_tile<WT, EPI, I + 1>(i, m, g, splits, s);
+    constexpr MmTile t = MmTiles<WT>::t[I];
+    if constexpr (t.kg == 1 || EPI == kEpiQkv) return mm_launch<WT, EPI, t.rb, t.cp, t.nw, t.pf, t.kg>(m, g, splits, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+// T: the tiled weights, X: the input's planes. *splits receives the K slices
+// that a residual product stored.
+template <typename WT, int EPI>
+hipError_t gemm(const GemmArgs& g, const void* T, const void* X, const BatchBuffers& b, int n_cu, int* splits,
+                hipStream_t s) {
   constexpr bool kResid = EPI == kEpiResid;
-  // 16 positions: the weight stream counts, four steps of it in flight. More
-  // positions: 32 to 64 per workgroup. Eight waves of three row blocks share
-  // the activations of 64 positions among 384 rows, the fewest cache reads.
-  // The QKV product of few positions has few tiles and whole sums to finish:
-  // four groups of waves share a tile's K.
-  static constexpr MmTile kTiles[] = {{1, 1, 8, 4, 1, 3}, {1, 2, 4, 4, 1, 3}, {2, 2, 4, 2, 1, 4}, {3, 2, 4, 2, 1, 3},
-                                      {4, 2, 4, 2, 1, 2}, {3, 3, 4, 2, 1, 2}, {3, 4, 4, 1, 1, 2}, {3, 4, 8, 1, 1, 1},
-                                      {2, 4, 8, 1, 1, 1}, {1, 1, 2, 2, 4, 2}, {1, 2, 2, 2, 4, 1}};
+  constexpr size_t kTiles = sizeof(MmTiles<WT>::t) / sizeof(MmTile);
   MmArgs m{};
   m.W = static_cast<const u32x4*>(T);
-  m.X = X;
+  m.X = static_cast<const u32x4*>(X);
   m.P = g.P;
   m.N = g.N;
   m.NB = (g.N + 15) / 16;
   m.PB = (g.P + 15) / 16;
-  m.k32 = mm_k32(g.K);
-  const int steps = m.k32 / 2;
+  m.blocks = mm_blocks<WT>(g.K);
+  const int steps = m.blocks * MmOp<WT>::kBK / 64;
   int most = 1;
   if (kResid) {
     const size_t per = static_cast<size_t>(g.P) * g.N;
     most = static_cast<int>(std::min<size_t>(16, b.gemm_ws_floats / per));
     if (most < 1) return hipErrorInvalidValue;
   }
-  int best = -1, best_s = 1;
+  size_t best = kTiles;
+  int best_s = 1;
   double best_t = 0.0;
-  for (int i = 0; i < static_cast<int>(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
-    const MmTile& t = kTiles[i];
+  for (size_t i = 0; i < kTiles; ++i) {
+    const MmTile& t = MmTiles<WT>::t[i];
     if ((t.cp == 1) != (g.P <= 16) || (t.cp == 3 && g.P > 256) || (t.kg > 1 && EPI != kEpiQkv)) continue;
     for (int sp : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
       if (sp > most || (sp > 1 && steps / sp < 4) || (t.kg > 1 && steps < 2 * t.kg)) break;
-      const double us = mm_time(t, g.P, g.N, g.K, sp, kResid, n_cu);
-      if (best < 0 || us < best_t) {
+      const double us = mm_time<WT>(t, g.P, g.N, g.K, sp, kResid, n_cu);
+      if (best == kTiles || us < best_t) {
         best = i;
         best_s = sp;
         best_t = us;
@@ -1261,31 +711,15 @@ hipError_t gemm_mm(const GemmArgs& g, const void* T, const u32x4* X, const Batch
     const int per = (steps + best_s - 1) / best_s;
     *splits = (steps + per - 1) / per;
   }
-  switch (best) {
-    case 0: return mm_launch<EPI, 1, 1, 8, 4, 1>(m, g, best_s, s);
-    case 1: return mm_launch<EPI, 1, 2, 4, 4, 1>(m, g, best_s, s);
-    case 2: return mm_launch<EPI, 2, 2, 4, 2, 1>(m, g, best_s, s);
-    case 3: return mm_launch<EPI, 3, 2, 4, 2, 1>(m, g, best_s, s);
-    case 4: return mm_launch<EPI, 4, 2, 4, 2, 1>(m, g, best_s, s);
-    case 5: return mm_launch<EPI, 3, 3, 4, 2, 1>(m, g, best_s, s);
-    case 6: return mm_launch<EPI, 3, 4, 4, 1, 1>(m, g, best_s, s);
-    case 7: return mm_launch<EPI, 3, 4, 8, 1, 1>(m, g, best_s, s);
-    case 8: return mm_launch<EPI, 2, 4, 8, 1, 1>(m, g, best_s, s);
-    case 9:
-      if constexpr (EPI == kEpiQkv) return mm_launch<EPI, 1, 1, 2, 2, 4>(m, g, best_s, s);
-      break;
-    case 10:
-      if constexpr (EPI == kEpiQkv) return mm_launch<EPI, 1, 2, 2, 2, 4>(m, g, best_s, s);
-      break;
-  }
-  return hipErrorInvalidValue;
+  return mm_launch_tile<WT, EPI>(best, m, g, best_s, s);
 }
 
+template <typename WT>
 hipError_t reduce_norm(const BatchBuffers& b, float* X, int splits, int P, int H, const float* gain, float eps, hipStream_t s) {
   if (H > 8 * kNormThreads) return hipErrorInvalidValue;
   const int blocks = (P + 127) / 128 * 128;  // whole groups of 16 positions on each of the 8 XCDs
-  hipLaunchKernelGGL(k_bp_reduce_norm, dim3(blocks), dim3(kNormThreads), 0, s, X, b.gemm_ws, splits, P, H, gain, eps,
-                     static_cast<u32x4*>(b.Xp), mm_k32(H));
+  hipLaunchKernelGGL((k_bp_reduce_norm<WT>), dim3(blocks), dim3(kNormThreads), 0, s, X, b.gemm_ws, splits, P, H, gain, eps,
+                     static_cast<u32x4*>(b.Xp), mm_blocks<WT>(H));
   return hipGetLastError();
 }
 
@@ -1293,8 +727,8 @@ hipError_t reduce_norm(const BatchBuffers& b, float* X, int splits, int P, int H
 // workgroups at a time, a tile takes ~2.8 us (the same for one workgroup and
 // for two side by side), splits add the merging launch (4.5 us) and their
 // records' stores and loads.
-template <int D>
-hipError_t attention_mfma(AttnArgs a, const BatchBuffers& b, int n_cu, hipStream_t s) {
+template <typename WT, int D>
+hipError_t attention(AttnArgs a, const BatchBuffers& b, int n_cu, hipStream_t s) {
   const int qb = a.G >= 4 ? 1 : a.G >= 2 ? 2 : 4;  // 4 to 8 waves per workgroup
   const int blocks = a.K * ((a.P + 16 * qb - 1) / (16 * qb));
   const int t_max = a.pos0 + a.P, key_tiles = (t_max + kKT - 1) / kKT;
@@ -1317,42 +751,7 @@ hipError_t attention_mfma(AttnArgs a, const BatchBuffers& b, int n_cu, hipStream
   switch (a.G) {
 #define EE_ATTN_G(GG)                                                                                         \
   case GG:                                                                                                    \
-    hipLaunchKernelGGL((k_bp_attn_mfma<D, GG, (GG >= 4 ? 1 : GG >= 2 ? 2 : 4)>), grid, block, 0, s, a);        \
-    break;
-    EE_ATTN_G(1) EE_ATTN_G(2) EE_ATTN_G(3) EE_ATTN_G(4) EE_ATTN_G(5) EE_ATTN_G(6) EE_ATTN_G(7) EE_ATTN_G(8)
-#undef EE_ATTN_G
-    default: return hipErrorInvalidValue;
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.nsplit == 1) return e;
-  hipLaunchKernelGGL((k_bp_attn_merge<uint16_t, D>), dim3((a.P * a.A + 3) / 4), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-template <typename WT, int D>
-hipError_t attention(AttnArgs a, const BatchBuffers& b, int n_cu, hipStream_t s) {
-  constexpr int kQT = 4;  // query positions per block of the prompt's path
-  const int nqt = (a.P + kQT - 1) / kQT;
-  const int t_max = a.pos0 + a.P;
-  const int key_tiles = (t_max + kKT - 1) / kKT;
-  int ns = std::max(1, (4 * n_cu + a.K * nqt - 1) / (a.K * nqt));
-  ns = std::min(ns, key_tiles);
-  const size_t per = static_cast<size_t>(a.P) * a.A * (D + 2);
-  ns = static_cast<int>(std::min<size_t>(ns, std::max<size_t>(1, b.attn_ws_floats / per)));
-  a.keys_per_split = (key_tiles + ns - 1) / ns * kKT;
-  a.nsplit = (t_max + a.keys_per_split - 1) / a.keys_per_split;
-  // few blocks: blocks of two query positions whose waves take one query
-  // head each; else four positions, one wave each with all heads
-  const bool split_heads = static_cast<int64_t>(a.K) * nqt * a.nsplit < 2 * n_cu && a.G >= 2;
-  const dim3 grid(a.K * (split_heads ? (a.P + 1) / 2 : nqt) * a.nsplit);
-  switch (a.G) {
-#define EE_ATTN_G(GG)                                                                                  \
-  case GG:                                                                                             \
-    if (GG >= 2 && split_heads) {                                                                      \
-      hipLaunchKernelGGL((k_bp_attn<WT, D, GG, 1, (GG >= 2 ? 2 : 4)>), grid, dim3(128 * GG), 0, s, a); \
-    } else {                                                                                           \
-      hipLaunchKernelGGL((k_bp_attn<WT, D, GG, GG, 4>), grid, dim3(64 * kQT), 0, s, a);                \
-    }                                                                                                  \
+    hipLaunchKernelGGL((k_bp_attn<WT, D, GG, (GG >= 4 ? 1 : GG >= 2 ? 2 : 4)>), grid, block, 0, s, a);        \
     break;
     EE_ATTN_G(1) EE_ATTN_G(2) EE_ATTN_G(3) EE_ATTN_G(4) EE_ATTN_G(5) EE_ATTN_G(6) EE_ATTN_G(7) EE_ATTN_G(8)
 #undef EE_ATTN_G
@@ -1366,14 +765,9 @@ hipError_t attention(AttnArgs a, const BatchBuffers& b, int n_cu, hipStream_t s)
 
 template <typename WT>
 hipError_t attention_d(const AttnArgs& a, const BatchBuffers& b, int n_cu, hipStream_t s) {
-  switch (a.D) {
-    case 32: return hipErrorInvalidValue;  // rows of at least 64 dimensions (one per lane)
-    case 64:
-      if constexpr (sizeof(WT) == 2) return attention_mfma<64>(a, b, n_cu, s);
-      else return attention<WT, 64>(a, b, n_cu, s);
-    case 128:
-      if constexpr (sizeof(WT) == 2) return attention_mfma<128>(a, b, n_cu, s);
-  }
+  if (a.D == 64) return attention<WT, 64>(a, b, n_cu, s);
+  if constexpr (sizeof(WT) == 2)
+    if (a.D == 128) return attention<WT, 128>(a, b, n_cu, s);
   return hipErrorInvalidValue;
 }
 
@@ -1388,15 +782,14 @@ hipError_t pass(const BatchPass& bp, int pos0, const int32_t* d_tokens, int n, h
     hipLaunchKernelGGL((k_bp_embed<WT>), dim3(P), dim3(256), 0, s, static_cast<const WT*>(p.embed), d_tokens + c0, P,
                        p.H, p.V, b.X, p.hist_tok, cpos, p.ctl);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if constexpr (sizeof(WT) == 2)
-      if ((e = reduce_norm(b, b.X, 0, P, p.H, bp.layers[0].g_attn, p.eps, s)) != hipSuccess) return e;
+    if ((e = reduce_norm<WT>(b, b.X, 0, P, p.H, bp.layers[0].g_attn, p.eps, s)) != hipSuccess) return e;
     for (int l = 0; l < p.L; ++l) {
       const LayerW& lw = bp.layers[l];
+      const LayerT& lt = bp.tiled[l];
       GemmArgs g{};
       g.P = P;
-      g.eps = p.eps;
       g.part = b.gemm_ws;
-      g.tile_ctr = b.tile_ctr;
+      g.Q = b.Q;
       g.pos0 = cpos;
       g.Aq = p.A;
       g.Kh = p.K;
@@ -1410,14 +803,14 @@ hipError_t pass(const BatchPass& bp, int pos0, const int32_t* d_tokens, int n, h
       g.page_shift = p.page_shift;
       g.page_size = p.page_size;
       GemmArgs q = g, o = g, gu = g, dn = g;
-      q.A = b.X; q.W = lw.wqkv; q.N = p.qkv_rows; q.K = p.H; q.gain = lw.g_attn; q.Y = b.Q;
-      o.A = b.O; o.W = lw.wo; o.N = p.H; o.K = p.A * p.D; o.Y = b.X;
-      gu.A = b.X; gu.W = lw.wgu; gu.N = 2 * p.F; gu.K = p.H; gu.gain = lw.g_mlp; gu.Y = b.Act;
-      gu.planes = static_cast<u32x4*>(b.Ap); gu.k32_out = mm_k32(p.F);
-      dn.A = b.Act; dn.W = lw.wd; dn.N = p.H; dn.K = p.F; dn.Y = b.X;
+      q.N = p.qkv_rows; q.K = p.H;
+      o.N = p.H; o.K = p.A * p.D;
+      gu.N = 2 * p.F; gu.K = p.H;
+      gu.planes = static_cast<u32x4*>(b.Ap); gu.blocks = mm_blocks<WT>(p.F);
+      dn.N = p.H; dn.K = p.F;
       AttnArgs at{};
-      at.Q = b.Q; at.O = b.O; at.part = b.attn_ws;
-      at.planes = static_cast<u32x4*>(b.Op); at.k32 = mm_k32(p.A * p.D);
+      at.Q = b.Q; at.part = b.attn_ws;
+      at.planes = static_cast<u32x4*>(b.Op); at.blocks = mm_blocks<WT>(p.A * p.D);
       at.kpool = p.kpool; at.vpool = p.vpool; at.layer_base = g.layer_base;
       at.block_table = p.block_table; at.page_shift = p.page_shift; at.page_size = p.page_size;
       at.P = P; at.pos0 = cpos; at.A = p.A; at.K = p.K; at.G = p.G; at.D = p.D; at.scale = p.attn_scale;
@@ -1431,35 +824,20 @@ hipError_t pass(const BatchPass& bp, int pos0, const int32_t* d_tokens, int n, h
         at.Q += row * p.A * p.D;
         at.pos0 += P - 1;
         at.P = o.P = gu.P = dn.P = 1;
-        o.Y = dn.Y = X;
-        gu.A = X;
       }
       const bool stop = last && !(bp.head && c0 + P == n);
-      if constexpr (sizeof(WT) == 2) {
-        // the input's term planes are in Xp; each residual product's slices
-        // are summed by the kernel that prepares the next product's input
-        const LayerT& lt = bp.tiled[l];
-        const u32x4* Xp = static_cast<const u32x4*>(b.Xp);
-        int sp = 0;
-        if ((e = gemm_mm<kEpiQkv>(q, lt.wqkv, Xp, b, bp.n_cu, nullptr, s)) != hipSuccess) return e;
-        if (stop) break;
-        if ((e = attention_d<WT>(at, b, bp.n_cu, s)) != hipSuccess) return e;
-        if ((e = gemm_mm<kEpiResid>(o, lt.wo, static_cast<const u32x4*>(b.Op), b, bp.n_cu, &sp, s)) != hipSuccess)
-          return e;
-        if ((e = reduce_norm(b, X, sp, at.P, p.H, lw.g_mlp, p.eps, s)) != hipSuccess) return e;
-        if ((e = gemm_mm<kEpiSwiGlu>(gu, lt.wgu, Xp, b, bp.n_cu, nullptr, s)) != hipSuccess) return e;
-        if ((e = gemm_mm<kEpiResid>(dn, lt.wd, static_cast<const u32x4*>(b.Ap), b, bp.n_cu, &sp, s)) != hipSuccess)
-          return e;
-        const float* next = l + 1 < p.L ? bp.layers[l + 1].g_attn : nullptr;
-        if ((e = reduce_norm(b, X, sp, at.P, p.H, next, p.eps, s)) != hipSuccess) return e;
-      } else {
-        if ((e = gemm<WT, kEpiQkv>(q, b, bp.n_cu, s)) != hipSuccess) return e;
-        if (stop) break;
-        if ((e = attention_d<WT>(at, b, bp.n_cu, s)) != hipSuccess) return e;
-        if ((e = gemm<WT, kEpiResid>(o, b, bp.n_cu, s)) != hipSuccess) return e;
-        if ((e = gemm<WT, kEpiSwiGlu>(gu, b, bp.n_cu, s)) != hipSuccess) return e;
-        if ((e = gemm<WT, kEpiResid>(dn, b, bp.n_cu, s)) != hipSuccess) return e;
-      }
+      // the input's planes are in Xp; each residual product's slices are
+      // summed by the kernel that prepares the next product's input
+      int sp = 0;
+      if ((e = gemm<WT, kEpiQkv>(q, lt.wqkv, b.Xp, b, bp.n_cu, nullptr, s)) != hipSuccess) return e;
+      if (stop) break;
+      if ((e = attention_d<WT>(at, b, bp.n_cu, s)) != hipSuccess) return e;
+      if ((e = gemm<WT, kEpiResid>(o, lt.wo, b.Op, b, bp.n_cu, &sp, s)) != hipSuccess) return e;
+      if ((e = reduce_norm<WT>(b, X, sp, at.P, p.H, lw.g_mlp, p.eps, s)) != hipSuccess) return e;
+      if ((e = gemm<WT, kEpiSwiGlu>(gu, lt.wgu, b.Xp, b, bp.n_cu, nullptr, s)) != hipSuccess) return e;
+      if ((e = gemm<WT, kEpiResid>(dn, lt.wd, b.Ap, b, bp.n_cu, &sp, s)) != hipSuccess) return e;
+      if ((e = reduce_norm<WT>(b, X, sp, at.P, p.H, last ? nullptr : bp.layers[l + 1].g_attn, p.eps, s)) != hipSuccess)
+        return e;
     }
   }
   return hipSuccess;
@@ -1472,20 +850,25 @@ hipError_t launch_batched_pass(const BatchPass& bp, int pos0, const int32_t* d_t
   return bp.wbf16 ? pass<uint16_t>(bp, pos0, d_tokens, n, s) : pass<float>(bp, pos0, d_tokens, n, s);
 }
 
-size_t batch_tile_counters(int max_positions, int N_max) {
-  // fp32 weights: tiles of 64 x 64 (more than 16 positions) and 16 x 64 (at most 16)
-  return static_cast<size_t>((N_max + 63) / 64) * ((max_positions + 63) / 64);
-}
-
-size_t batch_weight_bytes(int N, int K) { return mm_weight_bytes(N, K); }
-size_t batch_plane_bytes(int P, int K) { return mm_plane_bytes(P, K); }
-
-hipError_t launch_tile_weights(const void* W, int N, int K, void* T, hipStream_t s) {
-  const int64_t chunks = static_cast<int64_t>(mm_weight_bytes(N, K) / 16);
+namespace {
+template <typename WT>
+size_t weight_bytes(int N, int K) { return static_cast<size_t>((N + 15) / 16) * mm_blocks<WT>(K) * 1024; }
+template <typename WT>
+hipError_t tile_weights(const void* W, int N, int K, void* T, hipStream_t s) {
+  const int64_t chunks = static_cast<int64_t>(weight_bytes<WT>(N, K) / 16);
   const int blocks = static_cast<int>(std::min<int64_t>((chunks + 255) / 256, 8192));
-  hipLaunchKernelGGL(k_bp_tile_weights, dim3(blocks), dim3(256), 0, s, static_cast<const uint16_t*>(W), N, K, mm_k32(K),
-                     chunks, static_cast<u32x4*>(T));
+  hipLaunchKernelGGL((k_bp_tile_weights<WT>), dim3(blocks), dim3(256), 0, s, static_cast<const WT*>(W), N, K,
+                     mm_blocks<WT>(K), chunks, static_cast<u32x4*>(T));
   return hipGetLastError();
+}
+}  // namespace
+
+size_t batch_weight_bytes(int wbf16, int N, int K) { return wbf16 ? weight_bytes<uint16_t>(N, K) : weight_bytes<float>(N, K); }
+size_t batch_plane_bytes(int wbf16, int P, int K) {
+  return static_cast<size_t>((P + 15) / 16) * (wbf16 ? mm_blocks<uint16_t>(K) * 3 : mm_blocks<float>(K)) * 1024;
+}
+hipError_t launch_tile_weights(int wbf16, const void* W, int N, int K, void* T, hipStream_t s) {
+  return wbf16 ? tile_weights<uint16_t>(W, N, K, T, s) : tile_weights<float>(W, N, K, T, s);
 }
 
 }  // namespace ee

@@ -140,23 +140,17 @@ struct BatchBuffers {
   int max_positions;
   float* X;               // [max_positions][H] residual stream
   float* Q;               // [max_positions][A*D] queries after RoPE
-  float* O;               // [max_positions][A*D] attention output (fp32 weights)
-  float* Act;             // [max_positions][F] SiLU(gate) * up (fp32 weights)
-  // bf16 weights: the inputs of the products as term planes (ee_mm.h); what
-  // pads K stays zero
+  // the inputs of the products as planes (ee_mm.h); what pads K stays zero
   void* Xp;               // the normalised residual stream [H]
   void* Op;               // attention output [A*D]
   void* Ap;               // SiLU(gate) * up [F]
   float* gemm_ws;         // split-K partial sums
   size_t gemm_ws_floats;
-  uint32_t* tile_ctr;     // arrivals per output tile (zero between launches; fp32 weights)
-  size_t n_tile_ctr;
   float* attn_ws;         // attention partial records of key splits
   size_t attn_ws_floats;
 };
 
-// A layer's matrices in the order of the matrix cores' operands (bf16 weights;
-// same rows as LayerW's)
+// A layer's matrices in the order of the matrix cores' operands (same rows as LayerW's)
 struct LayerT {
   void* wqkv;
   void* wo;
@@ -167,7 +161,7 @@ struct LayerT {
 struct BatchPass {
   DevParams p;            // shapes, embedding, cache, RoPE tables, block table, token history, step record
   const LayerW* layers;   // host array [L] of the layers' device pointers
-  const LayerT* tiled;    // host array [L], null for fp32 weights
+  const LayerT* tiled;    // host array [L]
   BatchBuffers buf;
   int wbf16;
   int n_cu;
@@ -180,13 +174,11 @@ struct BatchPass {
 // in its row of buf.X (nothing reads the other positions' final states: the
 // last layer stops at their cache entries).
 hipError_t launch_batched_pass(const BatchPass& bp, int pos0, const int32_t* d_tokens, int n, hipStream_t s);
-// tile counters the pass needs for chunks of max_positions and outputs of at most N_max rows
-size_t batch_tile_counters(int max_positions, int N_max);
-// bytes of the tiled copy of [N][K] bf16 weights, and of the term planes of [P][K] activations
-size_t batch_weight_bytes(int N, int K);
-size_t batch_plane_bytes(int P, int K);
-// write the tiled copy T of the row-major bf16 matrix W [N][K]
-hipError_t launch_tile_weights(const void* W, int N, int K, void* T, hipStream_t s);
+// bytes of the tiled copy of [N][K] weights, and of the planes of [P][K] activations
+size_t batch_weight_bytes(int wbf16, int N, int K);
+size_t batch_plane_bytes(int wbf16, int P, int K);
+// write the tiled copy T of the row-major matrix W [N][K]
+hipError_t launch_tile_weights(int wbf16, const void* W, int N, int K, void* T, hipStream_t s);
 
 // Host launchers (defined in ee_kernels.hip).
 hipError_t launch_decode_per_op(const DevParams& p, int wbf16, int pos0, int n, int head_wgs,
