@@ -700,7 +700,9 @@ hipError_t gemm(const GemmArgs& g, const void* T, const void* X, const BatchBuff
     for (int sp : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
       if (sp > most || (sp > 1 && steps / sp < 4) || (t.kg > 1 && steps < 2 * t.kg)) break;
       const double us = mm_time<WT>(t, g.P, g.N, g.K, sp, kResid, n_cu);
-      if (best == kTiles || us < best_t) {
+      // of equals the tile of more waves, which reads less from the caches (1024 positions: gate/up 139 against
+      // 150 us, down 64 against 75)
+      if (best == kTiles || us < best_t || (us == best_t && t.nw > MmTiles<WT>::t[best].nw)) {
         best = i;
         best_s = sp;
         best_t = us;
