@@ -41,6 +41,7 @@ struct ee_ctx {
   ee::LayerW* d_layers = nullptr;
   std::vector<ee::LayerW> h_layers;   // the same pointers, host side (batched pass)
   std::vector<ee::LayerT> tiled;      // the batched pass's copies of the layers' matrices
+  void* tiled_block = nullptr;
   std::set<const void*> untiled;      // matrices loaded since their copies were made
   ee::BatchBuffers bbuf{};            // batched full-depth pass (prompt, refresh)
   int prefill_chunk = -1;             // -1: batched in chunks of bbuf.max_positions; 0: one position per step
@@ -796,16 +797,24 @@ static int create_body(ee_ctx* c, const ee_config* cfg, void* hip_stream, ee_ctx
     if ((r = dalloc(c, &c->wo[l], H * A * D * es))) return bail(r);
     if ((r = dalloc(c, &c->wgu[l], 2 * F * H * es))) return bail(r);
     if ((r = dalloc(c, &c->wd[l], H * F * es))) return bail(r);
-    c->tiled.push_back(ee::LayerT{});
-    ee::LayerT& t = c->tiled.back();
-    const int h = static_cast<int>(H), ad = static_cast<int>(A * D), f = static_cast<int>(F);
-    if ((r = dalloc(c, &t.wqkv, ee::batch_weight_bytes(c->wbf16, static_cast<int>((A + 2 * K) * D), h))) ||
-        (r = dalloc(c, &t.wo, ee::batch_weight_bytes(c->wbf16, h, ad))) ||
-        (r = dalloc(c, &t.wgu, ee::batch_weight_bytes(c->wbf16, 2 * f, h))) ||
-        (r = dalloc(c, &t.wd, ee::batch_weight_bytes(c->wbf16, h, f))))
-      return bail(r);
     if ((r = dalloc(c, &c->g_attn[l], H * 4))) return bail(r);
     if ((r = dalloc(c, &c->g_mlp[l], H * 4))) return bail(r);
+  }
+  {
+    // the batched pass's tiled copies, one allocation; the tiling writes every byte, padding included
+    const int h = static_cast<int>(H), ad = static_cast<int>(A * D), f = static_cast<int>(F);
+    const size_t n[4] = {ee::batch_weight_bytes(c->wbf16, static_cast<int>((A + 2 * K) * D), h),
+                         ee::batch_weight_bytes(c->wbf16, h, ad), ee::batch_weight_bytes(c->wbf16, 2 * f, h),
+                         ee::batch_weight_bytes(c->wbf16, h, f)};
+    const size_t layer = n[0] + n[1] + n[2] + n[3];
+    if (hipMalloc(&c->tiled_block, layer * L) != hipSuccess) {
+      (void)hipGetLastError();
+      return bail(fail(c, EE_ENOMEM, "hipMalloc of " + std::to_string(layer * L) + " bytes failed"));
+    }
+    for (size_t l = 0; l < L; ++l) {
+      char* t = static_cast<char*>(c->tiled_block) + layer * l;
+      c->tiled.push_back(ee::LayerT{t, t + n[0], t + n[0] + n[1], t + n[0] + n[1] + n[2]});
+    }
   }
   if ((r = dalloc(c, &c->g_final, H * 4))) return bail(r);
   if ((r = dalloc(c, &c->d_layers, L * sizeof(ee::LayerW)))) return bail(r);
@@ -1403,12 +1412,7 @@ static void destroy_impl(ee_ctx* c) {
   for (void* p : c->wo) dfree(p);
   for (void* p : c->wgu) dfree(p);
   for (void* p : c->wd) dfree(p);
-  for (const ee::LayerT& t : c->tiled) {
-    dfree(t.wqkv);
-    dfree(t.wo);
-    dfree(t.wgu);
-    dfree(t.wd);
-  }
+  dfree(c->tiled_block);
   for (float* p : c->g_attn) dfree(p);
   for (float* p : c->g_mlp) dfree(p);
   dfree(c->g_final);
