@@ -81,7 +81,6 @@ struct ee_ctx {
   int force_cap = 0;
   int32_t *d_force_tok = nullptr, *d_force_exit = nullptr;
   int32_t* h_force = nullptr;          // pinned: tokens, then exits, force_cap entries each
-  int up_tok = 0, up_exit = 0;         // entries of them the next call's kernels need on the device
   int pages_uploaded = 0;              // block-table entries the device has
   // pinned: the step record, then what a call returns (results of the latest call)
   char* mail = nullptr;
@@ -295,15 +294,23 @@ int ensure_pages(ee_ctx* c, int pos_end) {
   return EE_OK;
 }
 
+// A call's imposed inputs: the device arrays its kernels read (or null), and
+// how many entries of them its first kernel copies from h_force. Held by the
+// call alone: what a call that fails has staged never reaches a later one.
+struct Imposed {
+  const int32_t* tok = nullptr;
+  const int32_t* exit = nullptr;
+  int up_tok = 0, up_exit = 0;
+};
+
 // The call's first kernel: the step record's per-call fields cleared, and
 // the imposed inputs and new pages (pinned host memory) copied to the device
 // together with whatever the caller has put into b.
-int begin_call(ee_ctx* c, ee::IoBatch& b) {
+int begin_call(ee_ctx* c, ee::IoBatch& b, const Imposed& im = Imposed{}) {
   b.ctl = c->d_ctl;
-  b.add(c->d_force_tok, c->h_force, c->up_tok);
-  b.add(c->d_force_exit, c->h_force + c->force_cap, c->up_exit);
+  b.add(c->d_force_tok, c->h_force, im.up_tok);
+  b.add(c->d_force_exit, c->h_force + c->force_cap, im.up_exit);
   b.add(c->d_block_table + c->pages_uploaded, c->h_block_table + c->pages_uploaded, c->pages_mapped - c->pages_uploaded);
-  c->up_tok = c->up_exit = 0;
   const hipError_t e = ee::launch_io(b, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "call preparation launch");
   c->pages_uploaded = c->pages_mapped;
@@ -473,9 +480,8 @@ size_t debug_off(const ee_ctx* c, int n, int which) {
 // results in the mail and wait. With na set, the outputs go to the caller's
 // device arrays and the working set to the library-resident scratch: nothing
 // is allocated.
-int run_steps(ee_ctx* c, float tau, int exit_layer, int n, const int32_t* d_force_tok,
-              const int32_t* d_force_exit, bool prefill, const Collect& want = Collect{},
-              const NoAlloc* na = nullptr, ee::StepCtl* out_ctl = nullptr) {
+int run_steps(ee_ctx* c, float tau, int exit_layer, int n, const Imposed& im, bool prefill,
+              const Collect& want = Collect{}, const NoAlloc* na = nullptr, ee::StepCtl* out_ctl = nullptr) {
   int r;
   DevParams p = make_params(c, tau, prefill ? 0 : exit_layer);
   if (na && (r = bind_scratch(c, p))) return r;
@@ -495,8 +501,8 @@ int run_steps(ee_ctx* c, float tau, int exit_layer, int n, const int32_t* d_forc
     p.ring_mass = c->d_ring_mass;
   }
   p.nucleus = c->nucleus && !prefill;
-  p.force_tok = d_force_tok;
-  p.force_exit = d_force_exit;
+  p.force_tok = im.tok;
+  p.force_exit = im.exit;
   if (want.logits) {
     p.dbg_logits_r = c->d_dbg_r;
     p.dbg_logits_f = c->d_dbg_f;
@@ -512,13 +518,13 @@ int run_steps(ee_ctx* c, float tau, int exit_layer, int n, const int32_t* d_forc
     in.tw_words = p.tw_words;
     in.add(c->d_params, c->params_pinned, sizeof(DevParams) / 4);
   }
-  if ((r = begin_call(c, in))) return r;
+  if ((r = begin_call(c, in, im))) return r;
   hipError_t e;
   if (pers) {
     const ee::PersistentLaunch L{c->params_pinned, c->slot, c->wbf16, c->nwg_persistent, c->lds, c->stream};
     e = prefill ? ee::launch_prefill_persistent(L, c->pos, n) : ee::launch_decode_persistent(L, c->pos, n);
   } else if (prefill) {
-    e = ee::launch_prefill_per_op(p, c->wbf16, c->pos, d_force_tok, n, c->head_wgs, c->stream);
+    e = ee::launch_prefill_per_op(p, c->wbf16, c->pos, im.tok, n, c->head_wgs, c->stream);
   } else {
     e = ee::launch_decode_per_op(p, c->wbf16, c->pos, n, c->head_wgs, c->stream);
   }
@@ -565,9 +571,8 @@ void copy_ring(ee_ctx* c, int n, int32_t* tokens, int32_t* exited, float* conf, 
 }
 
 // Imposed inputs, checked and staged for the call's first kernel.
-int upload_force(ee_ctx* c, int n, const int32_t* force_tokens, const int32_t* force_exit) {
+int upload_force(ee_ctx* c, int n, const int32_t* force_tokens, const int32_t* force_exit, Imposed* im) {
   int r;
-  c->up_tok = c->up_exit = 0;
   if (!force_tokens && !force_exit) return EE_OK;
   if ((r = ensure_force(c, n))) return r;
   if (force_tokens) {
@@ -582,8 +587,14 @@ int upload_force(ee_ctx* c, int n, const int32_t* force_tokens, const int32_t* f
         return fail(c, EE_EINVAL, "force_exit values must be -1, 0 or 1");
     memcpy(c->h_force + c->force_cap, force_exit, sizeof(int32_t) * n);
   }
-  if (force_tokens) c->up_tok = n;
-  if (force_exit) c->up_exit = n;
+  if (force_tokens) {
+    im->tok = c->d_force_tok;
+    im->up_tok = n;
+  }
+  if (force_exit) {
+    im->exit = c->d_force_exit;
+    im->up_exit = n;
+  }
   return EE_OK;
 }
 
@@ -596,9 +607,9 @@ int decode_common(ee_ctx* c, float tau, int exit_layer, int n, const int32_t* fo
   if ((r = check_gate_args(c, tau, exit_layer))) return r;
   if (!force_tokens && !c->have_next)
     return fail(c, EE_ESTATE, "no input token: run ee_prefill first (or force the input tokens)");
-  if ((r = upload_force(c, n, force_tokens, force_exit))) return r;
-  return run_steps(c, tau, exit_layer, n, force_tokens ? c->d_force_tok : nullptr,
-                   force_exit ? c->d_force_exit : nullptr, false, want, nullptr, out_ctl);
+  Imposed im;
+  if ((r = upload_force(c, n, force_tokens, force_exit, &im))) return r;
+  return run_steps(c, tau, exit_layer, n, im, false, want, nullptr, out_ctl);
 }
 
 // Copy a matrix given in canonical layout into a row range of a repacked one.
@@ -932,7 +943,8 @@ static int load_weights_impl(ee_ctx* c, const ee_tensor* tensors, int32_t n_tens
 // d_tokens, batched (chunks of positions through each layer together); with
 // head, the final head of the last position sets the next input token.
 // Advances the position; synchronous.
-static int batched_full_depth(ee_ctx* c, const int32_t* d_tokens, int n, bool head, int32_t* first) {
+static int batched_full_depth(ee_ctx* c, const int32_t* d_tokens, int n, bool head, int32_t* first,
+                              const Imposed& im = Imposed{}) {
   int r;
   if ((r = ensure_pages(c, c->pos + n))) return r;
   ee::BatchPass bp{};
@@ -946,7 +958,7 @@ static int batched_full_depth(ee_ctx* c, const int32_t* d_tokens, int n, bool he
   bp.head = head;
   HIPCHK(c, hipEventRecord(c->ev0, c->stream));
   ee::IoBatch in{}, out{};
-  if ((r = begin_call(c, in))) return r;
+  if ((r = begin_call(c, in, im))) return r;
   hipError_t e = ee::launch_batched_pass(bp, c->pos, d_tokens, n, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "batched pass launch");
   if (head) {
@@ -975,14 +987,15 @@ static int prefill_impl(ee_ctx* c, const int32_t* tokens, int32_t n, int32_t* ou
   if (!weights_ready(c)) return fail(c, EE_ESTATE, "weights not fully loaded");
   if (!tokens || n <= 0) return fail(c, EE_EINVAL, "prefill needs at least one token");
   int r;
-  if ((r = upload_force(c, n, tokens, nullptr))) return r;
+  Imposed im;
+  if ((r = upload_force(c, n, tokens, nullptr, &im))) return r;
   int32_t tok = -1;
   if (c->prefill_chunk != 0) {
-    if ((r = batched_full_depth(c, c->d_force_tok, n, true, &tok))) return r;
+    if ((r = batched_full_depth(c, im.tok, n, true, &tok, im))) return r;
     c->have_next = true;
   } else {
     ee::StepCtl ctl;
-    if ((r = run_steps(c, INFINITY, 0, n, c->d_force_tok, nullptr, true, Collect{}, nullptr, &ctl))) return r;
+    if ((r = run_steps(c, INFINITY, 0, n, im, true, Collect{}, nullptr, &ctl))) return r;
     tok = ctl.next_token;
   }
   if (out_first_token) *out_first_token = tok;
@@ -1012,7 +1025,9 @@ static int refresh_impl(ee_ctx* c, int32_t n) {
   int32_t next = 0;
   HIPCHK(c, hipMemcpy(&next, &c->d_ctl->next_token, sizeof(next), hipMemcpyDeviceToHost));
   c->pos -= n;
-  r = run_steps(c, INFINITY, 0, n, c->d_force_tok, nullptr, true);
+  Imposed im;
+  im.tok = c->d_force_tok;  // from the history, on the device already
+  r = run_steps(c, INFINITY, 0, n, im, true);
   if (r) {
     c->pos += n;
     c->have_next = false;
@@ -1049,7 +1064,7 @@ static int decode_n_noalloc_impl(ee_ctx* c, float tau, int32_t exit_layer, int32
   if (!c->have_next) return fail(c, EE_ESTATE, "no input token: run ee_prefill first");
   if (!c->scratch) return fail(c, EE_ESTATE, "no library scratch on this device");
   const NoAlloc na{d_tokens, d_exited, d_conf};
-  return run_steps(c, tau, exit_layer, n, nullptr, nullptr, false, Collect{}, &na);
+  return run_steps(c, tau, exit_layer, n, Imposed{}, false, Collect{}, &na);
 }
 
 static int decode_step_impl(ee_ctx* c, float tau, int32_t exit_layer, int32_t* out_token,

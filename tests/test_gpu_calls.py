@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import synth
+from paper_2609_14144_amd import EEError
 from tests.gpu_helpers import engine
 
 pytestmark = pytest.mark.gpu
@@ -63,3 +64,28 @@ def test_mixed_calls_equal_single_steps(persistent):
         np.testing.assert_array_equal(d[k], e[k])
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("chunk", [0, 16], ids=["stepwise", "batched"])
+def test_refused_call_leaves_no_inputs(chunk):
+    """A prompt and imposed steps beyond the capacity are refused; the refresh
+    after them recomputes the same cache as in a context that made no such call."""
+    cfg = synth.get_config("tiny_bf16")
+    prompt = synth.prompts(cfg, 4, 40)
+    toks = synth.prompts(cfg, 5, 60)
+    kept = []
+    for disturb in (False, True):
+        e = engine("tiny_bf16", 48, page_size=16)
+        e.ee_set_prefill_chunk(chunk)
+        e.ee_prefill(prompt)
+        if disturb:
+            with pytest.raises(EEError):
+                e.ee_prefill(toks)
+            with pytest.raises(EEError):
+                e.ee_decode_n_ex(0.3, 2, 60, force_tokens=toks, force_exit=np.ones(60, np.int32))
+        e.ee_refresh(40)
+        kv = [np.concatenate(e.ee_read_kv(l, t)) for l in range(cfg.n_layers) for t in range(40)]
+        kept.append((np.stack(kv), *e.ee_decode_n(0.3, 2, 4)))
+        e.close()
+    for a, b in zip(*kept):
+        np.testing.assert_array_equal(a, b)
