@@ -317,26 +317,35 @@ int begin_call(ee_ctx* c, ee::IoBatch& b, const Imposed& im = Imposed{}) {
   return EE_OK;
 }
 
-// Room for a call's results behind the step record, in pinned host memory.
+// Room for a call's results behind the step record, in pinned host memory. A
+// block that cannot grow stays: every call's last kernel writes to it, also of
+// the calls that need no more room than it has.
 constexpr size_t kMailHead = 256;
 static_assert(sizeof(ee::StepCtl) <= kMailHead, "the step record fits its place");
 int ensure_mail(ee_ctx* c, size_t bytes) {
   if (kMailHead + bytes <= c->mail_cap) return EE_OK;
-  if (c->mail) (void)hipHostFree(c->mail);
-  c->mail = nullptr;
-  c->mail_cap = 0;
   const size_t cap = std::max<size_t>(kMailHead + bytes, 64 << 10);
   void* p = nullptr;
   if (hipHostMalloc(&p, cap) != hipSuccess) {
     (void)hipGetLastError();
     return fail(c, EE_ENOMEM, "hipHostMalloc of " + std::to_string(cap) + " bytes failed");
   }
+  if (c->mail) (void)hipHostFree(c->mail);
   c->mail = static_cast<char*>(p);
   c->mail_cap = cap;
   return EE_OK;
 }
 template <typename T>
 T* mail_at(const ee_ctx* c, size_t off) { return reinterpret_cast<T*>(c->mail + kMailHead + off); }
+
+// Both heads' logits on the device (calls that return logits); one of them
+// may be there already after a call that ran out of memory.
+int ensure_logits(ee_ctx* c) {
+  int r;
+  for (float** p : {&c->d_dbg_r, &c->d_dbg_f})
+    if (!*p && (r = dalloc(c, p, static_cast<size_t>(c->cfg.vocab) * 4))) return r;
+  return EE_OK;
+}
 
 // The call's last kernel: the step record and b's copies; then wait.
 int end_call(ee_ctx* c, ee::IoBatch& b, ee::StepCtl* ctl) {
@@ -1079,10 +1088,7 @@ static int decode_step_ex_impl(ee_ctx* c, float tau, int32_t exit_layer, int32_t
   c->err.clear();
   int r;
   const bool want_logits = dbg && (dbg->logits_readout || dbg->logits_full);
-  if (want_logits && !c->d_dbg_r) {
-    if ((r = dalloc(c, &c->d_dbg_r, static_cast<size_t>(c->cfg.vocab) * 4))) return r;
-    if ((r = dalloc(c, &c->d_dbg_f, static_cast<size_t>(c->cfg.vocab) * 4))) return r;
-  }
+  if (want_logits && (r = ensure_logits(c))) return r;
   const int32_t ft[1] = {input_token};
   const int32_t fe[1] = {force_exit};
   c->nucleus = dbg != nullptr;
@@ -1273,10 +1279,7 @@ static int head_eval_impl(ee_ctx* c, int32_t readout_layer, const float* x, int3
   if (!x) return fail(c, EE_EINVAL, "x is null");
   int r;
   if ((r = check_gate_args(c, INFINITY, readout_layer))) return r;
-  if (out_logits && !c->d_dbg_r) {
-    if ((r = dalloc(c, &c->d_dbg_r, static_cast<size_t>(c->cfg.vocab) * 4))) return r;
-    if ((r = dalloc(c, &c->d_dbg_f, static_cast<size_t>(c->cfg.vocab) * 4))) return r;
-  }
+  if (out_logits && (r = ensure_logits(c))) return r;
   // mail: [x H][logits V]
   const int64_t H = c->cfg.hidden, V = c->cfg.vocab;
   if ((r = ensure_mail(c, (H + (out_logits ? V : 0)) * 4))) return r;

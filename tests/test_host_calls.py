@@ -62,3 +62,51 @@ def test_refused_call_leaves_no_inputs(host, chunk, persistent, call):  # noqa: 
     e.ee_refresh(3)
     assert entries(e) == list(prompt) + [58, 59]
     e.close()
+
+
+def check_calls(host, e, prompt):  # noqa: F811
+    """Every kind of call on a context, with the values the stand-in decoder gives."""
+    import ctypes as C
+
+    import paper_2609_14144_amd._binding as B
+    n = len(prompt)
+    e.ee_reset()
+    assert e.ee_prefill(prompt) == (prompt[-1] + 1) % CFG.vocab
+    e.ee_refresh(n)
+    d = [C.c_void_p() for _ in range(3)]
+    for p in d:
+        assert host.hipMalloc(C.byref(p), C.c_size_t(8)) == 0
+    e._check(B.lib.ee_decode_n_noalloc(e._ctx, 0.5, 1, 2, *d))
+    assert (C.c_int32 * 2).from_address(d[0].value)[:] == [prompt[-1] + 2, prompt[-1] + 3]
+    for p in d:
+        host.hipFree(p)
+    assert list(e.ee_decode_n(0.5, 1, 1)[0]) == [prompt[-1] + 4]
+    assert entries(e) == list(prompt) + [prompt[-1] + 1 + i for i in range(3)]
+
+
+@pytest.mark.parametrize("kind", [0, 1], ids=["pinned", "device"])
+@pytest.mark.parametrize("nth", [1, 2])
+def test_results_that_find_no_memory(host, kind, nth):  # noqa: F811
+    """Calls whose results need more memory than there is are refused; the
+    calls after them work, and so do they once there is memory."""
+    big = replace(CFG, name="big", vocab=40000)
+    from paper_2609_14144_amd import Engine
+    e = Engine(big, 12, page_size=4)
+    e.ee_load_weights(synth.generate_weights(big))
+    prompt = np.arange(90, 94, dtype=np.int32)
+    x = np.full(big.hidden, 9.0, np.float32)
+    e.ee_prefill(prompt)
+    for call in (lambda: e.ee_head_eval(0, x), lambda: e.ee_decode_step_ex(0.5, 1, 5, 0)):
+        host.host_fail_alloc(kind, nth)
+        try:
+            call()
+        except RuntimeError as err:
+            assert err.code == ENOMEM
+        host.host_fail_alloc(kind, 0)
+        check_calls(host, e, prompt)
+    e.ee_reset()
+    e.ee_prefill(prompt)
+    d = e.ee_decode_step_ex(0.5, 1, 5, 0)
+    assert d["token"] == 6 and d["logits_full"][6] == 1.0 and d["logits_readout"].sum() == 1.0
+    assert e.ee_head_eval(0, x)[0] == 10
+    e.close()
