@@ -37,6 +37,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -1245,7 +1246,10 @@ struct RowTask {
   }
 };
 
-template <typename WT, int CPL>
+// LONG: rows of more than 64 * CPL chunks (W_o where A * D is wider than any
+// CPL covers) continue in further pieces. A program of its own: the loop in
+// the ordinary one costs registers that its wide instances do not have.
+template <typename WT, int CPL, bool LONG = false>
 __device__ void phase_rows(const DevParams& p, const WT* W, int rows, int cols, const uint64_t* x,
                            uint64_t* out, const float* bias, int residual, int wg, int nwg, float* xs,
                            RowTask<WT, CPL>& t, const Sync& sy) {
@@ -1262,6 +1266,14 @@ __device__ void phase_rows(const DevParams& p, const WT* W, int rows, int cols, 
     if (r != r0) t.blk.load(W, cols, r, 1, 0, nch);
     float acc[1];
     t.blk.dot(xs, 1, 0, nch, acc);
+    if constexpr (LONG) {
+      for (int c = 64 * CPL; c < nch; c += 64 * CPL) {
+        float more[1];
+        t.blk.load(W, cols, r, 1, c, nch);
+        t.blk.dot(xs, 1, c, nch, more);
+        acc[0] += more[0];
+      }
+    }
     acc[0] = wave_sum(acc[0]);
     if ((threadIdx.x & 63) == 0) {
       float prev = r == r0 ? prev0 : (bias ? bias[r] : 0.f);
@@ -1736,8 +1748,19 @@ __device__ inline Lds lds_carve(const DevParams& p, float* smem) {
 // one-kernel-per-operation drivers
 // ---------------------------------------------------------------------------
 enum OpKind : int {
-  kOpQkv = 0, kOpAttn, kOpWo, kOpGateUp, kOpDown, kOpReadout, kOpHeadR, kOpHeadF, kOpFill
+  kOpQkv = 0, kOpAttn, kOpWo, kOpGateUp, kOpDown, kOpReadout, kOpHeadR, kOpHeadF, kOpFill,
+  kOpWoLong
 };
+
+// Most chunks per lane that the programs are compiled for; create refuses
+// residual streams that need more.
+template <typename WT>
+constexpr int max_chunks_per_lane() { return sizeof(WT) == 2 ? 4 : 2; }
+static int chunks_of(int cols, int wbf16) { return (cols / (wbf16 ? 8 : 4) + 63) / 64; }
+// whether a row of W_o has more chunks than that
+static bool wo_rows_long(const DevParams& p, int wbf16) {
+  return chunks_of(p.A * p.D, wbf16) > (wbf16 ? max_chunks_per_lane<uint16_t>() : max_chunks_per_lane<float>());
+}
 
 template <typename WT, int CPL, int OP>
 __global__ __launch_bounds__(kWG) void k_op(DevParams p, int l, int pos, int step, int skip_if_exited) {
@@ -1752,11 +1775,11 @@ __global__ __launch_bounds__(kWG) void k_op(DevParams p, int l, int pos, int ste
     phase_qkv<WT, CPL>(p, l, pos, step, wg, nwg, s.xs, s.red, t, sy);
   }
   if constexpr (OP == kOpAttn) attn_dispatch<WT, kPosPerWaveLong>(p, l, pos, wg, nwg, s.xs, sy, [](uint32_t) {});
-  if constexpr (OP == kOpWo) {
+  if constexpr (OP == kOpWo || OP == kOpWoLong) {
     const WT* W = static_cast<const WT*>(p.layers[l].wo);
     RowTask<WT, CPL> t;
     t.prefetch(W, p.H, p.A * p.D, wg);
-    phase_rows<WT, CPL>(p, W, p.H, p.A * p.D, p.o, p.h, nullptr, 1, wg, nwg, s.xs, t, sy);
+    phase_rows<WT, CPL, OP == kOpWoLong>(p, W, p.H, p.A * p.D, p.o, p.h, nullptr, 1, wg, nwg, s.xs, t, sy);
   }
   if constexpr (OP == kOpGateUp) {
     GateUpTask<WT, CPL> t;
@@ -1819,6 +1842,12 @@ static hipError_t op(const DevParams& p, int kind, int l, int pos, int step, int
     EE_OP_CASE(kOpHeadR)
     EE_OP_CASE(kOpHeadF)
     EE_OP_CASE(kOpFill)
+    case kOpWoLong:
+      if constexpr (CPL == max_chunks_per_lane<WT>())
+        hipLaunchKernelGGL((k_op<WT, CPL, kOpWoLong>), dim3(op_grid(p, kOpWo, pos, head_wgs)), dim3(kWG), lds, s, p, l, pos,
+                           step, skip);
+      else return hipErrorInvalidValue;
+      break;
 #undef EE_OP_CASE
   }
   return hipGetLastError();
@@ -1830,7 +1859,8 @@ static hipError_t layer_ops(const DevParams& p, int l, int pos, int step, int sk
   hipError_t e;
   if ((e = op<WT, CPL>(p, kOpQkv, l, pos, step, skip, hw, s)) != hipSuccess) return e;
   if ((e = op<WT, CPL>(p, kOpAttn, l, pos, step, skip, hw, s)) != hipSuccess) return e;
-  if ((e = op<WT, CPL>(p, kOpWo, l, pos, step, skip, hw, s)) != hipSuccess) return e;
+  if ((e = op<WT, CPL>(p, wo_rows_long(p, sizeof(WT) == 2) ? kOpWoLong : kOpWo, l, pos, step, skip, hw, s)) != hipSuccess)
+    return e;
   if ((e = op<WT, CPL>(p, kOpGateUp, l, pos, step, skip, hw, s)) != hipSuccess) return e;
   return op<WT, CPL>(p, kOpDown, l, pos, step, skip, hw, s);
 }
@@ -1962,7 +1992,9 @@ __device__ __forceinline__ void run_attn(const DevParams& p, int l, int pos, flo
 // (early_gu false): there the attention's K and V rows are a large read of
 // their own, which the gate/up tiles would delay; they are requested when
 // the gate/up phase starts instead.
-EE_PHASE_FN run_wo(const DevParams& p, int l, float* smem, Tags& tg, GateUpTask<WT, CPL>& gu, bool early_gu) {
+template <typename WT, int CPL, bool LONG>
+__device__ __forceinline__ void run_wo(const DevParams& p, int l, float* smem, Tags& tg, GateUpTask<WT, CPL>& gu,
+                                       bool early_gu) {
   const int wg = opaque_wg();
   const Lds s = lds_carve(p, smem);
   const WT* W = static_cast<const WT*>(p.layers[l].wo);
@@ -1971,8 +2003,8 @@ EE_PHASE_FN run_wo(const DevParams& p, int l, float* smem, Tags& tg, GateUpTask<
   if (early_gu) gu.prefetch(p, l, wg, gridDim.x);
   const uint32_t E = ++tg.ep;
   tl_mark(p, 2 * E);
-  phase_rows<WT, CPL>(p, W, p.H, p.A * p.D, p.o, p.h, nullptr, 1, wg, gridDim.x, s.xs, t,
-                      Sync{true, tg.o, tg.h, E, 0u});
+  phase_rows<WT, CPL, LONG>(p, W, p.H, p.A * p.D, p.o, p.h, nullptr, 1, wg, gridDim.x, s.xs, t,
+                            Sync{true, tg.o, tg.h, E, 0u});
   tl_mark(p, 2 * E + 1);
   tg.h = E;
 }
@@ -2048,14 +2080,14 @@ EE_PHASE_FN run_fill_batch(const DevParams& p, int np, const int* ppos, const ui
 }
 #undef EE_PHASE_FN
 
-template <typename WT, int CPL, int CAP>
+template <typename WT, int CPL, int CAP, bool LONG>
 __device__ __forceinline__ void run_layer(const DevParams& p, int l, int pos, int step, float* smem,
                                           Tags& tg) {
   run_qkv<WT, CPL>(p, l, pos, step, smem, tg);
   run_attn<WT, CPL, CAP>(p, l, pos, smem, tg);
   GateUpTask<WT, CPL> gu;
   const bool early_gu = !(CAP > kPosPerWave && pos >= kLongAttnFrom);
-  run_wo<WT, CPL>(p, l, smem, tg, gu, early_gu);
+  run_wo<WT, CPL, LONG>(p, l, smem, tg, gu, early_gu);
   run_gateup<WT, CPL>(p, l, smem, tg, gu, early_gu);
   run_down<WT, CPL>(p, l, smem, tg);
 }
@@ -2079,7 +2111,8 @@ __constant__ DevParams c_params[kParamSlots];
 // slots are full, and before the launch ends.
 // CAP: attention positions per wave the launch may use (kPosPerWave when
 // every position of the launch lies below kLongAttnFrom).
-template <typename WT, int CPL, int CAP>
+// LONG: rows of W_o longer than CPL covers (phase_rows).
+template <typename WT, int CPL, int CAP, bool LONG = false>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_decode_persistent(
     int slot, int pos0, int n, int prefill) {
   extern __shared__ float smem[];
@@ -2097,7 +2130,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int pos = pos0 + i;
     int exited = 0;
     for (int l = 0; l < p.L; ++l) {
-      run_layer<WT, CPL, CAP>(p, l, pos, i, smem, tg);
+      run_layer<WT, CPL, CAP, LONG>(p, l, pos, i, smem, tg);
       if (l + 1 == Le) {
         run_readout<WT, CPL>(p, smem, tg, lazy ? npend : 0);
         run_head<WT, CPL>(p, 1, i, smem, tg);
@@ -2239,8 +2272,11 @@ hipError_t scratch_address(int device, void** out) {
 // host dispatch over (storage type, chunks per lane)
 // ---------------------------------------------------------------------------
 int chunks_per_lane(const DevParams& p, int wbf16) {
-  const int nch = p.H / (wbf16 ? 8 : 4);
-  return (nch + 63) / 64;
+  // of the residual stream's rows, or of W_o's where those are longer and the
+  // programs have an instance (beyond it: wo_rows_long)
+  const int h = chunks_of(p.H, wbf16);
+  const int most = wbf16 ? max_chunks_per_lane<uint16_t>() : max_chunks_per_lane<float>();
+  return std::max(h, std::min(most, chunks_of(p.A * p.D, wbf16)));
 }
 
 template <typename F>
@@ -2321,7 +2357,13 @@ hipError_t launch_head_eval(const DevParams& p, int wbf16, const float* d_x, int
 }
 
 template <int CAP>
-static const void* persistent_fn_cap(int wbf16, int cpl) {
+static const void* persistent_fn_cap(const DevParams& p, int wbf16) {
+  const int cpl = chunks_per_lane(p, wbf16);
+  if (wo_rows_long(p, wbf16)) {
+    if (cpl > (wbf16 ? max_chunks_per_lane<uint16_t>() : max_chunks_per_lane<float>())) return nullptr;
+    return wbf16 ? reinterpret_cast<const void*>(&k_decode_persistent<uint16_t, max_chunks_per_lane<uint16_t>(), CAP, true>)
+                 : reinterpret_cast<const void*>(&k_decode_persistent<float, max_chunks_per_lane<float>(), CAP, true>);
+  }
   if (wbf16) {
     switch (cpl) {
       case 1: return reinterpret_cast<const void*>(&k_decode_persistent<uint16_t, 1, CAP>);
@@ -2340,14 +2382,13 @@ static const void* persistent_fn_cap(int wbf16, int cpl) {
 
 // positions [pos0, end): the program whose attention items take as many
 // positions per wave as the launch's last position needs
-static const void* persistent_fn(int wbf16, int cpl, int end) {
-  return end > kLongAttnFrom ? persistent_fn_cap<kPosPerWaveLong>(wbf16, cpl)
-                             : persistent_fn_cap<kPosPerWave>(wbf16, cpl);
+static const void* persistent_fn(const DevParams& p, int wbf16, int end) {
+  return end > kLongAttnFrom ? persistent_fn_cap<kPosPerWaveLong>(p, wbf16) : persistent_fn_cap<kPosPerWave>(p, wbf16);
 }
 
 static hipError_t persistent(const PersistentLaunch& L, int pos0, int n, int prefill) {
   const DevParams& p = *L.params_host;
-  const void* fn = persistent_fn(L.wbf16, chunks_per_lane(p, L.wbf16), pos0 + n);
+  const void* fn = persistent_fn(p, L.wbf16, pos0 + n);
   if (!fn || L.slot < 0 || L.slot >= kParamSlots) return hipErrorInvalidValue;
   int slot = L.slot;
   void* args[] = {&slot, &pos0, &n, &prefill};
@@ -2366,8 +2407,8 @@ hipError_t launch_prefill_persistent(const PersistentLaunch& L, int pos0, int n)
 int persistent_max_wgs_per_cu(const DevParams& p, int wbf16, size_t lds) {
   // both programs: the grid must fit either
   int nb = 0, nl = 0;
-  const void* fn = persistent_fn_cap<kPosPerWave>(wbf16, chunks_per_lane(p, wbf16));
-  const void* fl = persistent_fn_cap<kPosPerWaveLong>(wbf16, chunks_per_lane(p, wbf16));
+  const void* fn = persistent_fn_cap<kPosPerWave>(p, wbf16);
+  const void* fl = persistent_fn_cap<kPosPerWaveLong>(p, wbf16);
   if (!fn || !fl || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kWG, lds) != hipSuccess ||
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&nl, fl, kWG, lds) != hipSuccess)
     return 0;
