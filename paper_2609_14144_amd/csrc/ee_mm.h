@@ -139,7 +139,13 @@ struct MmArgs {
 // a total, about as short a chain as a K split over many waves gives; the
 // additions cost the vector ALU 4% of a step's matrix-core time with groups
 // of four steps, and nothing that counts where the weight stream bounds the
-// tile (groups of one or two). One chain over the whole of K had 1.4 times the error.
+// tile (groups of one or two). One chain over the whole of K had 1.4 times the
+// error. Within a K block the smallest term goes first: added to the large sum
+// of the block's first term it would round like it, so a chain's first block
+// rounds once instead of three times, at no cost. Error against 64 bits, over
+// that of the product that split its activations itself (896 to 11008 wide
+// products of three decoders, 13 to 1024 positions): 0.23 to 0.89, largest
+// term first 0.24 to 1.03 (896 wide, 17 to 256 positions).
 // With fp32 weights every product rounds, so each K block of 16 is summed from
 // zero, and its sum added while the next block runs.
 // A workgroup's tile follows from its XCD (blockIdx % 8): every XCD takes a
@@ -218,9 +224,11 @@ __device__ __forceinline__ void mm_tile(const MmArgs& g, Pre&& pre, Epi&& epi) {
       if constexpr (kBlockSum) odd[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
   u32x4 xf[2][CP];
-  auto read_f = [&](int buf, int gi, int d) {  // group gi = (K block gi / kTerms, term gi % kTerms)
+  // group gi = (K block gi / kTerms, its terms from the smallest on)
+  auto read_f = [&](int buf, int gi, int d) {
+    const int f = gi / Op::kTerms * Op::kTerms + Op::kTerms - 1 - gi % Op::kTerms;
 #pragma unroll
-    for (int c = 0; c < CP; ++c) xf[d][c] = Xs[buf][(c * NG + gi) * 64 + lane];
+    for (int c = 0; c < CP; ++c) xf[d][c] = Xs[buf][(c * NG + f) * 64 + lane];
   };
 
   // what the epilogue reads (pre(p, n)): requested here by the small tiles,
