@@ -321,10 +321,12 @@ int begin_call(ee_ctx* c, ee::IoBatch& b, const Imposed& im = Imposed{}) {
 // block that cannot grow stays: every call's last kernel writes to it, also of
 // the calls that need no more room than it has.
 constexpr size_t kMailHead = 256;
+constexpr size_t kMailSteps = 1024;   // decode steps whose results a new context has room for
+constexpr int kForceEntries = 8192;   // imposed inputs a new context has room for
 static_assert(sizeof(ee::StepCtl) <= kMailHead, "the step record fits its place");
 int ensure_mail(ee_ctx* c, size_t bytes) {
   if (kMailHead + bytes <= c->mail_cap) return EE_OK;
-  const size_t cap = std::max<size_t>(kMailHead + bytes, 64 << 10);
+  const size_t cap = kMailHead + bytes;
   void* p = nullptr;
   if (hipHostMalloc(&p, cap) != hipSuccess) {
     (void)hipGetLastError();
@@ -920,7 +922,11 @@ static int create_body(ee_ctx* c, const ee_config* cfg, void* hip_stream, ee_ctx
     return bail(hip_fail(c, he, "hipHostMalloc parameter block"));
   if (c->slot >= 0 && (he = ee::params_address(c->slot, &c->d_params)) != hipSuccess)
     return bail(hip_fail(c, he, "hipGetSymbolAddress of the parameter blocks"));
-  if ((r = ensure_mail(c, 0))) return bail(r);
+  // pinned memory for what calls commonly move, so that a first call does not
+  // stop to allocate it: imposed inputs (and prompts) of the sequence, the
+  // results of some steps and a debug step's vectors and logits
+  if ((r = ensure_mail(c, (5 * kMailSteps + 2 * H + 2 * V) * 4))) return bail(r);
+  if ((r = ensure_force(c, std::min(g.max_seq, kForceEntries)))) return bail(r);
   // without a free parameter slot the context uses the one-kernel-per-operation program
   c->nwg_persistent = (c->max_wgs_per_cu > 0 && c->slot >= 0) ? default_grid(c) : 0;
   c->persistent = c->nwg_persistent > 0;

@@ -89,14 +89,12 @@ def check_calls(host, e, prompt):  # noqa: F811
 def test_results_that_find_no_memory(host, kind, nth):  # noqa: F811
     """Calls whose results need more memory than there is are refused; the
     calls after them work, and so do they once there is memory."""
-    big = replace(CFG, name="big", vocab=40000)
-    from paper_2609_14144_amd import Engine
-    e = Engine(big, 12, page_size=4)
-    e.ee_load_weights(synth.generate_weights(big))
+    e = make(4000)
     prompt = np.arange(90, 94, dtype=np.int32)
-    x = np.full(big.hidden, 9.0, np.float32)
+    x = np.full(CFG.hidden, 9.0, np.float32)
     e.ee_prefill(prompt)
-    for call in (lambda: e.ee_head_eval(0, x), lambda: e.ee_decode_step_ex(0.5, 1, 5, 0)):
+    for call in (lambda: e.ee_head_eval(0, x), lambda: e.ee_decode_step_ex(0.5, 1, 5, 0),
+                 lambda: e.ee_decode_n(0.5, 1, 2000), lambda: e.ee_decode_n(0.5, 1, 3900)):
         host.host_fail_alloc(kind, nth)
         try:
             call()
@@ -109,4 +107,21 @@ def test_results_that_find_no_memory(host, kind, nth):  # noqa: F811
     d = e.ee_decode_step_ex(0.5, 1, 5, 0)
     assert d["token"] == 6 and d["logits_full"][6] == 1.0 and d["logits_readout"].sum() == 1.0
     assert e.ee_head_eval(0, x)[0] == 10
+    assert len(e.ee_decode_n(0.5, 1, 3900)[0]) == 3900
+    e.close()
+
+
+def test_first_calls_pin_no_memory(host):  # noqa: F811
+    """A new context has the pinned memory that its first calls need; only
+    more steps at once than it has room for allocate."""
+    e = make(4000)
+    n = host.host_pinned_allocs()
+    e.ee_prefill(np.arange(50, 58, dtype=np.int32))
+    e.ee_decode_step_ex(0.5, 1, 5, 0)
+    e.ee_head_eval(0, np.ones(CFG.hidden, np.float32))
+    e.ee_decode_n(0.5, 1, 1000)
+    e.ee_decode_n_ex(0.5, 1, 1000, force_tokens=np.full(1000, 7, np.int32), force_exit=np.zeros(1000, np.int32))
+    assert host.host_pinned_allocs() == n
+    e.ee_decode_n(0.5, 1, 1900)
+    assert host.host_pinned_allocs() == n + 1
     e.close()
