@@ -133,7 +133,13 @@ typedef struct ee_ctx ee_ctx;
 
 /* Create a context on the current HIP device. hip_stream is a hipStream_t
  * (for instance torch's current stream) or NULL for a library-owned stream.
- * Allocates the KV pool for max_seq positions and the workspace.
+ * Allocates the weights, the KV pool for max_seq positions and the workspace,
+ * and, where memory allows, a second copy of the layers' matrices in the order
+ * of the matrix cores' operands for the batched passes (as large as the
+ * layers' weights: 2.6 GB at 28 layers of 1536 x 8960 in bf16). A context that
+ * runs out of memory, now or in a later call, does without those copies: its
+ * batched passes then make one matrix's copy before each product (same
+ * results, slower).
  * Errors: EE_EINVAL (shape constraints above), EE_ENOMEM, EE_EHIP. */
 int ee_create(const ee_config* cfg, void* hip_stream, ee_ctx** out);
 

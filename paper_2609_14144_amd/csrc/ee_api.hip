@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
 #include <initializer_list>
 #include <atomic>
 #include <map>
@@ -40,8 +41,10 @@ struct ee_ctx {
   std::map<int, std::pair<void*, float*>> readout;
   ee::LayerW* d_layers = nullptr;
   std::vector<ee::LayerW> h_layers;   // the same pointers, host side (batched pass)
-  std::vector<ee::LayerT> tiled;      // the batched pass's copies of the layers' matrices
+  std::vector<ee::LayerT> tiled;      // the batched pass's copies of the layers' matrices (empty: no room)
   void* tiled_block = nullptr;
+  size_t tiled_bytes = 0;
+  void* spare = nullptr;              // without them: room for one matrix's copy
   std::set<const void*> untiled;      // matrices loaded since their copies were made
   ee::BatchBuffers bbuf{};            // batched full-depth pass (prompt, refresh)
   int prefill_chunk = -1;             // -1: batched in chunks of bbuf.max_positions; 0: one position per step
@@ -173,12 +176,42 @@ int hip_fail(ee_ctx* c, hipError_t e, const char* what) {
     if (e_ != hipSuccess) return hip_fail((ctx), e_, #call);  \
   } while (0)
 
+// Sizes of a layer's tiled copies (wqkv, wo, wgu, wd).
+std::array<size_t, 4> tiled_sizes(const ee_ctx* c) {
+  const ee_config& g = c->cfg;
+  const int H = g.hidden, AD = g.n_q_heads * g.head_dim, QKV = AD + 2 * g.n_kv_heads * g.head_dim;
+  return {ee::batch_weight_bytes(c->wbf16, QKV, H), ee::batch_weight_bytes(c->wbf16, H, AD),
+          ee::batch_weight_bytes(c->wbf16, 2 * g.ffn, H), ee::batch_weight_bytes(c->wbf16, H, g.ffn)};
+}
+
+// The tiled copies take as much memory as the layers' weights and can be made
+// again, so they are what a context goes without when memory runs out: this
+// gives them back and keeps room for one matrix, which each batched pass then
+// fills before each product (the same values, in the same order).
+bool give_back_tiled(ee_ctx* c) {
+  if (!c->tiled_block || hipStreamSynchronize(c->stream) != hipSuccess) return false;
+  (void)hipFree(c->tiled_block);
+  c->tiled_block = nullptr;
+  c->tiled.clear();
+  c->untiled.clear();
+  const auto n = tiled_sizes(c);
+  if (hipMalloc(&c->spare, *std::max_element(n.begin(), n.end())) == hipSuccess) return true;
+  (void)hipGetLastError();
+  c->spare = nullptr;
+  return false;
+}
+
 template <typename T>
 int dalloc(ee_ctx* c, T** p, size_t bytes) {
   void* q = nullptr;
-  if (hipMalloc(&q, bytes ? bytes : 16) != hipSuccess) {
+  const size_t n = bytes ? bytes : 16;
+  if (hipMalloc(&q, n) != hipSuccess) {
     (void)hipGetLastError();
-    return fail(c, EE_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+    q = nullptr;
+    if (n > c->tiled_bytes || !give_back_tiled(c) || hipMalloc(&q, n) != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(c, EE_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+    }
   }
   const hipError_t e = hipMemset(q, 0, bytes ? bytes : 16);
   if (e != hipSuccess) {
@@ -822,22 +855,6 @@ static int create_body(ee_ctx* c, const ee_config* cfg, void* hip_stream, ee_ctx
     if ((r = dalloc(c, &c->g_attn[l], H * 4))) return bail(r);
     if ((r = dalloc(c, &c->g_mlp[l], H * 4))) return bail(r);
   }
-  {
-    // the batched pass's tiled copies, one allocation; the tiling writes every byte, padding included
-    const int h = static_cast<int>(H), ad = static_cast<int>(A * D), f = static_cast<int>(F);
-    const size_t n[4] = {ee::batch_weight_bytes(c->wbf16, static_cast<int>((A + 2 * K) * D), h),
-                         ee::batch_weight_bytes(c->wbf16, h, ad), ee::batch_weight_bytes(c->wbf16, 2 * f, h),
-                         ee::batch_weight_bytes(c->wbf16, h, f)};
-    const size_t layer = n[0] + n[1] + n[2] + n[3];
-    if (hipMalloc(&c->tiled_block, layer * L) != hipSuccess) {
-      (void)hipGetLastError();
-      return bail(fail(c, EE_ENOMEM, "hipMalloc of " + std::to_string(layer * L) + " bytes failed"));
-    }
-    for (size_t l = 0; l < L; ++l) {
-      char* t = static_cast<char*>(c->tiled_block) + layer * l;
-      c->tiled.push_back(ee::LayerT{t, t + n[0], t + n[0] + n[1], t + n[0] + n[1] + n[2]});
-    }
-  }
   if ((r = dalloc(c, &c->g_final, H * 4))) return bail(r);
   if ((r = dalloc(c, &c->d_layers, L * sizeof(ee::LayerW)))) return bail(r);
   {
@@ -933,6 +950,24 @@ static int create_body(ee_ctx* c, const ee_config* cfg, void* hip_stream, ee_ctx
   c->head_wgs = 2 * c->n_cu;
   c->max_parts = std::max(c->head_wgs, c->nwg_persistent);
   if ((r = dalloc(c, &c->d_head_part, static_cast<size_t>(c->max_parts) * ee::kStatFloats * 4))) return bail(r);
+  {
+    // the batched pass's tiled copies, last, in what memory is left: one
+    // allocation (the tiling writes every byte, padding included), or room
+    // for one matrix
+    const auto n = tiled_sizes(c);
+    const size_t layer = n[0] + n[1] + n[2] + n[3];
+    if (hipMalloc(&c->tiled_block, layer * L) == hipSuccess) {
+      c->tiled_bytes = layer * L;
+      for (size_t l = 0; l < L; ++l) {
+        char* t = static_cast<char*>(c->tiled_block) + layer * l;
+        c->tiled.push_back(ee::LayerT{t, t + n[0], t + n[0] + n[1], t + n[0] + n[1] + n[2]});
+      }
+    } else {
+      (void)hipGetLastError();
+      c->tiled_block = nullptr;
+      if ((r = dalloc(c, &c->spare, *std::max_element(n.begin(), n.end())))) return bail(r);
+    }
+  }
   *out = c;
   return EE_OK;
 }
@@ -961,11 +996,16 @@ static int load_weights_impl(ee_ctx* c, const ee_tensor* tensors, int32_t n_tens
 static int batched_full_depth(ee_ctx* c, const int32_t* d_tokens, int n, bool head, int32_t* first,
                               const Imposed& im = Imposed{}) {
   int r;
+  if (c->tiled.empty() && !c->spare) {
+    const auto sizes = tiled_sizes(c);
+    if ((r = dalloc(c, &c->spare, *std::max_element(sizes.begin(), sizes.end())))) return r;
+  }
   if ((r = ensure_pages(c, c->pos + n))) return r;
   ee::BatchPass bp{};
   bp.p = make_params(c, INFINITY, 0);
   bp.layers = c->h_layers.data();
-  bp.tiled = c->tiled.data();
+  bp.tiled = c->tiled.empty() ? nullptr : c->tiled.data();
+  bp.spare = c->spare;
   bp.buf = c->bbuf;
   if (c->prefill_chunk > 0) bp.buf.max_positions = std::min(c->prefill_chunk, c->bbuf.max_positions);
   bp.wbf16 = c->wbf16;
@@ -1426,6 +1466,9 @@ static int reset_impl(ee_ctx* c) {
   return EE_OK;
 }
 
+// Test hook, not in the header: what a context does that runs out of memory.
+int ee_test_give_back_tiled(ee_ctx* c) { return c && give_back_tiled(c) ? EE_OK : EE_ENOMEM; }
+
 const char* ee_last_error(const ee_ctx* c) { return c ? c->err.c_str() : g_create_err.c_str(); }
 
 static void destroy_impl(ee_ctx* c) {
@@ -1437,6 +1480,7 @@ static void destroy_impl(ee_ctx* c) {
   for (void* p : c->wgu) dfree(p);
   for (void* p : c->wd) dfree(p);
   dfree(c->tiled_block);
+  dfree(c->spare);
   for (float* p : c->g_attn) dfree(p);
   for (float* p : c->g_mlp) dfree(p);
   dfree(c->g_final);

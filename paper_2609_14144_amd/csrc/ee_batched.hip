@@ -787,7 +787,12 @@ hipError_t pass(const BatchPass& bp, int pos0, const int32_t* d_tokens, int n, h
     if ((e = reduce_norm<WT>(b, b.X, 0, P, p.H, bp.layers[0].g_attn, p.eps, s)) != hipSuccess) return e;
     for (int l = 0; l < p.L; ++l) {
       const LayerW& lw = bp.layers[l];
-      const LayerT& lt = bp.tiled[l];
+      // a matrix's tiled copy: made once, or here where the context has room for one only
+      auto tiled = [&](const void* w, void* LayerT::*kept, int N, int K, const void** t) {
+        *t = bp.tiled ? bp.tiled[l].*kept : bp.spare;
+        return bp.tiled ? hipSuccess : launch_tile_weights(sizeof(WT) == 2, w, N, K, bp.spare, s);
+      };
+      const void* t = nullptr;
       GemmArgs g{};
       g.P = P;
       g.part = b.gemm_ws;
@@ -831,13 +836,17 @@ hipError_t pass(const BatchPass& bp, int pos0, const int32_t* d_tokens, int n, h
       // the input's planes are in Xp; each residual product's slices are
       // summed by the kernel that prepares the next product's input
       int sp = 0;
-      if ((e = gemm<WT, kEpiQkv>(q, lt.wqkv, b.Xp, b, bp.n_cu, nullptr, s)) != hipSuccess) return e;
+      if ((e = tiled(lw.wqkv, &LayerT::wqkv, q.N, q.K, &t)) != hipSuccess) return e;
+      if ((e = gemm<WT, kEpiQkv>(q, t, b.Xp, b, bp.n_cu, nullptr, s)) != hipSuccess) return e;
       if (stop) break;
       if ((e = attention_d<WT>(at, b, bp.n_cu, s)) != hipSuccess) return e;
-      if ((e = gemm<WT, kEpiResid>(o, lt.wo, b.Op, b, bp.n_cu, &sp, s)) != hipSuccess) return e;
+      if ((e = tiled(lw.wo, &LayerT::wo, o.N, o.K, &t)) != hipSuccess) return e;
+      if ((e = gemm<WT, kEpiResid>(o, t, b.Op, b, bp.n_cu, &sp, s)) != hipSuccess) return e;
       if ((e = reduce_norm<WT>(b, X, sp, at.P, p.H, lw.g_mlp, p.eps, s)) != hipSuccess) return e;
-      if ((e = gemm<WT, kEpiSwiGlu>(gu, lt.wgu, b.Xp, b, bp.n_cu, nullptr, s)) != hipSuccess) return e;
-      if ((e = gemm<WT, kEpiResid>(dn, lt.wd, b.Ap, b, bp.n_cu, &sp, s)) != hipSuccess) return e;
+      if ((e = tiled(lw.wgu, &LayerT::wgu, gu.N, gu.K, &t)) != hipSuccess) return e;
+      if ((e = gemm<WT, kEpiSwiGlu>(gu, t, b.Xp, b, bp.n_cu, nullptr, s)) != hipSuccess) return e;
+      if ((e = tiled(lw.wd, &LayerT::wd, dn.N, dn.K, &t)) != hipSuccess) return e;
+      if ((e = gemm<WT, kEpiResid>(dn, t, b.Ap, b, bp.n_cu, &sp, s)) != hipSuccess) return e;
       if ((e = reduce_norm<WT>(b, X, sp, at.P, p.H, last ? nullptr : bp.layers[l + 1].g_attn, p.eps, s)) != hipSuccess)
         return e;
     }

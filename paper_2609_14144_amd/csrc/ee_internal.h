@@ -161,7 +161,8 @@ struct LayerT {
 struct BatchPass {
   DevParams p;            // shapes, embedding, cache, RoPE tables, block table, token history, step record
   const LayerW* layers;   // host array [L] of the layers' device pointers
-  const LayerT* tiled;    // host array [L]
+  const LayerT* tiled;    // host array [L], or null: the context has no room for the copies
+  void* spare;            // then: room for the copy of one matrix, made before each product
   BatchBuffers buf;
   int wbf16;
   int n_cu;

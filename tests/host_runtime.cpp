@@ -248,7 +248,33 @@ hipError_t launch_prefill_per_op(const DevParams& p, int wbf16, int pos0, const 
 hipError_t launch_prefill_persistent(const PersistentLaunch& L, int pos0, int n) {
   return full_depth(*L.params_host, L.wbf16, pos0, L.params_host->force_tok, n, true);
 }
-hipError_t launch_batched_pass(const BatchPass& bp, int pos0, const int32_t* tok, int n, hipStream_t) {
+// A tiled copy names its matrix and holds its first bytes.
+static void stamp(const void* W, void* T) {
+  memcpy(T, &W, 8);
+  memcpy(static_cast<char*>(T) + 8, W, 8);
+}
+static bool stamped(const void* W, const void* T) {
+  if (!ok(T, 16)) return false;
+  return memcmp(T, &W, 8) == 0 && memcmp(static_cast<const char*>(T) + 8, W, 8) == 0;
+}
+
+hipError_t launch_batched_pass(const BatchPass& bp, int pos0, const int32_t* tok, int n, hipStream_t s) {
+  for (int l = 0; l < bp.p.L; ++l) {
+    const LayerW& w = bp.layers[l];
+    const int H = bp.p.H, AD = bp.p.A * bp.p.D, F = bp.p.F;
+    const struct { const void* w; int n, k; } m[4] = {{w.wqkv, bp.p.qkv_rows, H}, {w.wo, H, AD}, {w.wgu, 2 * F, H}, {w.wd, H, F}};
+    for (int i = 0; i < 4; ++i) {
+      void* t = bp.spare;
+      if (bp.tiled) {
+        const LayerT& lt = bp.tiled[l];
+        void* const kept[4] = {lt.wqkv, lt.wo, lt.wgu, lt.wd};
+        t = kept[i];
+      } else if (launch_tile_weights(bp.wbf16, m[i].w, m[i].n, m[i].k, t, s) != hipSuccess) {
+        return hipErrorInvalidValue;
+      }
+      if (!stamped(m[i].w, t)) ++g_bad;  // a copy that is not there or not up to date
+    }
+  }
   const int row = (n - 1) % bp.buf.max_positions;
   if (!ok(bp.buf.X, 4ll * (row + 1) * bp.p.H)) return hipErrorInvalidValue;
   const hipError_t e = full_depth(bp.p, bp.wbf16, pos0, tok, n, false);
@@ -265,8 +291,10 @@ hipError_t launch_head_eval(const DevParams& p, int, const float* x, int, int, h
 }
 hipError_t launch_tile_weights(int wbf16, const void* W, int N, int K, void* T, hipStream_t) {
   ++g_tilings;
-  return ok(W, static_cast<int64_t>(N) * K * (wbf16 ? 2 : 4)) && ok(T, batch_weight_bytes(wbf16, N, K)) ? hipSuccess
-                                                                                                       : hipErrorInvalidValue;
+  if (!ok(W, static_cast<int64_t>(N) * K * (wbf16 ? 2 : 4)) || !ok(T, batch_weight_bytes(wbf16, N, K)))
+    return hipErrorInvalidValue;
+  stamp(W, T);
+  return hipSuccess;
 }
 size_t batch_weight_bytes(int wbf16, int N, int K) {
   return static_cast<size_t>((N + 15) / 16 * 16) * ((K + 63) / 64 * 64) * (wbf16 ? 2 : 4);

@@ -132,3 +132,31 @@ def test_attention_key_splits():
     e = engine(cfg.name, P + 2, page_size=64, cfg=cfg, weights=w)
     check_prompt(e, o, cfg, synth.prompts(cfg, 91, P), 1, [0, 1023, 1024, 1100, 1279, 1280, 1498, 1499])
     e.close()
+
+
+@pytest.mark.parametrize("name", ["tiny", "tiny_bf16"])
+def test_copies_made_per_product_give_the_same(name):
+    """A context that has given its weight copies back makes them one at a time: the same cache bits and logits,
+    over chunks, a refresh and replaced weights."""
+    from paper_2609_14144_amd import lib
+    cfg = replace(synth.get_config(name), n_layers=3, vocab=600, readout_layers=(1,))
+    w = synth.generate_weights(cfg)
+    prompt = synth.prompts(cfg, 14, 90)
+    other = {"layers.1.w_down": synth.generate_weights(cfg, seed=1)["layers.1.w_down"]}
+    runs = []
+    for give_back in (False, True):
+        e = engine(name, 128, page_size=16, cfg=cfg, weights=w)
+        e.ee_set_prefill_chunk(48)
+        if give_back:
+            assert lib.ee_test_give_back_tiled(e._ctx) == 0
+        got = [e.ee_prefill(prompt)]
+        e.ee_decode_n_ex(0.5, 1, 4, force_tokens=prompt[:4], force_exit=np.ones(4, np.int32))
+        e.ee_refresh(20)
+        e.ee_load_weights(other)
+        e.ee_refresh(7)
+        got.append(np.stack([np.concatenate(e.ee_read_kv(l, t)) for l in range(3) for t in range(94)]))
+        got.append(e.ee_decode_step_ex(0.5, 1, 7, 0)["logits_full"])
+        runs.append(got)
+        e.close()
+    for a, b in zip(*runs):
+        np.testing.assert_array_equal(a, b)

@@ -125,3 +125,64 @@ def test_first_calls_pin_no_memory(host):  # noqa: F811
     e.ee_decode_n(0.5, 1, 1900)
     assert host.host_pinned_allocs() == n + 1
     e.close()
+
+
+def context_bytes(host):  # noqa: F811
+    """Device bytes of a context with room for everything, its copies included, and of one with its weights loaded."""
+    before = host.host_device_bytes()
+    e = make(200)
+    n = host.host_device_bytes() - before
+    e.close()
+    assert host.host_device_bytes() == before
+    return before, n
+
+
+@pytest.mark.parametrize("short", [16, 4096, 0], ids=lambda s: "short_%d" % s)
+def test_context_without_room_for_the_tiled_copies(host, short):  # noqa: F811
+    """The prompt pass's copies of the weights are what a context goes without
+    when memory is short: it is made, and its passes make one copy at a time."""
+    before, need = context_bytes(host)
+    host.host_device_limit(before + need - short)
+    e = make(200)
+    tilings = host.host_tilings()
+    prompt = np.arange(90, 94, dtype=np.int32)
+    e.ee_prefill(prompt)
+    e.ee_refresh(4)
+    assert entries(e) == list(prompt)
+    made = host.host_tilings() - tilings
+    assert made == (2 * 4 * CFG.n_layers if short else 0)
+    w = {"layers.1.wo": 2 * _W["layers.1.wo"] + 1}
+    e.ee_load_weights(w)
+    e.ee_prefill(prompt)
+    e.close()
+
+
+def test_copies_make_room_for_later_buffers(host):  # noqa: F811
+    """A call that finds no memory gives the copies back and goes on."""
+    before, need = context_bytes(host)
+    e = make(200)
+    prompt = np.arange(90, 94, dtype=np.int32)
+    e.ee_prefill(prompt)
+    host.host_device_limit(host.host_device_bytes() + 16)
+    e.ee_decode_n(0.5, 1, 100)     # the ring buffers
+    d = e.ee_decode_step_ex(0.5, 1, 5, 0)
+    assert d["token"] == 6 and d["logits_full"][6] == 1.0
+    tilings = host.host_tilings()
+    e.ee_reset()
+    e.ee_prefill(prompt)
+    assert entries(e) == list(prompt) and host.host_tilings() > tilings
+    e.ee_load_weights(_W)
+    e.ee_prefill(prompt)
+    # a buffer larger than the copies does not cost them
+    e2_limit = host.host_device_bytes() + need
+    host.host_device_limit(e2_limit)
+    f = make(200)
+    f.ee_prefill(prompt)
+    host.host_device_limit(host.host_device_bytes())
+    assert refused(f.ee_stream_probe, 1 << 30) == ENOMEM
+    tilings = host.host_tilings()
+    f.ee_prefill(prompt)
+    assert host.host_tilings() == tilings
+    f.close()
+    e.close()
+    assert host.host_device_bytes() == before
