@@ -948,7 +948,7 @@ static int create_body(ee_ctx* c, const ee_config* cfg, void* hip_stream, ee_ctx
   c->nwg_persistent = (c->max_wgs_per_cu > 0 && c->slot >= 0) ? default_grid(c) : 0;
   c->persistent = c->nwg_persistent > 0;
   c->head_wgs = 2 * c->n_cu;
-  c->max_parts = std::max(c->head_wgs, c->nwg_persistent);
+  c->max_parts = std::max(c->head_wgs, c->n_cu * c->max_wgs_per_cu);  // any grid that can be selected
   if ((r = dalloc(c, &c->d_head_part, static_cast<size_t>(c->max_parts) * ee::kStatFloats * 4))) return bail(r);
   {
     // the batched pass's tiled copies, last, in what memory is left: one

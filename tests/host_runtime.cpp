@@ -31,7 +31,7 @@ size_t g_device_bytes = 0, g_limit = ~size_t(0);
 int g_fail[2] = {0, 0};  // pinned, device: countdown to a failing allocation
 int g_bad = 0;
 int g_pinned_allocs = 0, g_tilings = 0;
-int g_max_wgs = 1;
+int g_max_wgs = 1, g_grid = 0;
 
 hipError_t host_alloc(void** p, size_t bytes, bool device) {
   *p = nullptr;
@@ -147,6 +147,7 @@ int host_bad_ranges() { return g_bad; }
 int host_pinned_allocs() { return g_pinned_allocs; }
 int host_tilings() { return g_tilings; }
 void host_max_wgs(int n) { g_max_wgs = n; }
+int host_last_grid() { return g_grid; }
 int host_live_blocks() { return static_cast<int>(g_blocks.size()); }
 
 hipError_t hipMalloc(void** p, size_t n) { return host_alloc(p, n, true); }
@@ -239,6 +240,7 @@ hipError_t launch_decode_per_op(const DevParams& p, int wbf16, int pos0, int n, 
 }
 hipError_t launch_decode_persistent(const PersistentLaunch& L, int pos0, int n) {
   // every workgroup stores a head partial record
+  g_grid = L.nwg;
   if (!ok(L.params_host->head_part, 4ll * kStatFloats * L.nwg)) return hipErrorInvalidValue;
   return decode(*L.params_host, L.wbf16, pos0, n);
 }

@@ -186,3 +186,19 @@ def test_copies_make_room_for_later_buffers(host):  # noqa: F811
     f.close()
     e.close()
     assert host.host_device_bytes() == before
+
+
+@pytest.mark.parametrize("per_cu", [1, 2, 3, 4])
+def test_every_grid_has_its_partial_records(host, per_cu):  # noqa: F811
+    """Each workgroup of a grid that can be selected has its head partial record."""
+    host.host_max_wgs(4)
+    e = make(64)
+    e.ee_prefill(np.arange(50, 58, dtype=np.int32))
+    for select, grid in ((lambda: e.ee_set_persistent(per_cu), 256 * per_cu),
+                         (lambda: e.ee_set_persistent_grid(256 * per_cu - 3), 256 * per_cu - 3)):
+        select()
+        assert list(e.ee_decode_n_ex(0.5, 1, 2, force_tokens=[4, 5])[0]) == [5, 6]
+        assert host.host_last_grid() == grid
+    assert refused(e.ee_set_persistent, 5) == EINVAL
+    assert refused(e.ee_set_persistent_grid, 4 * 256 + 1) == EINVAL
+    e.close()
