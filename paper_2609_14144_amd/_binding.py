@@ -271,7 +271,8 @@ class Engine:
     def ee_set_persistent(self, wgs_per_cu):
         """0/False: one kernel per operation; True (or a negative value): the
         persistent kernel with as many workgroups per compute unit as can be
-        co-resident; n >= 2: n workgroups per compute unit."""
+        co-resident; n >= 1: n workgroups per compute unit. A new Engine's own
+        choice may be smaller (small models)."""
         if wgs_per_cu is True:
             wgs_per_cu = -1
         self._check(lib.ee_set_persistent(self._ctx, int(wgs_per_cu)))

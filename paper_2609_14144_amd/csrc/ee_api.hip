@@ -443,14 +443,14 @@ bool weights_ready(const ee_ctx* c) {
          c->loaded.count("embed") && c->loaded.count("final_norm");
 }
 
-// Workgroups of the persistent program. Every phase waits for words that all
+// Workgroups of a new context's persistent program. Every phase waits for words that all
 // producing workgroups store, and every workgroup polls for them, so a model
 // too small to give them work runs faster on fewer: tiny shape (2048 gate/up
 // rows, 4 MB head) 61.6 us a step on 64, 67.4 on 256, 64.9 on 48; with a 17
 // MB head 68.4 on 128, 69.8 on 256; with a 51 MB head 83.5 on 128, 80.0 on
 // 256. Hence at least four gate/up rows per wave, 128 KB of the head and
-// one attention item of the longest sequence per workgroup; larger models
-// take as many workgroups as can be co-resident.
+// one attention item per workgroup (of a sequence of max_seq: the grid is
+// chosen once); larger models take as many workgroups as can be co-resident.
 int default_grid(const ee_ctx* c) {
   const ee_config& g = c->cfg;
   const int64_t most = static_cast<int64_t>(c->n_cu) * c->max_wgs_per_cu;
@@ -1396,12 +1396,7 @@ static int set_persistent_impl(ee_ctx* c, int32_t wgs_per_cu) {
     c->persistent = false;
     return EE_OK;
   }
-  if (wgs_per_cu < 0 && c->max_wgs_per_cu > 0 && c->slot >= 0) {
-    c->persistent = true;
-    c->nwg_persistent = default_grid(c);
-    return EE_OK;
-  }
-  if (wgs_per_cu < 0) wgs_per_cu = 1;
+  if (wgs_per_cu < 0) wgs_per_cu = std::max(1, c->max_wgs_per_cu);
   if (wgs_per_cu > c->max_wgs_per_cu)
     return fail(c, EE_EINVAL, "at most " + std::to_string(c->max_wgs_per_cu) +
                                   " persistent workgroups per CU can be co-resident");

@@ -89,3 +89,31 @@ def test_refused_call_leaves_no_inputs(chunk):
         e.close()
     for a, b in zip(*kept):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("name", ["tiny", "tiny_bf16"])
+def test_default_grid_equals_the_full_one(name):
+    """A new engine's own grid (small models: fewer workgroups) gives the cache
+    bits and tokens of the full one; confidences differ by the order in which
+    the head's partial sums (at most two per unit, positive terms) are added:
+    512 roundings of 2^-24."""
+    from paper_2609_14144_amd import Engine
+    from tests.conftest import weights_for
+    cfg = synth.get_config(name)
+    prompt, toks = synth.prompts(cfg, 6, 30), synth.prompts(cfg, 7, 12)
+    runs = []
+    for full in (False, True):
+        e = Engine(cfg, 64, page_size=16)
+        e.ee_load_weights(weights_for(name))
+        if full:
+            e.ee_set_persistent(-1)
+        e.ee_set_prefill_chunk(0)
+        e.ee_prefill(prompt)
+        r = e.ee_decode_n_ex(0.3, 2, 12, force_tokens=toks, force_exit=np.resize([0, 1, 1, 0], 12))
+        kv = np.stack([np.concatenate(e.ee_read_kv(l, t)) for l in range(cfg.n_layers) for t in range(42)])
+        runs.append((kv, r))
+        e.close()
+    (kva, a), (kvb, b) = runs
+    np.testing.assert_array_equal(kva, kvb)
+    np.testing.assert_array_equal(a[0], b[0])
+    np.testing.assert_allclose(a[2], b[2], rtol=512 * 2.0 ** -24)

@@ -202,3 +202,19 @@ def test_every_grid_has_its_partial_records(host, per_cu):  # noqa: F811
     assert refused(e.ee_set_persistent, 5) == EINVAL
     assert refused(e.ee_set_persistent_grid, 4 * 256 + 1) == EINVAL
     e.close()
+
+
+def test_grid_selection(host):  # noqa: F811
+    """A new context's grid follows its shape; a negative count selects as
+    many workgroups as can be co-resident, as the header says."""
+    host.host_max_wgs(2)
+    e = make(64)
+    step = lambda: e.ee_decode_n_ex(0.5, 1, 1, force_tokens=[4])
+    step()
+    assert 1 <= host.host_last_grid() < 256
+    for select in (-1, True):
+        e.ee_set_persistent(0)
+        e.ee_set_persistent(select)
+        step()
+        assert host.host_last_grid() == 512
+    e.close()
