@@ -23,17 +23,16 @@
 //
 // Numerics follow the decode program: weights as stored (bf16 or fp32),
 // activations and accumulation fp32, cache entries rounded to the storage
-// type (round to nearest even), RMSNorm as x * rsqrt(mean(x^2) + eps) * g
-// , e^x in the
-// softmax and SiLU on the hardware base-2 exponential.
+// type (round to nearest even), RMSNorm as x * rsqrt(mean(x^2) + eps) * g,
+// e^x in the softmax and SiLU on the hardware base-2 exponential.
 #include <math.h>
 #include <stdint.h>
 
 #include <algorithm>
-#include <vector>
 
 #include "ee_internal.h"
 #include "ee_mm.h"
+#include "ee_tiles.h"
 
 namespace ee {
 
@@ -598,35 +597,6 @@ __global__ __launch_bounds__(256) void k_bp_attn_merge(AttnArgs a) {
 // ---------------------------------------------------------------------------
 namespace {
 
-// The tile and K split of a product. Every candidate's time is estimated (microseconds; constants fitted to a sweep of tiles and splits
-// over the products of three decoder widths, 16 to 1024 positions, where the
-// choice costs 1.7% over the best on average):
-//   * a unit runs the tile's workgroups in rounds of `occ` (what registers
-//     and LDS allow); a step of a round takes the matrix-core time of its
-//     workgroups or, if longer, the latency of one workgroup's step;
-//   * no less than the weights' read from HBM, nor than the tiles' reads of
-//     weights and activations from the caches;
-//   * the stores of the outputs, and for the residual products the next
-//     kernel's reads of the K slices.
-struct MmTile {
-  int rb, cp, nw, pf, kg, occ;
-};
-template <typename WT>
-double mm_time(const MmTile& t, int P, int N, int K, int splits, bool resid, int n_cu) {
-  constexpr double kStep = 0.02127 * (sizeof(WT) == 2 ? 1.0 : 512.0 / 96.0);  // cycles of a step's instructions
-  constexpr double wb = sizeof(WT), xb = sizeof(WT) == 2 ? 6.0 : 4.0;
-  const double mfma = kStep * t.rb * t.cp * t.nw * t.kg;
-  const double lat = (t.pf == 1 ? 0.733 : 0.262) + 0.377 * mfma / t.kg;
-  const int tiles = ((N + 16 * t.rb * t.nw - 1) / (16 * t.rb * t.nw)) * ((P + 16 * t.cp - 1) / (16 * t.cp)) * splits;
-  const int per_cu = (tiles + n_cu - 1) / n_cu, full = per_cu / t.occ, rest = per_cu % t.occ;
-  const int steps = ((K + 63) / 64 + splits * t.kg - 1) / (splits * t.kg);
-  const double round = full * std::max(t.occ * mfma, lat) + (rest ? std::max(rest * mfma, lat) : 0.0);
-  const double bytes = wb * N * K * ((P + 16 * t.cp - 1) / (16 * t.cp)) +
-                       xb * P * K * ((N + 16 * t.rb * t.nw - 1) / (16 * t.rb * t.nw));
-  const double out = 4.0 * splits * P * N;
-  return 3.2 + std::max({round * steps, wb * N * K / 5.8e6, bytes / 14.8e6}) + out / 8.5e6 + (resid ? out / 5e6 : 0.0);
-}
-
 template <typename WT, int EPI, int RB, int CP, int NW, int PF, int KG>
 hipError_t mm_launch(MmArgs m, const GemmArgs& g, int splits, hipStream_t s) {
   const int steps = m.blocks * MmOp<WT>::kBK / 64;
@@ -640,24 +610,6 @@ hipError_t mm_launch(MmArgs m, const GemmArgs& g, int splits, hipStream_t s) {
   return hipGetLastError();
 }
 
-// 16 positions: the weight stream counts, four steps of it in flight. More
-// positions: 32 to 64 per workgroup. Eight waves of three row blocks share the
-// activations of 64 positions among 384 rows, the fewest cache reads. The QKV
-// product of few positions has few tiles and whole sums to finish: four groups
-// of waves share a tile's K. fp32 weights come with narrow models (at most 512
-// wide), whose few steps want many small tiles.
-template <typename WT>
-struct MmTiles;
-template <>
-struct MmTiles<uint16_t> {
-  static constexpr MmTile t[] = {{1, 1, 8, 4, 1, 3}, {1, 2, 4, 4, 1, 3}, {2, 2, 4, 2, 1, 4}, {3, 2, 4, 2, 1, 3},
-                                 {4, 2, 4, 2, 1, 2}, {3, 3, 4, 2, 1, 2}, {3, 4, 4, 1, 1, 2}, {3, 4, 8, 1, 1, 1},
-                                 {2, 4, 8, 1, 1, 1}, {1, 1, 2, 2, 4, 2}, {1, 2, 2, 2, 4, 1}};
-};
-template <>
-struct MmTiles<float> {
-  static constexpr MmTile t[] = {{1, 1, 4, 2, 1, 4}, {1, 1, 2, 2, 4, 2}, {1, 2, 4, 2, 1, 3}, {2, 2, 4, 2, 1, 2}};
-};
 template <typename WT, int EPI, size_t I = 0>
 hipError_t mm_launch_tile(size_t i, const MmArgs& m, const GemmArgs& g, int splits, hipStream_t s) {
   constexpr size_t n = sizeof(MmTiles<WT>::t) / sizeof(MmTile);
@@ -675,7 +627,6 @@ template <typename WT, int EPI>
 hipError_t gemm(const GemmArgs& g, const void* T, const void* X, const BatchBuffers& b, int n_cu, int* splits,
                 hipStream_t s) {
   constexpr bool kResid = EPI == kEpiResid;
-  constexpr size_t kTiles = sizeof(MmTiles<WT>::t) / sizeof(MmTile);
   MmArgs m{};
   m.W = static_cast<const u32x4*>(T);
   m.X = static_cast<const u32x4*>(X);
@@ -684,36 +635,13 @@ hipError_t gemm(const GemmArgs& g, const void* T, const void* X, const BatchBuff
   m.NB = (g.N + 15) / 16;
   m.PB = (g.P + 15) / 16;
   m.blocks = mm_blocks<WT>(g.K);
-  const int steps = m.blocks * MmOp<WT>::kBK / 64;
-  int most = 1;
-  if (kResid) {
-    const size_t per = static_cast<size_t>(g.P) * g.N;
-    most = static_cast<int>(std::min<size_t>(16, b.gemm_ws_floats / per));
-    if (most < 1) return hipErrorInvalidValue;
-  }
-  size_t best = kTiles;
-  int best_s = 1;
-  double best_t = 0.0;
-  for (size_t i = 0; i < kTiles; ++i) {
-    const MmTile& t = MmTiles<WT>::t[i];
-    if ((t.cp == 1) != (g.P <= 16) || (t.cp == 3 && g.P > 256) || (t.kg > 1 && EPI != kEpiQkv)) continue;
-    for (int sp : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
-      if (sp > most || (sp > 1 && steps / sp < 4) || (t.kg > 1 && steps < 2 * t.kg)) break;
-      const double us = mm_time<WT>(t, g.P, g.N, g.K, sp, kResid, n_cu);
-      // of equals the tile of more waves, which reads less from the caches (1024 positions: gate/up 139 against
-      // 150 us, down 64 against 75)
-      if (best == kTiles || us < best_t || (us == best_t && t.nw > MmTiles<WT>::t[best].nw)) {
-        best = i;
-        best_s = sp;
-        best_t = us;
-      }
-    }
-  }
+  const MmChoice ch = mm_choose<WT>(kResid, EPI == kEpiQkv, g.P, g.N, g.K, b.gemm_ws_floats, n_cu);
+  if (!ch.splits) return hipErrorInvalidValue;
   if (splits) {
-    const int per = (steps + best_s - 1) / best_s;
+    const int steps = m.blocks * MmOp<WT>::kBK / 64, per = (steps + ch.splits - 1) / ch.splits;
     *splits = (steps + per - 1) / per;
   }
-  return mm_launch_tile<WT, EPI>(best, m, g, best_s, s);
+  return mm_launch_tile<WT, EPI>(ch.tile, m, g, ch.splits, s);
 }
 
 template <typename WT>

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import synth
+from tests import tile_shapes
 from tests.gpu_helpers import MARGIN, check_kv, engine, lockstep, oracle_for
 
 pytestmark = pytest.mark.gpu
@@ -160,3 +161,44 @@ def test_copies_made_per_product_give_the_same(name):
         e.close()
     for a, b in zip(*runs):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("shape", tile_shapes.SHAPES, ids=lambda s: "%s_H%d_A%d_K%d_F%d" % s[:5])
+def test_every_tile(shape):
+    """Shapes whose products take every tile of the table in turn (the list is checked against the choice itself on
+    the CPU), with remainders of rows, positions and K."""
+    cfg = tile_shapes.config(shape)
+    w = synth.generate_weights(cfg)
+    for P in shape[-1]:
+        o = oracle_for(cfg.name, P + 2, cfg=cfg, weights=w)
+        e = engine(cfg.name, P + 2, page_size=16, cfg=cfg, weights=w)
+        check_prompt(e, o, cfg, synth.prompts(cfg, 110 + P, P), 1, sorted({0, P // 3, P // 2, max(P - 17, 0), max(P - 2, 0), P - 1}))
+        e.close()
+
+
+@pytest.mark.parametrize("G", range(1, 9))
+def test_attention_head_groups_f32(G):
+    """fp32 caches: every number of query heads per KV head, over two KV heads, about the edges of query blocks and
+    key tiles, in one chunk and in several; K padding (104 of 128) in the products."""
+    cfg = replace(synth.get_config("tiny"), name="heads_f32", n_layers=2, hidden=104, n_q_heads=2 * G, n_kv_heads=2,
+                  head_dim=64, ffn=152, vocab=512, readout_layers=(1,))
+    w = synth.generate_weights(cfg)
+    for P, chunk in ((3, None), (64, None), (97, 48), (197, None)):
+        o = oracle_for(cfg.name, P + 2, cfg=cfg, weights=w)
+        e = engine(cfg.name, P + 2, page_size=16, cfg=cfg, weights=w)
+        if chunk:
+            e.ee_set_prefill_chunk(chunk)
+        check_prompt(e, o, cfg, synth.prompts(cfg, 120 + P, P), 1, sorted({0, 15, 16, 63, 64, P // 2, P - 2, P - 1} & set(range(P))))
+        e.close()
+
+
+def test_attention_key_splits_f32():
+    """As test_attention_key_splits over an fp32 cache."""
+    cfg = replace(synth.get_config("tiny"), name="splits_f32", n_layers=2, hidden=128, n_q_heads=2, n_kv_heads=1,
+                  ffn=256, vocab=512, readout_layers=(1,))
+    w = synth.generate_weights(cfg)
+    P = 1500
+    o = oracle_for(cfg.name, P + 2, cfg=cfg, weights=w)
+    e = engine(cfg.name, P + 2, page_size=64, cfg=cfg, weights=w)
+    check_prompt(e, o, cfg, synth.prompts(cfg, 91, P), 1, [0, 1023, 1024, 1100, 1279, 1280, 1498, 1499])
+    e.close()
