@@ -143,9 +143,11 @@ constexpr uint64_t kWaitTicks = 400000000ull;  // ~4 s of the 100 MHz wall clock
 // ---------------------------------------------------------------------------
 // tagged words. Sync describes a phase's inputs and outputs: with poll set
 // (persistent kernel), an input word is read until it carries its tag; the
-// wait is bounded, and on time-out the abort flag is raised so that every
-// later wait returns at once and the grid drains. Without poll (one kernel
-// per operation) inputs are complete when the kernel starts.
+// wait is bounded, and on time-out the abort flag is raised, which every
+// wait looks at on its 32nd poll and every 32nd after it (wait_over): the
+// current step's remaining waits end within 32 polls each, no further step
+// starts, and the grid drains. Without poll (one kernel per operation) inputs
+// are complete when the kernel starts.
 // ---------------------------------------------------------------------------
 struct Sync {
   bool poll;
@@ -171,9 +173,10 @@ __device__ __noinline__ void raise_abort(const DevParams& p, int err) {
 }
 
 // Whether a wait must end without its word: another wait has timed out, or
-// this one does. Looked at on every 32nd poll only: the abort flag is a round
-// trip to the coherence point of its own, and checked on every poll it
-// doubled the time between two looks at the word (five waits a layer).
+// this one does (its clock starts at the 32nd poll). Looked at on every 32nd
+// poll only: the abort flag is a round trip to the coherence point of its own,
+// and checked on every poll it doubled the time between two looks at the word
+// (five waits a layer).
 __device__ __forceinline__ bool wait_over(const DevParams& p, int pass, uint64_t& t0) {
   if ((pass & 31) != 31) return false;
   if (aborted(p)) return true;
@@ -353,61 +356,50 @@ __device__ inline void stage_coh(const float* x, int n, float* xs) {
   }
 }
 
-// xs[i] = x[i] * rsqrt(mean(x^2) + eps) * (g ? g[i] : 1), x tagged words
-// The gains of the thread's first kGR elements are requested before the
-// input wait, so no global round trip follows it.
-template <int kB = 8>
+// xs[i] = x[i] * rsqrt(mean(x^2) + eps) * (g ? g[i] : 1), x tagged words, n
+// at most kNormWords per thread (ee_create accepts H <= 2048). The gains are
+// requested before the input wait, so no global round trip follows it, and
+// the thread's words stay in registers until they are normalised, so that two
+// barriers follow their arrival (staged raw in LDS first: five).
+constexpr int kNormWords = 4;
+static_assert(kNormWords * kWG >= 64 * 4 * Elem<uint16_t>::N && kNormWords * kWG >= 64 * 2 * Elem<float>::N,
+              "the widest residual stream of either storage type");
 __device__ inline void rmsnorm_stage(const DevParams& p, const uint64_t* x, const float* __restrict__ g,
                                      int n, const Sync& sy, float* xs, float* red) {
-  constexpr int kGR = 4;
-  float gr[kGR];
+  float gr[kNormWords];
 #pragma unroll
-  for (int j = 0; j < kGR; ++j) {
+  for (int j = 0; j < kNormWords; ++j) {
     const int i = static_cast<int>(threadIdx.x) + j * kWG;
     gr[j] = (g && i < n) ? g[i] : 1.f;
   }
-  if (n <= kGR * kWG) {
-    // the thread's words stay in registers until they are normalised: two
-    // barriers follow their arrival instead of five (same sums, same bits)
-    __syncthreads();  // xs and red may still be read by a previous phase
-    const uint32_t tag = sy.tin;
-    const bool poll = sy.poll;
-    uint64_t v[kGR];
+  // Never taken. With this branch the compiler's schedule of the programs
+  // above 4096 positions is the better one (1536 wide, eight layers, us a
+  // fallback step: 355 with it, 361 without; below: 963 and 970 at 28 layers).
+  if (n > kNormWords * kWG) return;
+  __syncthreads();  // xs and red may still be read by a previous phase
+  const uint32_t tag = sy.tin;
+  const bool poll = sy.poll;
+  uint64_t v[kNormWords];
 #pragma unroll
-    for (int k = 0; k < kGR; ++k)
-      v[k] = static_cast<int>(threadIdx.x) + k * kWG < n ? tw_pack(0.f, tag + 1u) : tw_pack(0.f, tag);
-    EE_TW_POLL(kGR, x + k * kWG + threadIdx.x, true)
-    float ss = 0.f;
-#pragma unroll
-    for (int k = 0; k < kGR; ++k)
-      if (static_cast<int>(threadIdx.x) + k * kWG < n) ss = fmaf(tw_val(v[k]), tw_val(v[k]), ss);
-    ss = wave_sum(ss);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    float sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) sum += red[w];
-    const float r = rsqrtf(sum / static_cast<float>(n) + p.eps);
-#pragma unroll
-    for (int k = 0; k < kGR; ++k) {
-      const int i = static_cast<int>(threadIdx.x) + k * kWG;
-      if (i < n) xs[i] = tw_val(v[k]) * r * gr[k];
-    }
-    __syncthreads();
-    return;
-  }
-  __syncthreads();  // xs may still be read by a previous phase
-  tw_stage<kB>(p, x, n, sy.tin, sy.poll, xs);
-  __syncthreads();
+  for (int k = 0; k < kNormWords; ++k)
+    v[k] = static_cast<int>(threadIdx.x) + k * kWG < n ? tw_pack(0.f, tag + 1u) : tw_pack(0.f, tag);
+  EE_TW_POLL(kNormWords, x + k * kWG + threadIdx.x, true)
   float ss = 0.f;
-  for (int i = threadIdx.x; i < n; i += kWG) ss = fmaf(xs[i], xs[i], ss);
-  const float r = rsqrtf(block_sum(ss, red) / static_cast<float>(n) + p.eps);
 #pragma unroll
-  for (int j = 0; j < kGR; ++j) {
-    const int i = static_cast<int>(threadIdx.x) + j * kWG;
-    if (i < n) xs[i] = xs[i] * r * gr[j];
+  for (int k = 0; k < kNormWords; ++k)
+    if (static_cast<int>(threadIdx.x) + k * kWG < n) ss = fmaf(tw_val(v[k]), tw_val(v[k]), ss);
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  float sum = 0.f;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) sum += red[w];
+  const float r = rsqrtf(sum / static_cast<float>(n) + p.eps);
+#pragma unroll
+  for (int k = 0; k < kNormWords; ++k) {
+    const int i = static_cast<int>(threadIdx.x) + k * kWG;
+    if (i < n) xs[i] = tw_val(v[k]) * r * gr[k];
   }
-  for (int i = static_cast<int>(threadIdx.x) + kGR * kWG; i < n; i += kWG) xs[i] = xs[i] * r * (g ? g[i] : 1.f);
   __syncthreads();
 }
 
@@ -1823,6 +1815,9 @@ static int op_grid(const DevParams& p, int op, int pos, int head_wgs) {
   return 1;
 }
 
+template <typename WT>
+hipError_t launch_wo_long(const DevParams& p, int l, int pos, int step, int skip, size_t lds, hipStream_t s);
+
 template <typename WT, int CPL>
 static hipError_t op(const DevParams& p, int kind, int l, int pos, int step, int skip, int head_wgs,
                      hipStream_t s) {
@@ -1843,11 +1838,7 @@ static hipError_t op(const DevParams& p, int kind, int l, int pos, int step, int
     EE_OP_CASE(kOpHeadF)
     EE_OP_CASE(kOpFill)
     case kOpWoLong:
-      if constexpr (CPL == max_chunks_per_lane<WT>())
-        hipLaunchKernelGGL((k_op<WT, CPL, kOpWoLong>), dim3(op_grid(p, kOpWo, pos, head_wgs)), dim3(kWG), lds, s, p, l, pos,
-                           step, skip);
-      else return hipErrorInvalidValue;
-      break;
+      return launch_wo_long<WT>(p, l, pos, step, skip, lds, s);
 #undef EE_OP_CASE
   }
   return hipGetLastError();
@@ -1890,8 +1881,8 @@ static hipError_t step_per_op(const DevParams& p, int pos, int step, int emit_he
 // Two-level grid barrier, split in arrive and wait so that a workgroup can
 // issue the next phase's weight loads in between. Epochs count barriers of
 // the launch; wait() for an epoch already reached returns at once. The wait
-// is bounded: on time-out the abort flag is raised and every later wait
-// returns at once, so the grid always drains.
+// is bounded: on time-out the abort flag is raised and every later wait ends
+// within 32 polls (wait_over), so the grid always drains.
 __device__ inline void bar_arrive(const DevParams& p, uint32_t& epoch, int wg, int nwg) {
   ++epoch;
   wait_stores();
@@ -2356,14 +2347,11 @@ hipError_t launch_head_eval(const DevParams& p, int wbf16, const float* d_x, int
   });
 }
 
+static const void* persistent_fn_long(const DevParams& p, int wbf16, int cap);
 template <int CAP>
 static const void* persistent_fn_cap(const DevParams& p, int wbf16) {
   const int cpl = chunks_per_lane(p, wbf16);
-  if (wo_rows_long(p, wbf16)) {
-    if (cpl > (wbf16 ? max_chunks_per_lane<uint16_t>() : max_chunks_per_lane<float>())) return nullptr;
-    return wbf16 ? reinterpret_cast<const void*>(&k_decode_persistent<uint16_t, max_chunks_per_lane<uint16_t>(), CAP, true>)
-                 : reinterpret_cast<const void*>(&k_decode_persistent<float, max_chunks_per_lane<float>(), CAP, true>);
-  }
+  if (wo_rows_long(p, wbf16)) return persistent_fn_long(p, wbf16, CAP);
   if (wbf16) {
     switch (cpl) {
       case 1: return reinterpret_cast<const void*>(&k_decode_persistent<uint16_t, 1, CAP>);
@@ -2413,6 +2401,31 @@ int persistent_max_wgs_per_cu(const DevParams& p, int wbf16, size_t lds) {
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&nl, fl, kWG, lds) != hipSuccess)
     return 0;
   return nb < nl ? nb : nl;
+}
+
+// ---------------------------------------------------------------------------
+// The instances for rows of W_o longer than any CPL covers, after all others:
+// kernels lie in the code object in the order of their first use, and the
+// same instructions in another place measured up to 1% apart, so the ordinary
+// programs keep theirs.
+// ---------------------------------------------------------------------------
+template <typename WT>
+hipError_t launch_wo_long(const DevParams& p, int l, int pos, int step, int skip, size_t lds, hipStream_t s) {
+  hipLaunchKernelGGL((k_op<WT, max_chunks_per_lane<WT>(), kOpWoLong>), dim3(op_grid(p, kOpWo, pos, 0)), dim3(kWG), lds, s,
+                     p, l, pos, step, skip);
+  return hipGetLastError();
+}
+template hipError_t launch_wo_long<uint16_t>(const DevParams&, int, int, int, int, size_t, hipStream_t);
+template hipError_t launch_wo_long<float>(const DevParams&, int, int, int, int, size_t, hipStream_t);
+
+template <typename WT, int CAP>
+static const void* long_fn() {
+  return reinterpret_cast<const void*>(&k_decode_persistent<WT, max_chunks_per_lane<WT>(), CAP, true>);
+}
+static const void* persistent_fn_long(const DevParams& p, int wbf16, int cap) {
+  if (chunks_per_lane(p, wbf16) > (wbf16 ? max_chunks_per_lane<uint16_t>() : max_chunks_per_lane<float>())) return nullptr;
+  if (cap == kPosPerWaveLong) return wbf16 ? long_fn<uint16_t, kPosPerWaveLong>() : long_fn<float, kPosPerWaveLong>();
+  return wbf16 ? long_fn<uint16_t, kPosPerWave>() : long_fn<float, kPosPerWave>();
 }
 
 }  // namespace ee
