@@ -222,6 +222,10 @@ int dalloc(ee_ctx* c, T** p, size_t bytes) {
   return EE_OK;
 }
 
+// Host memory that kernels read and write in place (k_io): coherent by its
+// own flag, not by the default that the environment may change.
+hipError_t pinned_alloc(void** p, size_t bytes) { return hipHostMalloc(p, bytes, hipHostMallocMapped | hipHostMallocCoherent); }
+
 void dfree(void* p) {
   if (p) (void)hipFree(p);
 }
@@ -361,7 +365,7 @@ int ensure_mail(ee_ctx* c, size_t bytes) {
   if (kMailHead + bytes <= c->mail_cap) return EE_OK;
   const size_t cap = kMailHead + bytes;
   void* p = nullptr;
-  if (hipHostMalloc(&p, cap) != hipSuccess) {
+  if (pinned_alloc(&p, cap) != hipSuccess) {
     (void)hipGetLastError();
     return fail(c, EE_ENOMEM, "hipHostMalloc of " + std::to_string(cap) + " bytes failed");
   }
@@ -427,7 +431,7 @@ int ensure_force(ee_ctx* c, int n) {
   c->force_cap = 0;
   int r;
   void* h = nullptr;
-  if (hipHostMalloc(&h, 2 * sizeof(int32_t) * n) != hipSuccess) {
+  if (pinned_alloc(&h, 2 * sizeof(int32_t) * n) != hipSuccess) {
     (void)hipGetLastError();
     return fail(c, EE_ENOMEM, "hipHostMalloc of imposed inputs failed");
   }
@@ -870,7 +874,7 @@ static int create_body(ee_ctx* c, const ee_config* cfg, void* hip_stream, ee_ctx
   if ((r = dalloc(c, &c->kpool, L * c->layer_stride * es))) return bail(r);
   if ((r = dalloc(c, &c->vpool, L * c->layer_stride * es))) return bail(r);
   if ((r = dalloc(c, &c->d_block_table, sizeof(int32_t) * c->n_pages))) return bail(r);
-  if ((he = hipHostMalloc(reinterpret_cast<void**>(&c->h_block_table), sizeof(int32_t) * c->n_pages)) != hipSuccess)
+  if ((he = pinned_alloc(reinterpret_cast<void**>(&c->h_block_table), sizeof(int32_t) * c->n_pages)) != hipSuccess)
     return bail(hip_fail(c, he, "hipHostMalloc block table"));
   reset_pages(c);
   // RoPE: angle = pos * base^(-2i/D), computed in double, stored as float.
@@ -935,7 +939,7 @@ static int create_body(ee_ctx* c, const ee_config* cfg, void* hip_stream, ee_ctx
   }
   c->max_wgs_per_cu = ee::persistent_max_wgs_per_cu(p, c->wbf16, c->lds);
   c->slot = take_slot();
-  if ((he = hipHostMalloc(reinterpret_cast<void**>(&c->params_pinned), sizeof(DevParams))) != hipSuccess)
+  if ((he = pinned_alloc(reinterpret_cast<void**>(&c->params_pinned), sizeof(DevParams))) != hipSuccess)
     return bail(hip_fail(c, he, "hipHostMalloc parameter block"));
   if (c->slot >= 0 && (he = ee::params_address(c->slot, &c->d_params)) != hipSuccess)
     return bail(hip_fail(c, he, "hipGetSymbolAddress of the parameter blocks"));

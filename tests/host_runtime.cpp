@@ -152,7 +152,10 @@ int host_live_blocks() { return static_cast<int>(g_blocks.size()); }
 
 hipError_t hipMalloc(void** p, size_t n) { return host_alloc(p, n, true); }
 hipError_t hipFree(void* p) { return host_free(p); }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return host_alloc(p, n, false); }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned flags) {
+  if (!(flags & hipHostMallocCoherent)) ++g_bad;  // kernels read and write it in place
+  return host_alloc(p, n, false);
+}
 hipError_t hipHostFree(void* p) { return host_free(p); }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
   memcpy(d, s, n);
