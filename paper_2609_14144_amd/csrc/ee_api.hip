@@ -80,6 +80,7 @@ struct ee_ctx {
   std::vector<float> cal_confs, cal_masses;  // record of the latest calibration (test hook)
   bool fill_lazy = false;  // persistent program: batch the KV fill of consecutive exits
   int fill_slots = 0;      // exit-layer states one batched fill can take
+  bool clearing = false;  // buffers have been allocated whose clearing may still run
   bool nucleus = false;   // steps also measure the readout token's nucleus rank (calibration, debug)
   int force_cap = 0;
   int32_t *d_force_tok = nullptr, *d_force_exit = nullptr;
@@ -219,6 +220,17 @@ int dalloc(ee_ctx* c, T** p, size_t bytes) {
     return hip_fail(c, e, "hipMemset");
   }
   *p = static_cast<T*>(q);
+  c->clearing = true;
+  return EE_OK;
+}
+
+// Buffers are cleared on the null stream, which the context's stream does not
+// wait for: before anything of a call goes to that stream, clearings that the
+// call has asked for are over.
+int await_clearing(ee_ctx* c) {
+  if (!c->clearing) return EE_OK;
+  HIPCHK(c, hipStreamSynchronize(nullptr));
+  c->clearing = false;
   return EE_OK;
 }
 
@@ -344,6 +356,8 @@ struct Imposed {
 // the imposed inputs and new pages (pinned host memory) copied to the device
 // together with whatever the caller has put into b.
 int begin_call(ee_ctx* c, ee::IoBatch& b, const Imposed& im = Imposed{}) {
+  int r;
+  if ((r = await_clearing(c))) return r;
   b.ctl = c->d_ctl;
   b.add(c->d_force_tok, c->h_force, im.up_tok);
   b.add(c->d_force_exit, c->h_force + c->force_cap, im.up_exit);
@@ -555,6 +569,7 @@ int run_steps(ee_ctx* c, float tau, int exit_layer, int n, const Imposed& im, bo
     p.dbg_logits_r = c->d_dbg_r;
     p.dbg_logits_f = c->d_dbg_f;
   }
+  if ((r = await_clearing(c))) return r;
   HIPCHK(c, hipEventRecord(c->ev0, c->stream));
   const bool pers = c->persistent && c->nwg_persistent > 0 && c->slot >= 0;
   ee::IoBatch in{};
@@ -1015,6 +1030,7 @@ static int batched_full_depth(ee_ctx* c, const int32_t* d_tokens, int n, bool he
   bp.wbf16 = c->wbf16;
   bp.n_cu = c->n_cu;
   bp.head = head;
+  if ((r = await_clearing(c))) return r;
   HIPCHK(c, hipEventRecord(c->ev0, c->stream));
   ee::IoBatch in{}, out{};
   if ((r = begin_call(c, in, im))) return r;
@@ -1078,7 +1094,7 @@ static int refresh_impl(ee_ctx* c, int32_t n) {
     }
     return r;
   }
-  if ((r = ensure_force(c, n))) return r;
+  if ((r = ensure_force(c, n)) || (r = await_clearing(c))) return r;
   HIPCHK(c, hipMemcpyAsync(c->d_force_tok, c->d_hist + (c->pos - n), sizeof(int32_t) * n,
                            hipMemcpyDeviceToDevice, c->stream));
   int32_t next = 0;
@@ -1294,7 +1310,8 @@ static int stream_probe_impl(ee_ctx* c, int64_t bytes, int32_t reps, float* out_
     return r;
   }
   std::vector<float> ms;
-  hipError_t he = hipMemsetAsync(buf, 0, static_cast<size_t>(n) * 16, c->stream);
+  hipError_t he = hipStreamSynchronize(nullptr);  // the clearing
+  if (he == hipSuccess) he = hipMemsetAsync(buf, 0, static_cast<size_t>(n) * 16, c->stream);
   for (int i = 0; i <= reps && he == hipSuccess; ++i) {  // launch 0 warms up
     if ((he = hipEventRecord(c->ev0, c->stream)) != hipSuccess) break;
     if ((he = ee::launch_stream_read(buf, n, c->n_cu, sink, c->stream)) != hipSuccess) break;

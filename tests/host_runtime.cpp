@@ -33,6 +33,20 @@ int g_bad = 0;
 int g_pinned_allocs = 0, g_tilings = 0;
 int g_max_wgs = 1, g_grid = 0;
 
+// hipMemset runs on the null stream, which the contexts' streams do not wait
+// for: it happens with the next operation that does, and otherwise as late as
+// after the first kernel or copy of another stream.
+struct Pending {
+  void* p;
+  int v;
+  size_t n;
+};
+std::vector<Pending> g_memsets;
+void settle() {
+  for (const Pending& m : g_memsets) memset(m.p, m.v, m.n);
+  g_memsets.clear();
+}
+
 hipError_t host_alloc(void** p, size_t bytes, bool device) {
   *p = nullptr;
   if (g_fail[device] > 0 && --g_fail[device] == 0) return hipErrorOutOfMemory;
@@ -49,6 +63,7 @@ hipError_t host_alloc(void** p, size_t bytes, bool device) {
 
 hipError_t host_free(void* p) {
   if (!p) return hipSuccess;
+  settle();
   auto it = g_blocks.find(static_cast<char*>(p));
   if (it == g_blocks.end()) {
     ++g_bad;
@@ -158,22 +173,28 @@ hipError_t hipHostMalloc(void** p, size_t n, unsigned flags) {
 }
 hipError_t hipHostFree(void* p) { return host_free(p); }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+  settle();
   memcpy(d, s, n);
   return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
   memmove(d, s, n);
+  settle();
   return hipSuccess;
 }
 hipError_t hipMemcpy2D(void* d, size_t dp, const void* s, size_t sp, size_t w, size_t h, hipMemcpyKind) {
+  settle();
   for (size_t i = 0; i < h; ++i) memcpy(static_cast<char*>(d) + i * dp, static_cast<const char*>(s) + i * sp, w);
   return hipSuccess;
 }
 hipError_t hipMemset(void* d, int v, size_t n) {
+  g_memsets.push_back(Pending{d, v, n});
+  return hipSuccess;
+}
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
   memset(d, v, n);
   return hipSuccess;
 }
-hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { return hipMemset(d, v, n); }
 hipError_t hipGetDevice(int* d) {
   *d = 0;
   return hipSuccess;
@@ -182,8 +203,14 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) {
   *v = 256;
   return hipSuccess;
 }
-hipError_t hipDeviceSynchronize() { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipDeviceSynchronize() {
+  settle();
+  return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t s) {
+  if (!s) settle();
+  return hipSuccess;
+}
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
   *s = reinterpret_cast<hipStream_t>(1);
   return hipSuccess;
@@ -228,6 +255,7 @@ hipError_t launch_io(const IoBatch& b, hipStream_t) {
       else static_cast<uint32_t*>(q.dst)[i] = v;
     }
   }
+  settle();
   return hipSuccess;
 }
 hipError_t params_address(int slot, void** out) {

@@ -218,3 +218,26 @@ def test_grid_selection(host):  # noqa: F811
         step()
         assert host.host_last_grid() == 512
     e.close()
+
+
+@pytest.mark.parametrize("chunk", [0, None], ids=["stepwise", "batched"])
+@pytest.mark.parametrize("how", ["grown", "given_back"])
+def test_new_buffers_are_cleared_before_they_are_written(host, chunk, how):  # noqa: F811
+    """The clearing of a buffer that a call allocates is over before the
+    call's own kernels and copies write to it: longer prompts and imposed steps
+    than a new context has room for, a refresh of all of them, and a pass
+    whose room for one matrix had to be found again."""
+    n = 9000
+    e = make(n + 64, chunk)
+    prompt = (np.arange(n) % 190 + 1).astype(np.int32)
+    if how == "given_back":
+        host.host_fail_alloc(1, 1)   # no room for one matrix either
+        assert host.ee_test_give_back_tiled(e._ctx) != 0
+        prompt = prompt[:8]
+    assert e.ee_prefill(prompt) == prompt[-1] + 1
+    forced = np.full(5, 9, np.int32)
+    assert list(e.ee_decode_n_ex(0.5, 1, 5, force_tokens=forced)[0]) == [10] * 5
+    e.ee_refresh(len(prompt) + 5)
+    assert [int(e.ee_read_kv(1, t)[0][0]) for t in (0, 1, 7, len(prompt) - 1, len(prompt) + 4)] == \
+        [int(prompt[t]) for t in (0, 1, 7, len(prompt) - 1)] + [9]
+    e.close()
